@@ -186,7 +186,11 @@ typedef struct grtx_rays {
  * for every capacity. The lists live in a per-stream pool of
  * 512 B x (288 + 2 x defer + 2 x evict + k) per wave in flight (3072 waves at k <= 32:
  * about 1.7 GB with 256/128, 49 GB with 12288/3072), kept for later calls on the stream;
- * RESTART keeps no lists and takes 512 B x (288 + k) per wave. */
+ * RESTART keeps no lists and takes 512 B x (288 + k) per wave.
+ * A CHECKPOINT launch over a SPHERE_INSTANCE structure that writes no counters (stats NULL)
+ * gives sixteen lanes to each ray and gathers its hits in batches of its own: k and the
+ * list capacities are checked but do not enter, and the pool takes 32 KB per wave in
+ * flight (about 130 MB). The outputs are the same bits as with counters. */
 typedef struct grtx_trace_params {
   int32_t k;
   float T_min;
@@ -198,7 +202,8 @@ typedef struct grtx_trace_params {
   int32_t reserved;
 } grtx_trace_params;
 
-/* Per-ray counters written to grtx_trace_outputs.stats. They count the work a ray took.
+/* Per-ray counters written to grtx_trace_outputs.stats. They count the work a ray took in
+ * the launch that writes them (k-buffer rounds, one lane per ray).
  * Where a checkpoint list fills and is compacted, the point at which that happens follows
  * the launch's scheduling, so the counts of entries written and of the work after it can
  * differ between launches, and so can the rounds of a ray that then restarts from the
@@ -295,8 +300,8 @@ grtx_status grtx_trace(const grtx_bvh* bvh, const grtx_rays* rays, const grtx_tr
  * is a static array of GRTX_NOALLOC_SCRATCH_MB MiB that each device running the library
  * holds from the library's first use on it until the process ends. As many persistent
  * workgroups run as their lists fit in it (about 2.1 MiB per workgroup at k = 16 with
- * the 256/128 default capacities, 11 MiB with 2048/512), so throughput can be below
- * grtx_trace's; image rays are taken in row-major tile order and other rays in the
+ * the 256/128 default capacities, 11 MiB with 2048/512; every workgroup of a launch that
+ * gives sixteen lanes to a ray fits), so throughput can be below grtx_trace's; image rays are taken in row-major tile order and other rays in the
  * caller's order (grtx_trace orders both by estimated cost). GRTX_ERR_CAPACITY when not
  * even one workgroup's lists fit (lower defer_capacity / evict_capacity). Every call on a
  * device uses that device's one array: calls that overlap on one device (different

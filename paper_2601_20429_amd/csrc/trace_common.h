@@ -76,27 +76,38 @@ constexpr float SH31 = (float)(cx_sqrt(2.0) * K(3, 1, 1.0 / 12.0) * 0.5);    // 
 constexpr float SH32 = (float)(cx_sqrt(2.0) * K(3, 2, 1.0 / 120.0) * 15.0);  // z (x^2-y^2), 2xyz
 constexpr float SH33 = (float)(cx_sqrt(2.0) * K(3, 3, 1.0 / 720.0) * 15.0);  // -(x^3-3xy^2), -(3x^2y-y^3)
 
+// Contraction is written out (fmaf, and none elsewhere) here and in the functions below: the
+// trace's kernels share them, and an image must not depend on which kernel rendered it.
 __device__ __forceinline__ void sh_basis(float x, float y, float z, int L, float* Y) {
+#pragma clang fp contract(off)
   Y[0] = SH00;
   if (L < 1) return;
   Y[1] = -SH1 * y;
   Y[2] = SH1 * z;
   Y[3] = -SH1 * x;
   if (L < 2) return;
-  float xx = x * x, yy = y * y, zz = z * z;
+  const float xx = x * x, yy = y * y, zz = z * z;
+  const float xxyy = fmaf(x, x, -yy);
   Y[4] = SH22 * 2.f * x * y;
   Y[5] = -SH21 * y * z;
-  Y[6] = SH20 * (3.f * zz - 1.f);
+  Y[6] = SH20 * fmaf(zz, 3.f, -1.f);
   Y[7] = -SH21 * x * z;
-  Y[8] = SH22 * (xx - yy);
+  Y[8] = SH22 * xxyy;
   if (L < 3) return;
-  Y[9] = -SH33 * (3.f * xx * y - yy * y);
+  const float zz15 = fmaf(zz, 15.f, -3.f);
+  Y[9] = -SH33 * fmaf(y, 3.f * xx, -(y * yy));
   Y[10] = SH32 * 2.f * x * y * z;
-  Y[11] = -SH31 * y * (15.f * zz - 3.f);
-  Y[12] = SH30 * (5.f * zz * z - 3.f * z);
-  Y[13] = -SH31 * x * (15.f * zz - 3.f);
-  Y[14] = SH32 * z * (xx - yy);
-  Y[15] = -SH33 * (xx * x - 3.f * x * yy);
+  Y[11] = -SH31 * y * zz15;
+  Y[12] = SH30 * fmaf(z, 5.f * zz, -3.f * z);
+  Y[13] = -SH31 * x * zz15;
+  Y[14] = SH32 * z * xxyy;
+  Y[15] = -SH33 * fmaf(x, xx, -3.f * x * yy);
+}
+// The basis at direction d, made unit here.
+__device__ __forceinline__ void sh_basis_of(float dx, float dy, float dz, int L, float* Y) {
+#pragma clang fp contract(off)
+  const float dn = rsqrtf(fmaf(dz, dz, fmaf(dy, dy, dx * dx)));
+  sh_basis(dx * dn, dy * dn, dz * dn, L, Y);
 }
 
 // Sphere leaf: ray in the unit-sphere frame of instance record (r0, r1, r2).
@@ -106,19 +117,81 @@ struct SphereHit {
 
 __device__ __forceinline__ SphereHit sphere_terms(float4 r0, float4 r1, float4 r2, float ox, float oy, float oz,
                                                   float dx, float dy, float dz) {
-  float fx = ox - r0.w, fy = oy - r1.w, fz = oz - r2.w;
-  float ux = r0.x * fx + r0.y * fy + r0.z * fz;
-  float uy = r1.x * fx + r1.y * fy + r1.z * fz;
-  float uz = r2.x * fx + r2.y * fy + r2.z * fz;
-  float vx = r0.x * dx + r0.y * dy + r0.z * dz;
-  float vy = r1.x * dx + r1.y * dy + r1.z * dz;
-  float vz = r2.x * dx + r2.y * dy + r2.z * dz;
-  float cx = uy * vz - uz * vy, cy = uz * vx - ux * vz, cz = ux * vy - uy * vx;
+#pragma clang fp contract(off)
+  const float fx = ox - r0.w, fy = oy - r1.w, fz = oz - r2.w;
+  auto dot = [](float ax, float ay, float az, float bx, float by, float bz) __attribute__((always_inline)) {
+#pragma clang fp contract(off)
+    return fmaf(az, bz, fmaf(ax, bx, ay * by));
+  };
+  const float ux = dot(r0.x, r0.y, r0.z, fx, fy, fz);
+  const float uy = dot(r1.x, r1.y, r1.z, fx, fy, fz);
+  const float uz = dot(r2.x, r2.y, r2.z, fx, fy, fz);
+  const float vx = dot(r0.x, r0.y, r0.z, dx, dy, dz);
+  const float vy = dot(r1.x, r1.y, r1.z, dx, dy, dz);
+  const float vz = dot(r2.x, r2.y, r2.z, dx, dy, dz);
+  const float cx = fmaf(uy, vz, -(uz * vy)), cy = fmaf(uz, vx, -(ux * vz)), cz = fmaf(ux, vy, -(uy * vx));
   SphereHit h;
-  h.a = vx * vx + vy * vy + vz * vz;
-  h.b = ux * vx + uy * vy + uz * vz;
-  h.c2 = cx * cx + cy * cy + cz * cz;
+  h.a = dot(vx, vy, vz, vx, vy, vz);
+  h.b = dot(ux, uy, uz, vx, vy, vz);
+  h.c2 = dot(cx, cy, cz, cx, cy, cz);
   return h;
+}
+
+// Distance at which the ray of `h` (one that meets the sphere) enters it.
+__device__ __forceinline__ float sphere_entry(const SphereHit& h) {
+#pragma clang fp contract(off)
+  return (-h.b - __builtin_amdgcn_sqrtf(fmaxf(h.a - h.c2, 0.f))) * __builtin_amdgcn_rcpf(h.a);
+}
+
+// Eq. 2 at the point of maximum response: alpha, 1 - alpha, and minus its distance. Hardware
+// reciprocal and exp2 (about 1 ulp each); the exponent lies in [-log2(o / alpha_min), 0], far
+// from the denormal range a library exp2f guards.
+struct HitAlpha {
+  float alpha, rest, neg_t;
+};
+__device__ __forceinline__ HitAlpha hit_alpha(const SphereHit& h, float4 r3) {
+#pragma clang fp contract(off)
+  const float inva = __builtin_amdgcn_rcpf(h.a);
+  const float e = __builtin_amdgcn_exp2f(-r3.y * (h.c2 * inva));
+  HitAlpha q;
+  q.alpha = r3.x * e;
+  q.rest = fmaf(-r3.x, e, 1.f);
+  q.neg_t = h.b * inva;
+  return q;
+}
+
+// Colour of Gaussian `gid` for a ray with SH basis Y: 0.5 + sum Y sh per channel.
+__device__ __forceinline__ void sh_colour(const float* __restrict__ sh, uint32_t gid, int degree, const float* Y,
+                                          float c[3]) {
+#pragma clang fp contract(off)
+  c[0] = c[1] = c[2] = 0.5f;
+  const int ncoef = (degree + 1) * (degree + 1);
+  if (degree == 3) {
+    // all twelve loads in flight at once, then the sums
+    const float4* sp4 = reinterpret_cast<const float4*>(sh + (int64_t)gid * 48);
+    float4 shv[12];
+#pragma unroll
+    for (int q = 0; q < 12; ++q) shv[q] = sp4[q];
+#pragma unroll
+    for (int q = 0; q < 12; ++q) {
+      const float* vv = reinterpret_cast<const float*>(&shv[q]);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int f = 4 * q + e;
+        c[f % 3] = fmaf(Y[f / 3], vv[e], c[f % 3]);
+      }
+    }
+  } else {
+    const float* sc = sh + (int64_t)gid * 3 * ncoef;
+#pragma unroll
+    for (int f = 0; f < 16; ++f) {
+      if (f < ncoef) {
+        c[0] = fmaf(Y[f], sc[3 * f + 0], c[0]);
+        c[1] = fmaf(Y[f], sc[3 * f + 1], c[1]);
+        c[2] = fmaf(Y[f], sc[3 * f + 2], c[2]);
+      }
+    }
+  }
 }
 
 }  // namespace

@@ -1,0 +1,115 @@
+"""The sixteen-lanes-per-ray trace kernel against the one-lane-per-ray kernel: a launch that
+writes per-ray counters runs the latter, one without them the former, and every output bit
+and hit id must be the same. The cases sit where the former's structures change: trees of one
+leaf and a few, stacks and hit lists that overflow, rounds cut short, ray bounds and starting
+transmittances, waves with idle groups. Needs an MI355X."""
+import numpy as np
+import pytest
+
+from paper_2601_20429_amd import inputs
+
+pytestmark = pytest.mark.gpu
+torch = pytest.importorskip("torch")
+from paper_2601_20429_amd import grtx  # noqa: E402
+
+AMIN = float(np.float32(1.0 / 255.0))
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _gpu():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+
+
+def scene_of(n, seed, degree=3, spread=0.2, scale=-3.0, opacity=0.0, repeat=1):
+    rng = np.random.default_rng(seed)
+    m = (n + repeat - 1) // repeat
+    means = np.repeat(rng.normal(0.0, spread, (m, 3)), repeat, 0)[:n]
+    f = lambda a: np.ascontiguousarray(a, dtype=np.float32)
+    q = rng.standard_normal((n, 4))
+    return inputs.Scene(f(means), f(np.exp(rng.normal(scale, 0.5, (n, 3)))), f(q / np.linalg.norm(q, axis=1)[:, None]),
+                        f(1.0 / (1.0 + np.exp(-rng.normal(opacity, 1.5, n)))),
+                        f(rng.normal(0.0, 0.3, (n, (degree + 1) ** 2, 3))), degree)
+
+
+def rays_of(n, seed, box=0.6):
+    return tuple(torch.from_numpy(a).cuda() for a in inputs.incoherent_rays(seed, n, box))
+
+
+def check(scene, o, d, cap=512, k=16, ref_mode=grtx.CHECKPOINT, **kw):
+    bvh = grtx.build(grtx.SceneTensors.from_scene(scene, "cuda"), alpha_min=AMIN)
+    ref = grtx.trace(bvh, o, d, k=k, hit_capacity=cap, stats=True, mode=ref_mode, **kw)
+    got = grtx.trace(bvh, o, d, k=k, hit_capacity=cap, **kw)
+    torch.cuda.synchronize()
+    for key in ("rgb", "depth", "opacity", "hit_ids", "hit_counts"):
+        assert torch.equal(got[key], ref[key]), key
+    return ref
+
+
+@pytest.mark.parametrize("n", [1, 2, 3, 4, 5, 16, 17, 65, 257, 1000])
+@pytest.mark.parametrize("rays", [1, 3, 5, 63, 257])
+def test_small_trees_and_few_rays(n, rays):
+    check(scene_of(n, 10 + n, degree=n % 4), *rays_of(rays, n + rays))
+
+
+@pytest.mark.parametrize("opacity,t_min", [(-6.0, 0.0), (-6.0, 1e-3), (-3.0, 1e-3), (3.0, 1e-3), (6.0, 0.5)])
+def test_long_lists_and_cut_rounds(opacity, t_min):
+    # faint Gaussians: hundreds of hits a ray, more than a list holds; opaque ones: rays that
+    # end after a hit or two
+    ref = check(scene_of(20_000, 3, opacity=opacity), *rays_of(700, 4), cap=2048, T_min=t_min)
+    assert opacity > -6.0 or int(ref["hit_counts"].max()) > 160
+
+
+def test_stacks_beyond_lds():
+    # large overlapping Gaussians around the origins: a ray enters most of 60,000 boxes
+    check(scene_of(60_000, 5, spread=0.05, scale=-2.0, opacity=-5.0, degree=1), *rays_of(64, 6, box=0.02), cap=4096)
+
+
+@pytest.mark.parametrize("repeat", [8, 257])
+def test_equal_distances(repeat):
+    # the same centres many times: keys tie in distance and are told apart by their leaf (more
+    # ties than the one-lane kernel's lists hold, so it restarts each round from the root here)
+    sc = scene_of(2056, 7, repeat=repeat, opacity=-2.0)
+    sc.scales[:] = np.repeat(sc.scales[::repeat], repeat, 0)[:sc.n]
+    sc.quats[:] = np.repeat(sc.quats[::repeat], repeat, 0)[:sc.n]
+    sc.opacities[:] = np.repeat(sc.opacities[::repeat], repeat, 0)[:sc.n]
+    check(sc, *rays_of(300, 8), cap=1024, T_min=0.0, ref_mode=grtx.RESTART)
+
+
+@pytest.mark.parametrize("degree", [0, 1, 2, 3])
+def test_bounds_and_starting_transmittance(degree):
+    o, d = rays_of(900, 9)
+    g = torch.Generator(device="cuda").manual_seed(degree)
+    far = torch.rand(900, device="cuda", generator=g) * 2.0
+    far[::7] = float("inf")
+    trans = torch.rand(900, device="cuda", generator=g)
+    trans[::11] = 0.0
+    check(scene_of(5000, 20 + degree, degree), o, d, t_far=far, transmittance=trans, bg=(0.2, 0.5, 0.7), k=4)
+    check(scene_of(5000, 30 + degree, degree), o, d, t_near=0.3, bg=(0.2, 0.5, 0.7), cap=3)
+
+
+@pytest.mark.parametrize("width,height,free", [(1, 1, 0), (7, 9, 0), (33, 17, 5), (64, 64, 130)])
+def test_ragged_images_and_continuations(width, height, free):
+    cam = inputs.orbit_camera(width, height, eye=(0.0, -1.5, 0.2))
+    po, pd = grtx.pinhole_rays(cam)
+    fo, fd = rays_of(max(free, 1), 11)
+    o, d = torch.cat([fo[:free], po]), torch.cat([fd[:free], pd])
+    sc = scene_of(3000, 12)
+    check(sc, o, d, image_width=width, image_begin=free)
+    ob = grtx.object_rays({"sphere": (0.1, -0.3, 0.0, 0.25, 1.5), "mirror": (-0.2, 0.1, 0.0, 0.3, 0.2, 0, 0, 0, 0.4),
+                           "eps": 1e-4}, o, d)
+    check(sc, o, d, image_width=width, image_begin=free, t_far=ob["t_far"], continuation=ob)
+
+
+def test_degenerate_rays():
+    o, d = rays_of(64, 13)
+    o[::5] = 1e30
+    d[1::5] = 0.0
+    d[2::5, 0] = 0.0
+    o[3::5] = float("nan")
+    d[4::20] = float("nan")
+    bvh = grtx.build(grtx.SceneTensors.from_scene(scene_of(2000, 14), "cuda"), alpha_min=AMIN)
+    ref = grtx.trace(bvh, o, d, stats=True)
+    got = grtx.trace(bvh, o, d)
+    for key in ("rgb", "depth", "opacity"):
+        assert torch.equal(torch.nan_to_num(got[key], 7.0), torch.nan_to_num(ref[key], 7.0)), key
