@@ -1815,16 +1815,4 @@ grtx_status sort_by_key_into(uint64_t* keys, uint32_t* vals, uint64_t* tkeys, ui
   return radix_sort(keys, vals, tkeys, tvals, n, sc, s, passes, n_dev, kres, vres);
 }
 
-grtx_status sort_by_key(uint64_t* keys, uint32_t* vals, int64_t n, int key_bits, hipStream_t s,
-                        const uint32_t* n_dev) {
-  if (n <= 1) return GRTX_OK;
-  Scratch sc(s);
-  uint64_t* tkeys = nullptr;
-  uint32_t* tvals = nullptr;
-  GRTX_TRY(sc.get(&tkeys, n));
-  GRTX_TRY(sc.get(&tvals, n));
-  const int passes = std::max(1, std::min(8, (key_bits + 7) / 8));
-  return radix_sort(keys, vals, tkeys, tvals, n, sc, s, passes, n_dev);
-}
-
 }  // namespace grtx

@@ -320,12 +320,10 @@ class Scratch {
 // Device utilities of the build, reused by the backward pass (stream-ordered scratch).
 // Exclusive prefix sum of n uint32 values.
 grtx_status exclusive_scan_u32(const uint32_t* in, uint32_t* out, int64_t n, hipStream_t s);
-// Stable LSD radix sort of (keys, vals) by the low key_bits bits of the keys, in place. With
-// `n_dev` the first *n_dev (at most n) pairs are sorted, n being the host's bound.
-grtx_status sort_by_key(uint64_t* keys, uint32_t* vals, int64_t n, int key_bits, hipStream_t s,
-                        const uint32_t* n_dev = nullptr);
-// The same with caller-owned temporaries (tkeys, tvals of n entries); *kres / *vres receive
-// the arrays that hold the result (the inputs or the temporaries), so nothing is copied.
+// Stable LSD radix sort of (keys, vals) by the low key_bits bits of the keys, with caller-owned
+// temporaries (tkeys, tvals of n entries); *kres / *vres receive the arrays that hold the result
+// (the inputs or the temporaries). With `n_dev` the first *n_dev (at most n) pairs are sorted, n
+// being the host's bound.
 grtx_status sort_by_key_into(uint64_t* keys, uint32_t* vals, uint64_t* tkeys, uint32_t* tvals, int64_t n,
                              int key_bits, hipStream_t s, const uint32_t* n_dev, uint64_t** kres, uint32_t** vres);
 
