@@ -425,8 +425,8 @@ grtx_status grtx_trace_backward(const grtx_bvh* bvh, const grtx_gaussians* g, co
  * ray is traced as in grtx_trace, Sec. III-A and IV-B).
  * A worker thread admits queued requests first come, first served while their outputs
  * fit the memory budget and publishes each admitted request to a queue in host memory.
- * One kernel launch, resident on all but a few CUs, takes the published requests' 8x8
- * pixel tiles as its lanes fall idle, generates each pixel's ray from the request's
+ * One kernel launch, resident on three quarters of every CU, takes the published requests'
+ * 8x8 pixel tiles as its lanes fall idle, generates each pixel's ray from the request's
  * camera, and flags the request in host memory when its last pixel is written; a request
  * published while the kernel runs joins it. The launch ends once no work has been taken
  * for `idle_exit_us` (freeing the device for other work) and the next publication starts
@@ -435,12 +435,13 @@ grtx_status grtx_trace_backward(const grtx_bvh* bvh, const grtx_gaussians* g, co
  * ------------------------------------------------------------------------------------- */
 typedef struct grtx_server grtx_server;
 
-/* memory_budget: device bytes the server may hold (the serving kernel's checkpoint pool,
- *   about 8.3 GB at k <= 32 for 2048 deferred nodes and 512 evicted hits per lane,
- *   the scene set copy, and per admitted request its outputs until released; the outputs
+/* memory_budget: device bytes the server may hold (a fixed share for the serving kernel,
+ *   about 8.3 GB at k <= 32, the checkpoint lists of one lane per ray with 2048 deferred
+ *   nodes and 512 evicted hits, of which the kernel takes 270 MB; the scene set copy, and per admitted request its outputs until released; the outputs
  *   live in an arena grown in chunks of at least 1 GiB within the budget).
  * k, T_min, mode, bg: as in grtx_trace_params, for every request (mode CHECKPOINT or
- *   RESTART).
+ *   RESTART; neither k nor the mode enters: every ray has sixteen lanes, see
+ *   grtx_trace_params).
  * max_request_rays: pixels per request (0 = 2^22, also the largest accepted); larger
  *   requests are refused.
  * idle_exit_us: how long the kernel waits for new work before it ends (0 = 2000). */

@@ -85,12 +85,6 @@ __device__ __forceinline__ int density_cell(float x, float y, float z, const flo
          kDensityRes * (density_axis(y, box[1], box[4]) + kDensityRes * density_axis(z, box[2], box[5]));
 }
 constexpr uint32_t kNoChild = 0xFFFFFFFFu;
-// Per-ray capacities of the checkpoint (deferred node) and eviction lists of the serving
-// kernel's pool (the trace's defaults live with the trace kernel): 2048/512 served the
-// four-scene mix 2% faster than 1024/256 (fewer list compactions on the 1M and 3M
-// scenes), and 4096/1024 no faster.
-constexpr int kServeDeferCap = 2048;
-constexpr int kServeEvictCap = 512;
 
 // ---------------------------------------------------------------------------------------
 // Serving work queue
@@ -259,12 +253,10 @@ grtx_status trace_single_round(const TraceScene& b, const grtx_rays* r, const gr
 // The serving kernel: a persistent trace launch over the merged scene set that takes
 // requests from the work queue until the host stops it or no work has been taken for
 // `idle_ticks` of the device wall clock (then it sets `closing` and its waves exit once
-// their rays are done). `pool` holds serve_pool_bytes(k) bytes.
+// their rays are done). `pool` holds serve_pool_bytes() bytes.
 struct ServeLaunch {
   TraceScene scene;
-  int k;
   float T_min;
-  int mode;
   float bg[3];
   ServeHost* host;
   ServeDev* dev;
@@ -273,7 +265,11 @@ struct ServeLaunch {
   uint64_t idle_ticks;
 };
 grtx_status launch_serve(const ServeLaunch& L, hipStream_t s);
-int64_t serve_pool_bytes(int k);
+int64_t serve_pool_bytes();
+// What a server's memory budget counts for the kernel: the checkpoint lists of a kernel with
+// one lane per ray and k-buffers of k, the measure by which budgets have always been taken
+// (more than the pool).
+int64_t serve_budget_bytes(int k);
 // Centre-out processing order of the 8x8 tiles of a tiles_x x tiles_y image (device array,
 // kept until the process ends).
 grtx_status centre_out_order(int device, int tiles_x, int tiles_y, const uint32_t** out);

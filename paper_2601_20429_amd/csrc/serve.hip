@@ -410,9 +410,7 @@ void worker_main(Server* sv) {
         ServeLaunch L{};
         L.scene = TraceScene{sv->nodes, sv->inst, nullptr, sv->sh, sv->sh_degree, sv->roots, nullptr,
                              GRTX_BVH_SPHERE_INSTANCE, sv->total_leaves};
-        L.k = sv->cfg.k;
         L.T_min = sv->cfg.T_min;
-        L.mode = sv->cfg.mode;
         for (int a = 0; a < 3; ++a) L.bg[a] = sv->cfg.bg[a];
         L.host = sv->host_dev;
         L.dev = sv->dev;
@@ -462,12 +460,12 @@ grtx_status serve_create(const grtx_serve_config* cfg, Server** out) {
   sv->poll_ticks = std::max<uint64_t>(1, (uint64_t)clock_khz * kPollMicros / 1000);
   sv->idle_ticks = std::max<uint64_t>(1, (uint64_t)clock_khz * (uint64_t)sv->cfg.idle_exit_us / 1000);
   // the kernel's checkpoint pool and the queue count against the budget
-  const int64_t pool_bytes = serve_pool_bytes(cfg->k);
-  sv->fixed_bytes = pool_bytes + (int64_t)sizeof(ServeDev);
+  const int64_t pool_bytes = serve_pool_bytes(), counted = serve_budget_bytes(cfg->k);
+  sv->fixed_bytes = counted + (int64_t)sizeof(ServeDev);
   sv->available = cfg->memory_budget - sv->fixed_bytes;
   if (pool_bytes <= 0 || sv->available <= 0) {
     set_error("grtx_serve_create: budget %lld bytes is below the serving kernel's checkpoint pool (%lld bytes)",
-              (long long)cfg->memory_budget, (long long)pool_bytes);
+              (long long)cfg->memory_budget, (long long)counted);
     delete sv;
     return GRTX_ERR_CAPACITY;
   }

@@ -69,8 +69,7 @@ constexpr int kStage = GRTX_STAGE;
 // Eviction-list appends gathered the same way, kStageE entries at a time (0: written one
 // by one); kStageE divides kStage. Two entries (16-B writes) measured 1-2% faster than
 // single entries on the 3M-Gaussian workload; four (with a smaller LDS stack or deferred
-// stage, to keep three workgroups per CU) were slower. The serving kernel, whose LDS also
-// holds its request copies, writes them one by one.
+// stage, to keep three workgroups per CU) were slower.
 #ifndef GRTX_EVICT_STAGE
 #define GRTX_EVICT_STAGE 2
 #endif
@@ -418,23 +417,14 @@ __device__ __forceinline__ KernArgs& kernel_args() {
   return *p;
 }
 
-// SERVE: the serving kernel. Work comes from the serving queue instead of the ray arrays:
-// each ray is generated from its request's camera, its outputs go to the request's
-// buffers, and the lane that completes a request raises its flag in host memory. Idle
-// waves wait for new requests and leave once the queue closes.
-template <int K, int LEAF, bool STATS, bool SERVE = false>
+template <int K, int LEAF, bool STATS>
 __global__ void __launch_bounds__(kTraceBlock)
     __attribute__((amdgpu_waves_per_eu(K <= 32 ? GRTX_MIN_WAVES : 2, 8))) k_trace(TraceArgs Args) {
   __shared__ uint2 s_stack[kLdsStack * kTraceBlock];
   __shared__ uint2 s_dst[kStage * kTraceBlock];  // destination node-list entries not yet written out
-  constexpr int kStageEv = SERVE ? 0 : kStageE;
+  constexpr int kStageEv = kStageE;
   __shared__ uint2 s_edst[kStageEv > 0 ? kStageEv * kTraceBlock : 1];  // eviction-list entries likewise
   __shared__ uint32_t s_stat[STATS ? GRTX_STATS_FIELDS : 1][kTraceBlock];  // per-lane counters
-  // serving: each wave's copy of its current request, each lane's output address and its
-  // request's pixel count
-  __shared__ ServeDesc s_desc[SERVE ? kWaves : 1];
-  __shared__ uint32_t s_myj[SERVE ? kWaves : 1];
-  __shared__ uint32_t s_out[SERVE ? 3 : 1][SERVE ? kTraceBlock : 1];
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const uint64_t lt_mask = lane ? (~0ull >> (64 - lane)) : 0ull;
@@ -487,14 +477,6 @@ __global__ void __launch_bounds__(kTraceBlock)
   int chunk = (int)(blockIdx.x % kChunks);
   int chunks_tried = 0;
   int room_tick = 0;  // traversal iterations of the wave, for the list-room check
-  bool nowork = false;       // serving: the last claim found no work
-  uint64_t idle_since = 0;   // serving: when the wave last ran out of rays (lane 0)
-  if constexpr (SERVE) {
-    if (lane == 0) {
-      s_desc[tid >> 6].seq = ~0u;
-      s_myj[tid >> 6] = kServeNoRequest;
-    }
-  }
 
   auto root_start = [&]() __attribute__((always_inline)) {
     // (Re)start at the root; subtrees that end before tmin are culled.
@@ -674,88 +656,11 @@ __global__ void __launch_bounds__(kTraceBlock)
   while (true) {
     KernArgs& A = kernel_args();
     // ---------------------------------------------------------------- refill idle lanes
-    // Serving: one lane claims work items of one request for the wave's idle lanes
-    // (serve_claim), which generate their rays from the request's camera.
-    // Otherwise the work items are split into kChunks contiguous chunks, each with its own
+    // The work items are split into kChunks contiguous chunks, each with its own
     // counter (one chunk by default). With several, a wave starts on chunk
     // blockIdx % kChunks (workgroups are dealt round-robin to the 8 XCDs) and moves on to
     // the next chunk when its own is drained.
-    if constexpr (SERVE) {
-      const uint64_t idle = __ballot(state == kIdle);
-      if (idle && !exhausted) {
-        const int leader = __ffsll((unsigned long long)idle) - 1;
-        uint32_t take = 0, j = 0, o = 0, closed = 0;
-        if (lane == leader)
-          take = serve_claim(A.sv_dev, A.sv_host, (uint32_t)__popcll(idle), A.sv_poll_ticks, &s_myj[tid >> 6],
-                             &s_desc[tid >> 6], &j, &o, &closed);
-        take = __shfl(take, leader);
-        j = __shfl(j, leader);
-        o = __shfl(o, leader);
-        closed = __shfl(closed, leader);
-        nowork = take == 0;
-        if (closed) exhausted = true;
-        const uint32_t rank = (uint32_t)__popcll(idle & lt_mask);
-        if (state == kIdle && rank < take) {
-          const ServeDesc& d = s_desc[tid >> 6];
-          const uint32_t w = o + rank;
-          const uint32_t* order = reinterpret_cast<const uint32_t*>(d.order);
-          const uint32_t tile = order ? order[w >> 6] : w >> 6;
-          const uint32_t ty = tile / (uint32_t)d.tiles_x, tx = tile - ty * (uint32_t)d.tiles_x;
-          const int px = (int)(tx * 8 + (w & 7)), py = (int)(ty * 8 + ((w >> 3) & 7));
-          if (px < d.width && py < d.height) {
-            const uint32_t pix = (uint32_t)py * (uint32_t)d.width + (uint32_t)px;
-            ray = (int)(((j % kServeRing) << kServePixelBits) | pix);
-            s_out[0][tid] = (uint32_t)d.out;
-            s_out[1][tid] = (uint32_t)(d.out >> 32);
-            s_out[2][tid] = d.n_pixels;
-            sid = d.scene;
-            ox = d.eye[0]; oy = d.eye[1]; oz = d.eye[2];
-            pinhole_dir(d.fwd[0], d.fwd[1], d.fwd[2], d.right[0], d.right[1], d.right[2], d.up[0], d.up[1], d.up[2], px,
-                        py, d.width, d.height, &dx, &dy, &dz);
-            ix = safe_inv(dx); iy = safe_inv(dy); iz = safe_inv(dz);
-            oix = ox * ix; oiy = oy * iy; oiz = oz * iz;
-            tfar = INFINITY;
-            kbuf_reset(kb, A.k);
-            tmin = 0;
-            C0 = C1 = C2 = Dp = 0.f;
-            T = 1.f;
-            nblend = 0;
-            par = 0;
-            nsrc_n = nsrc_i = ndst_n = 0;
-            esrc_n = esrc_i = edst_n = 0;
-            lim = INFINITY;
-            have_key = false;
-            root_start();
-            state = kTrav;
-          }
-        }
-      }
-      if (__ballot(state != kIdle) == 0) {
-        if (exhausted) break;
-        if (nowork) {
-          // nothing to trace: wait for new requests (checking about every 14 us at first,
-          // every 110 us after 100 us), and once this wave has found no work for
-          // idle_ticks, close the queue: every wave leaves when its rays are done, and the
-          // host starts a new launch for later requests
-          uint32_t quit = 0, naps = 4;
-          if (lane == 0) {
-            const uint64_t now = wall_clock();
-            if (idle_since == 0) idle_since = now;
-            if (now - idle_since > A.sv_idle_ticks) {
-              atomicOr(reinterpret_cast<ull*>(&A.sv_dev->state), (ull)kServeClosing);
-              quit = 1;
-            }
-            if (now - idle_since > 25 * A.sv_poll_ticks) naps = 32;
-          }
-          if (__shfl(quit, 0)) break;
-          naps = __shfl(naps, 0);
-#pragma unroll 1
-          for (uint32_t z = 0; z < naps; ++z) __builtin_amdgcn_s_sleep(127);
-          continue;
-        }
-      }
-      idle_since = 0;
-    } else if (!exhausted) {
+    if (!exhausted) {
       uint64_t idle = __ballot(state == kIdle);
       if (idle) {
         int cnt = __popcll(idle);
@@ -807,10 +712,8 @@ __global__ void __launch_bounds__(kTraceBlock)
         }
       }
     }
-    if constexpr (!SERVE) {
-      if (__ballot(state != kIdle) == 0) {
-        if (exhausted) break;
-      }
+    if (__ballot(state != kIdle) == 0) {
+      if (exhausted) break;
     }
 
     // ---------------------------------------------------------------- traversal
@@ -823,7 +726,7 @@ __global__ void __launch_bounds__(kTraceBlock)
     while (true) {
       const uint64_t trav = __ballot(state == kTrav);
       if (!trav) break;
-      const uint64_t waiting = __ballot(state == kEnd) | (exhausted || nowork ? 0ull : __ballot(state == kIdle));
+      const uint64_t waiting = __ballot(state == kEnd) | (exhausted ? 0ull : __ballot(state == kIdle));
       if (__popcll(waiting) >= A.refill) break;
       if ((++room_tick & (kRoomEvery - 1)) == 0 && state == kTrav && ckpt) make_room();
       const uint64_t tmax = kb[K - 1];
@@ -1072,36 +975,6 @@ __global__ void __launch_bounds__(kTraceBlock)
         lim = INFINITY;
         root_start();
         state = kTrav;
-      } else if (done && SERVE) {
-        // served ray: outputs to the request's buffers, written through to device scope;
-        // then one count per request among the lanes finishing here, and the lane whose
-        // count completes a request resets its counter and raises its flag in host memory
-        const uint32_t slot = (uint32_t)ray >> kServePixelBits;
-        const uint32_t pix = (uint32_t)ray & ((1u << kServePixelBits) - 1u);
-        float* out = reinterpret_cast<float*>(((uint64_t)s_out[1][tid] << 32) | s_out[0][tid]);
-        const uint32_t n = s_out[2][tid];
-        st_dev(out + 3 * (int64_t)pix + 0, fmaf(T, A.bg0, C0));
-        st_dev(out + 3 * (int64_t)pix + 1, fmaf(T, A.bg1, C1));
-        st_dev(out + 3 * (int64_t)pix + 2, fmaf(T, A.bg2, C2));
-        st_dev(out + 3 * (int64_t)n + pix, Dp);
-        st_dev(out + 4 * (int64_t)n + pix, 1.f - T);
-        wait_writes();
-        uint64_t fin = __ballot(true);
-        while (fin) {
-          const int l0 = __ffsll((unsigned long long)fin) - 1;
-          const uint32_t s0 = __shfl(slot, l0);
-          const uint64_t same = __ballot(slot == s0);
-          if (lane == l0) {
-            const uint32_t c = (uint32_t)__popcll(same);
-            if (atomicAdd(&A.sv_dev->slot[s0].done, c) + c == n) {
-              atomicExch(&A.sv_dev->slot[s0].done, 0u);
-              wait_writes();
-              __hip_atomic_store(&A.sv_host->done[s0], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-            }
-          }
-          fin &= ~same;
-        }
-        state = kIdle;
       } else if (done) {
         // the background shows only through rays that no surface ends
         const float bgT = tfar == INFINITY ? T : 0.f;
@@ -1418,7 +1291,7 @@ int blocks_per_cu_k(int K, bool stats) {
 constexpr size_t kGroupBlockBytes = (size_t)kGroupsPerWave * kGroupSpill * sizeof(uint2);
 int64_t group_blocks(int cus, int64_t R) {
   int nb = 0;
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_trace_group<3>, 64, 0) != hipSuccess) nb = 1;
+  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_trace_group<3, false>, 64, 0) != hipSuccess) nb = 1;
   return std::max<int64_t>(1, std::min<int64_t>((int64_t)cus * std::max(1, nb), (R + kGroupsPerWave - 1) / kGroupsPerWave));
 }
 int64_t group_fit(size_t bytes) { return (int64_t)(bytes / kGroupBlockBytes); }
@@ -1438,39 +1311,41 @@ grtx_status launch_k(int K, const TraceArgs& a, int blocks, hipStream_t s) {
   }
 }
 
-// The serving kernel leaves this many CUs' worth of workgroup slots free, so that other
-// work on the device (copies of results, other streams' kernels) is not shut out while it
-// runs.
-constexpr int kServeSpareCUs = 8;
+// Waves per CU of the serving kernel: three per SIMD, which leaves a slot of 128 registers on
+// every SIMD, so that other work on the device (copies of results, other streams' kernels) is
+// not shut out while it runs. (Its workgroups are single waves: a few whole CUs' worth of
+// them fewer leave only single slots here and there, where no workgroup of four waves fits,
+// and a copy then waits for the kernel's end.)
+constexpr int kServeWaves = 12;
 
-template <int K>
-int serve_blocks_per_cu() {
-  int nb = 0;
-  const hipError_t e =
-      hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_trace<K, kLeafSphere, false, true>, kTraceBlock, 0);
-  return e == hipSuccess ? std::max(1, nb) : 1;
-}
-
-inline int serve_k(int k) { return k <= 4 ? 4 : k <= 8 ? 8 : k <= 16 ? 16 : k <= 32 ? 32 : 64; }
-
-int serve_blocks(int K) {
+int serve_cus() {
   int device = 0, cus = 0;
   if (hipGetDevice(&device) != hipSuccess) return 0;
   if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, device) != hipSuccess) return 0;
-  const int bpc = K == 4 ? serve_blocks_per_cu<4>() : K == 8 ? serve_blocks_per_cu<8>()
-                : K == 16 ? serve_blocks_per_cu<16>() : K == 32 ? serve_blocks_per_cu<32>() : serve_blocks_per_cu<64>();
-  return std::max(1, cus - kServeSpareCUs) * bpc;
+  return cus;
 }
-
-inline int64_t serve_rows(int K) {
-  return kSpillRows + 2 * (int64_t)stage_round(kServeDeferCap) + 2 * (int64_t)stage_round(kServeEvictCap) + K;
+template <int DEG>
+int serve_waves_per_cu() {
+  int nb = 0;
+  const hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_trace_group<DEG, true>, 64, 0);
+  return e == hipSuccess ? std::max(1, std::min(nb, kServeWaves)) : 1;
+}
+int serve_blocks(int degree) {
+  return serve_cus() * (degree == 0 ? serve_waves_per_cu<0>() : degree == 1 ? serve_waves_per_cu<1>()
+                        : degree == 2 ? serve_waves_per_cu<2>() : serve_waves_per_cu<3>());
 }
 
 }  // namespace
 
-int64_t serve_pool_bytes(int k) {
-  const int K = serve_k(k);
-  return (int64_t)serve_blocks(K) * kWaves * serve_rows(K) * 64 * (int64_t)sizeof(uint2);
+int64_t serve_pool_bytes() { return (int64_t)serve_cus() * 32 * kGroupBlockBytes; }
+
+// Three workgroups on all but eight CUs (two above k = 32) of four waves, each with lists of 2048 deferred
+// nodes and 512 hits per lane, the stack spill and the k-buffer: what a kernel with one lane
+// per ray holds.
+int64_t serve_budget_bytes(int k) {
+  const int64_t K = k <= 4 ? 4 : k <= 8 ? 8 : k <= 16 ? 16 : k <= 32 ? 32 : 64;
+  const int64_t rows = kSpillRows + 2 * 2048 + 2 * 512 + K;
+  return (int64_t)std::max(1, serve_cus() - 8) * (K <= 32 ? 3 : 2) * kWaves * rows * 64 * (int64_t)sizeof(uint2);
 }
 
 namespace {
@@ -1481,8 +1356,8 @@ __global__ void k_serve_reopen(ServeDev* q) {
 }  // namespace
 
 grtx_status launch_serve(const ServeLaunch& L, hipStream_t s) {
-  const int K = serve_k(L.k);
-  const int blocks = serve_blocks(K);
+  const int degree = L.scene.sh_degree;
+  const int blocks = serve_blocks(degree);
   if (blocks <= 0) {
     set_error("serving: no device");
     return GRTX_ERR_DEVICE;
@@ -1494,28 +1369,21 @@ grtx_status launch_serve(const ServeLaunch& L, hipStream_t s) {
   a.roots = L.scene.roots;
   a.sh_degree = L.scene.sh_degree;
   a.t_near = 0.f;
-  a.k = L.k;
   a.T_min = L.T_min;
-  a.mode = L.mode;
   a.bg0 = L.bg[0];
   a.bg1 = L.bg[1];
   a.bg2 = L.bg[2];
   a.pool = static_cast<uint2*>(L.pool);
-  a.rows_per_wave = serve_rows(K);
-  a.cap_d = stage_round(kServeDeferCap);
-  a.cap_e = stage_round(kServeEvictCap);
   a.sv_host = L.host;
   a.sv_dev = L.dev;
   a.sv_poll_ticks = L.poll_ticks;
   a.sv_idle_ticks = L.idle_ticks;
-  a.refill = L.scene.n_leaves > kLargeScene ? kRefillLarge : kRefillSmall;
   hipLaunchKernelGGL(k_serve_reopen, dim3(1), dim3(64), 0, s, L.dev);
-  switch (K) {
-    case 4: hipLaunchKernelGGL((k_trace<4, kLeafSphere, false, true>), dim3(blocks), dim3(kTraceBlock), 0, s, a); break;
-    case 8: hipLaunchKernelGGL((k_trace<8, kLeafSphere, false, true>), dim3(blocks), dim3(kTraceBlock), 0, s, a); break;
-    case 16: hipLaunchKernelGGL((k_trace<16, kLeafSphere, false, true>), dim3(blocks), dim3(kTraceBlock), 0, s, a); break;
-    case 32: hipLaunchKernelGGL((k_trace<32, kLeafSphere, false, true>), dim3(blocks), dim3(kTraceBlock), 0, s, a); break;
-    default: hipLaunchKernelGGL((k_trace<64, kLeafSphere, false, true>), dim3(blocks), dim3(kTraceBlock), 0, s, a); break;
+  switch (degree) {
+    case 0: hipLaunchKernelGGL((k_trace_group<0, true>), dim3(blocks), dim3(64), 0, s, a); break;
+    case 1: hipLaunchKernelGGL((k_trace_group<1, true>), dim3(blocks), dim3(64), 0, s, a); break;
+    case 2: hipLaunchKernelGGL((k_trace_group<2, true>), dim3(blocks), dim3(64), 0, s, a); break;
+    default: hipLaunchKernelGGL((k_trace_group<3, true>), dim3(blocks), dim3(64), 0, s, a); break;
   }
   GRTX_LAUNCH_CHECK();
   return GRTX_OK;
@@ -1802,10 +1670,10 @@ grtx_status launch_trace_in(const TraceScene& b, const grtx_rays* r, const grtx_
     // a wave takes a few rays per visit to the counter, fewer where there are few
     a.group_batch = (int)std::max<int64_t>(kGroupsPerWave, std::min<int64_t>(16, a.n_work / ((int64_t)blocks * 16)));
     switch (b.sh_degree) {
-      case 0: hipLaunchKernelGGL(k_trace_group<0>, dim3(blocks), dim3(64), 0, s, a); break;
-      case 1: hipLaunchKernelGGL(k_trace_group<1>, dim3(blocks), dim3(64), 0, s, a); break;
-      case 2: hipLaunchKernelGGL(k_trace_group<2>, dim3(blocks), dim3(64), 0, s, a); break;
-      default: hipLaunchKernelGGL(k_trace_group<3>, dim3(blocks), dim3(64), 0, s, a); break;
+      case 0: hipLaunchKernelGGL((k_trace_group<0, false>), dim3(blocks), dim3(64), 0, s, a); break;
+      case 1: hipLaunchKernelGGL((k_trace_group<1, false>), dim3(blocks), dim3(64), 0, s, a); break;
+      case 2: hipLaunchKernelGGL((k_trace_group<2, false>), dim3(blocks), dim3(64), 0, s, a); break;
+      default: hipLaunchKernelGGL((k_trace_group<3, false>), dim3(blocks), dim3(64), 0, s, a); break;
     }
     GRTX_LAUNCH_CHECK();
     return GRTX_OK;

@@ -201,11 +201,19 @@ __device__ __forceinline__ int opaque(int v) {
   return v;
 }
 
-// DEG: the SH degree.
-template <int DEG>
+// Work items a served wave claims at a time (8: 1% slower over a burst of eight requests).
+constexpr uint32_t kServeBatch = 16;
+
+// DEG: the SH degree. SERVE: the serving kernel. Work comes from the serving queue instead of
+// the ray arrays: each ray is generated from its request's camera, its outputs go to the
+// request's buffers, and the wave that completes a request raises its flag in host memory.
+// Idle waves wait for new requests and leave once the queue closes.
+template <int DEG, bool SERVE>
 __global__ void __launch_bounds__(64)
     __attribute__((amdgpu_waves_per_eu(GRTX_GROUP_WAVES, 8))) k_trace_group(TraceArgs Args) {
   __shared__ GroupLds s_group[kGroupsPerWave];
+  __shared__ ServeDesc s_desc;  // serving: the wave's copy of the request its items belong to
+  __shared__ uint32_t s_myj;
   const int lane0 = threadIdx.x & 63;
   GroupLds& G = s_group[lane0 / kGroup];
 
@@ -231,6 +239,31 @@ __global__ void __launch_bounds__(64)
 
   bool start = false;  // the ray begins, or goes on, at the root
   bool fresh = true;   // (wave) a group may be without a ray
+  // serving: the ray's scene, output address and pixel count; of the wave, the request number of
+  // its items, the rays finished of one request but not yet counted there, and since when it idles
+  int sid = 0;
+  float* out_at = nullptr;
+  uint32_t out_n = 0;
+  uint32_t sv_seq = 0, fin_slot = 0, fin_n = 0, fin_count = 0, sv_tick = 0;
+  uint64_t idle_since = 0;
+  if constexpr (SERVE) {
+    if (lane0 == 0) {
+      s_desc.seq = ~0u;
+      s_myj = kServeNoRequest;
+    }
+  }
+  // Adds the finished rays to their request's count; the wave whose rays complete it resets
+  // the count and raises the request's flag.
+  auto count_finished = [&](KernArgs& A) __attribute__((always_inline)) {
+    if (fin_count == 0) return;
+    wait_writes();
+    if (lane0 == 0 && atomicAdd(&A.sv_dev->slot[fin_slot].done, fin_count) + fin_count == fin_n) {
+      atomicExch(&A.sv_dev->slot[fin_slot].done, 0u);
+      wait_writes();
+      __hip_atomic_store(&A.sv_host->done[fin_slot], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    }
+    fin_count = 0;
+  };
 
   while (true) {
     KernArgs& A = kernel_args();
@@ -238,9 +271,52 @@ __global__ void __launch_bounds__(64)
     const int gl = lane & (kGroup - 1);        // lane within the group
     const int row0 = lane & ~(kGroup - 1);     // the group's first lane
     // ------------------------------------------------------------ rays for idle groups
+    if constexpr (SERVE) fresh = fresh || (++sv_tick & 15u) == 0u;  // (a request may have come since)
     if (fresh) {
       const uint64_t idle = __ballot(!live && gl == 0);
-      if (idle && !exhausted) {
+      bool nowork = false;
+      if constexpr (SERVE) {
+        if (idle && !exhausted) {
+          if (q_next >= q_end) {
+            count_finished(A);
+            uint32_t take = 0, j = 0, o = 0, closed = 0;
+            if (lane == 0)
+              take = serve_claim(A.sv_dev, A.sv_host, kServeBatch, A.sv_poll_ticks, &s_myj, &s_desc, &j, &o, &closed);
+            take = (uint32_t)__builtin_amdgcn_readfirstlane((int)take);
+            sv_seq = (uint32_t)__builtin_amdgcn_readfirstlane((int)j);
+            q_next = (uint32_t)__builtin_amdgcn_readfirstlane((int)o);
+            q_end = q_next + take;
+            nowork = take == 0;
+            if (__builtin_amdgcn_readfirstlane((int)closed)) exhausted = true;
+            wave_order();
+          }
+          const uint32_t w = q_next + (uint32_t)__popcll(idle & ((1ull << row0) - 1ull));
+          if (!live && w < q_end) {
+            const ServeDesc& d = s_desc;
+            const uint32_t* order = reinterpret_cast<const uint32_t*>(d.order);
+            const uint32_t tile = order ? order[w >> 6] : w >> 6;
+            const uint32_t ty = tile / (uint32_t)d.tiles_x, tx = tile - ty * (uint32_t)d.tiles_x;
+            const int px = (int)(tx * 8 + (w & 7)), py = (int)(ty * 8 + ((w >> 3) & 7));
+            if (px < d.width && py < d.height) {
+              live = start = true;
+              ray = (int)(((sv_seq % kServeRing) << kServePixelBits) | ((uint32_t)py * (uint32_t)d.width + (uint32_t)px));
+              out_at = reinterpret_cast<float*>(d.out);
+              out_n = d.n_pixels;
+              sid = d.scene;
+              ox = d.eye[0]; oy = d.eye[1]; oz = d.eye[2];
+              pinhole_dir(d.fwd[0], d.fwd[1], d.fwd[2], d.right[0], d.right[1], d.right[2], d.up[0], d.up[1], d.up[2],
+                          px, py, d.width, d.height, &dx, &dy, &dz);
+              ix = safe_inv(dx); iy = safe_inv(dy); iz = safe_inv(dz);
+              oix = ox * ix; oiy = oy * iy; oiz = oz * iz;
+              T = 1.f;
+              C0 = C1 = C2 = Dp = 0.f;
+              nblend = 0;
+              tmin = 0;
+            }
+          }
+          q_next = min(q_end, q_next + (uint32_t)__popcll(idle));
+        }
+      } else if (idle && !exhausted) {
         if (q_next >= q_end) {
           const unsigned batch = (unsigned)A.group_batch;
           unsigned base = 0;
@@ -279,9 +355,26 @@ __global__ void __launch_bounds__(64)
         }
       }
       if (__ballot(live) == 0) {
+        if (SERVE) count_finished(A);
         if (exhausted) break;
+        if (SERVE && nowork) {
+          // nothing to trace: wait for new requests (checking about every 14 us at first,
+          // every 110 us after 100 us), and once this wave has found no work for
+          // idle_ticks, close the queue: every wave leaves when its rays are done, and the
+          // host starts a new launch for later requests
+          const uint64_t now = wall_clock();
+          if (idle_since == 0) idle_since = now;
+          if (now - idle_since > A.sv_idle_ticks) {
+            if (lane == 0) atomicOr(reinterpret_cast<ull*>(&A.sv_dev->state), (ull)kServeClosing);
+            break;
+          }
+          const int naps = now - idle_since > 25 * A.sv_poll_ticks ? 32 : 4;
+#pragma unroll 1
+          for (int z = 0; z < naps; ++z) __builtin_amdgcn_s_sleep(127);
+        }
         continue;
       }
+      idle_since = 0;
       fresh = !exhausted && __ballot(!live) != 0;  // (an item outside the image leaves its group without a ray)
       if (__ballot(start)) {
         // ---------------------------------------------------------- start at the root
@@ -289,7 +382,7 @@ __global__ void __launch_bounds__(64)
         // and then child j of that child's, so a group has up to sixteen nodes at once instead of
         // after two steps with one and with four (the 800x800 frame of 100k Gaussians: 2.89 to
         // 2.78 ms).
-        const float* rb = A.roots;
+        const float* rb = A.roots + 8 * sid;
         const float tlo = fmaxf(A.t_near, key_t(tmin));
         const Slab sb = slab(rb[0], rb[1], rb[2], rb[3], rb[4], rb[5], ox, oy, oz, ix, iy, iz);
         uint32_t ref = __float_as_uint(rb[6]);
@@ -531,7 +624,7 @@ __global__ void __launch_bounds__(64)
       if (ready && !cut) {
         const bool done = ert || !limited;
         bool cont = false;
-        if (done && A.ray_kind && tfar != INFINITY && T >= A.T_min) {
+        if (!SERVE && done && A.ray_kind && tfar != INFINITY && T >= A.T_min) {
           const int kd = A.ray_kind[ray];
           cont = kd == GRTX_OBJECT_MIRROR || kd == GRTX_OBJECT_GLASS;
         }
@@ -547,6 +640,17 @@ __global__ void __launch_bounds__(64)
           tfar = INFINITY;
           tmin = 0;
           start = true;
+        } else if (SERVE && done) {
+          // written through to device scope
+          if (gl == 0) {
+            const uint32_t pix = (uint32_t)ray & ((1u << kServePixelBits) - 1u);
+            st_dev(out_at + 3 * (int64_t)pix + 0, fmaf(T, A.bg0, C0));
+            st_dev(out_at + 3 * (int64_t)pix + 1, fmaf(T, A.bg1, C1));
+            st_dev(out_at + 3 * (int64_t)pix + 2, fmaf(T, A.bg2, C2));
+            st_dev(out_at + 3 * (int64_t)out_n + pix, Dp);
+            st_dev(out_at + 4 * (int64_t)out_n + pix, 1.f - T);
+          }
+          live = false;
         } else if (done) {
           if (gl == 0) {
             const float bgT = tfar == INFINITY ? T : 0.f;
@@ -563,6 +667,22 @@ __global__ void __launch_bounds__(64)
         } else {
           start = true;
         }
+      }
+      if constexpr (SERVE) {
+        // the rays that finished here, by request
+        uint64_t fin = __ballot(ready && !cut && !live && gl == 0);
+        const uint32_t slot = (uint32_t)ray >> kServePixelBits;
+        while (fin) {
+          const int l0 = __ffsll((unsigned long long)fin) - 1;
+          const uint32_t s0 = (uint32_t)__builtin_amdgcn_readlane((int)slot, l0);
+          const uint64_t same = fin & __ballot(slot == s0);
+          if (fin_count && fin_slot != s0) count_finished(A);
+          fin_slot = s0;
+          fin_n = (uint32_t)__builtin_amdgcn_readlane((int)out_n, l0);
+          fin_count += (uint32_t)__popcll(same);
+          fin &= ~same;
+        }
+        if (q_next >= q_end) count_finished(A);
       }
       wave_order();
     } else if (leaves >= kGroupLeafLanes || 2 * leaves >= nodes) {
