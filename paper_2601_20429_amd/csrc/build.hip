@@ -1212,61 +1212,359 @@ __device__ __forceinline__ void restructure(uint32_t p, int64_t nint, uint32_t* 
   }
 }
 
-// The pass runs per subtree of at most NS leaves whose parent has more (the
-// nodes above keep the radix tree's topology): one workgroup takes a subtree, its threads
-// its leaves (a contiguous run [lo, hi] of sorted positions). The subtree's internal nodes
-// are exactly the indices lo..hi-1 of the radix tree (each internal node is numbered after
-// one end of its range), and restructuring only permutes them, so the arrival counters of
-// the bottom-up hand-over sit in LDS at index - lo, ordered with workgroup-scope fences.
-// Workgroups draw subtrees from a queue.
+// The passes run per subtree of at most NS leaves whose parent has more (the nodes above keep
+// the radix tree's topology): one workgroup takes a subtree, whose leaves are a contiguous run
+// [lo, hi] of sorted positions. An internal node of the radix tree is numbered after one end of
+// its range, a right child (and the root) after its first leaf, a left child after its last: the
+// subtree's internal nodes are the indices lo..hi-1 where its root is lo, and lo+1..hi where it
+// is hi. Restructuring only permutes them. The whole subtree sits in LDS for all of its passes. A pass takes the nodes
+// by height, lowest first (what a node's treelet holds was taken at a lower height), each by a
+// team of sixteen lanes that share out the subsets of the treelet's leaves; nodes that keep
+// their children take one lane.
+// What bounds it is the chain of heights, some 15 to 20 treelets one after the other: 3 to 4 us
+// each, where one lane per treelet with its data in global memory took 8 (100k leaves: 130 to
+// 78 us), and above a million leaves the vector units' issue (3M leaves, three passes: 5.42 to
+// 3.5 ms). The trees are the same.
+constexpr int kTeam = 16;
+constexpr uint16_t kNoLocal = 0xFFFFu;
+template <int NS>
+struct SubtreeLds {
+  // internal nodes 0..n-2, then leaves n-1..2n-2
+  float box[2 * NS - 1][6];
+  float area[2 * NS - 1];
+  float cost[2 * NS - 1];
+  uint16_t count[2 * NS - 1];
+  uint16_t kid[NS - 1][2];
+  uint16_t par[2 * NS - 1];
+  uint16_t list[NS - 1];           // internal nodes by height
+  uint32_t height[NS - 1];
+  uint32_t first[NS + 1];          // places of each height in `list`
+  uint32_t max_height;
+  struct Team {
+    float cost[kSets];
+    uint16_t leaf[8];              // the treelet's leaves
+    uint8_t node[kSets];           // which of its nodes stands for the subset once rebuilt
+    uint8_t split[kSets];
+  } team[NS / kTeam];
+};
+static_assert(kTreeletLeaves == 5, "a team holds the ten pairs, ten triples, five quads and the full set's fifteen splits");
+
+__device__ __forceinline__ void lds_order() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+
+// Rebuilds the treelet of node p, by the sixteen lanes tl = 0..15 of one team. A lane holds one
+// pair, one triple and one quad of the treelet's leaves, so that every size takes one round of
+// LDS reads; the full set takes one split per lane.
+template <int NS>
+__device__ __forceinline__ void team_restructure(SubtreeLds<NS>& L, typename SubtreeLds<NS>::Team& W, int n, uint32_t p,
+                                                 int tl) {
+  // treelet leaves and the nodes between them, the same in every lane
+  uint32_t leaf[kTreeletLeaves], inner[kTreeletLeaves - 1];
+  float larea[kTreeletLeaves];
+#pragma unroll
+  for (int q = 0; q < kTreeletLeaves; ++q) leaf[q] = 0u, larea[q] = -1.f;
+#pragma unroll
+  for (int q = 0; q < kTreeletLeaves - 1; ++q) inner[q] = p;
+  int nl = 2;
+  leaf[0] = L.kid[p][0];
+  leaf[1] = L.kid[p][1];
+  larea[0] = L.area[leaf[0]];
+  larea[1] = L.area[leaf[1]];
+#pragma unroll
+  for (int step = 0; step < kTreeletLeaves - 2; ++step) {
+    // open the internal treelet leaf of largest surface area
+    int best = -1;
+    float ba = -1.f;
+    uint32_t x = 0u;
+#pragma unroll
+    for (int q = 0; q < step + 2; ++q)
+      if (leaf[q] < (uint32_t)(n - 1) && larea[q] > ba) {
+        ba = larea[q];
+        best = q;
+        x = leaf[q];
+      }
+    if (best < 0) break;
+    inner[step + 1] = x;
+    const uint32_t c0 = L.kid[x][0], c1 = L.kid[x][1];
+    const float a0 = L.area[c0];
+#pragma unroll
+    for (int q = 0; q < step + 2; ++q)
+      if (q == best) leaf[q] = c0, larea[q] = a0;
+    leaf[step + 2] = c1;
+    larea[step + 2] = L.area[c1];
+    ++nl;
+  }
+  const uint32_t full = (1u << nl) - 1u;
+  if (tl < kTreeletLeaves) {
+    uint32_t mine = leaf[0];
+#pragma unroll
+    for (int q = 1; q < kTreeletLeaves; ++q)
+      if (q == tl) mine = leaf[q];
+    W.leaf[tl] = (uint16_t)mine;
+    W.cost[1 << tl] = L.cost[mine];
+  }
+  // this lane's subsets of two, three and four leaves (five bits each; none: beyond `full`)
+  constexpr uint64_t kPairs = 3ull | 5ull << 5 | 6ull << 10 | 9ull << 15 | 10ull << 20 | 12ull << 25 | 17ull << 30 |
+                              18ull << 35 | 20ull << 40 | 24ull << 45;
+  constexpr uint64_t kTriples = 7ull | 11ull << 5 | 13ull << 10 | 14ull << 15 | 19ull << 20 | 21ull << 25 | 22ull << 30 |
+                                25ull << 35 | 26ull << 40 | 28ull << 45;
+  constexpr uint32_t kQuads = 15u | 23u << 5 | 27u << 10 | 29u << 15 | 30u << 20;
+  const uint32_t set[3] = {tl < 10 ? (uint32_t)(kPairs >> (5 * tl)) & 31u : 32u,
+                           tl < 10 ? (uint32_t)(kTriples >> (5 * tl)) & 31u : 32u,
+                           tl < 5 ? (kQuads >> (5 * tl)) & 31u : 32u};
+  lds_order();
+  float box[3][6], area[3];
+  uint32_t cnt[3];
+#pragma unroll
+  for (int k = 0; k < 3; ++k) {
+    cnt[k] = 0u;
+    area[k] = 0.f;
+    if (set[k] <= full) {
+      W.node[set[k]] = 0xFFu;
+      uint32_t rest = set[k];
+#pragma unroll
+      for (int i = 0; i < k + 2; ++i) {
+        const uint32_t v = W.leaf[__ffs((int)rest) - 1];
+        rest &= rest - 1u;
+        const float* bv = L.box[v];
+        cnt[k] += L.count[v];
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+          box[k][a] = i == 0 ? bv[a] : fminf(box[k][a], bv[a]);
+          box[k][3 + a] = i == 0 ? bv[3 + a] : fmaxf(box[k][3 + a], bv[3 + a]);
+        }
+      }
+      area[k] = half_area(box[k]);
+    }
+  }
+  // optimal cost of every subset and the split that reaches it: a split is the part that holds
+  // the lowest leaf; in ascending order the first of the cheapest is taken
+  float own[3] = {0.f, 0.f, 0.f};
+  auto better = [](float c, uint32_t P, float& best, uint32_t& bp) __attribute__((always_inline)) {
+    if (c < best) best = c, bp = P;
+  };
+  if (set[0] <= full) {
+    const uint32_t S = set[0], lo = S & (0u - S);
+    own[0] = kCostNode * area[0] + (W.cost[lo] + W.cost[S ^ lo]);
+    W.cost[S] = own[0];
+    W.split[S] = (uint8_t)lo;
+  }
+  lds_order();
+  if (set[1] <= full) {
+    const uint32_t S = set[1], x = S & (0u - S), yz = S ^ x, y = yz & (0u - yz), z = yz ^ y;
+    const float cx = W.cost[x], cy = W.cost[y], cz = W.cost[z], cyz = W.cost[yz], cxy = W.cost[x | y],
+                cxz = W.cost[x | z];
+    float best = INFINITY;
+    uint32_t bp = x;
+    better(cx + cyz, x, best, bp);
+    better(cxy + cz, x | y, best, bp);
+    better(cxz + cy, x | z, best, bp);
+    own[1] = kCostNode * area[1] + best;
+    W.cost[S] = own[1];
+    W.split[S] = (uint8_t)bp;
+  }
+  lds_order();
+  if (set[2] <= full) {
+    const uint32_t S = set[2], x = S & (0u - S), r1 = S ^ x, y = r1 & (0u - r1), r2 = r1 ^ y, z = r2 & (0u - r2),
+                   w = r2 ^ z;
+    const float c1 = W.cost[x] + W.cost[r1], c2 = W.cost[x | y] + W.cost[r2], c3 = W.cost[x | z] + W.cost[y | w],
+                c4 = W.cost[x | y | z] + W.cost[w], c5 = W.cost[x | w] + W.cost[y | z],
+                c6 = W.cost[x | y | w] + W.cost[z], c7 = W.cost[x | z | w] + W.cost[y];
+    float best = INFINITY;
+    uint32_t bp = x;
+    better(c1, x, best, bp);
+    better(c2, x | y, best, bp);
+    better(c3, x | z, best, bp);
+    better(c4, x | y | z, best, bp);
+    better(c5, x | w, best, bp);
+    better(c6, x | y | w, best, bp);
+    better(c7, x | z | w, best, bp);
+    own[2] = kCostNode * area[2] + best;
+    W.cost[S] = own[2];
+    W.split[S] = (uint8_t)bp;
+  }
+  lds_order();
+  uint32_t full_split = 0u;
+  if (nl == kTreeletLeaves) {
+    const uint32_t q = 2u * (uint32_t)tl;
+    const float c = tl < 15 ? W.cost[1u | q] + W.cost[30u ^ q] : INFINITY;
+    float least = c;
+#pragma unroll
+    for (int off = 8; off > 0; off >>= 1) least = fminf(least, __shfl_xor(least, off));
+    const uint32_t eq = (uint32_t)(__ballot(c == least) >> (threadIdx.x & 48)) & 0xFFFFu;
+    full_split = 1u | 2u * (uint32_t)(eq ? __ffs((int)eq) - 1 : 0);
+    if (tl == 0) L.cost[p] = kCostNode * L.area[p] + least;
+  }
+  // rebuild top-down, reusing the treelet's internal nodes (p stays the root); the subsets still
+  // to be split are stacked in one register, eight bits each: the subset and its node's number
+  if (tl == 0) {
+    uint32_t stack = full | 0x80u, next = 1u;  // (the top byte's bit 7 marks an entry)
+    while (stack) {
+      const uint32_t S = stack & 31u, me = stack >> 5 & 3u;
+      stack >>= 8;
+      const uint32_t P = S == 31u ? full_split : W.split[S];
+      uint32_t node = p;
+#pragma unroll
+      for (int q = 1; q < kTreeletLeaves - 1; ++q)
+        if ((uint32_t)q == me) node = inner[q];
+      if (S != 31u) W.node[S] = (uint8_t)me;
+#pragma unroll
+      for (int k = 0; k < 2; ++k) {
+        const uint32_t X = k == 0 ? P : S ^ P;
+        uint32_t c;
+        if ((X & (X - 1u)) == 0u) {
+          c = leaf[0];
+#pragma unroll
+          for (int q = 1; q < kTreeletLeaves; ++q)
+            if (X == (1u << q)) c = leaf[q];
+        } else {
+          c = inner[1];
+#pragma unroll
+          for (int q = 2; q < kTreeletLeaves - 1; ++q)
+            if ((uint32_t)q == next) c = inner[q];
+          stack = stack << 8 | (X | next << 5 | 0x80u);
+          ++next;
+        }
+        L.kid[node][k] = (uint16_t)c;
+      }
+    }
+  }
+  lds_order();
+#pragma unroll
+  for (int k = 0; k < 3; ++k) {
+    const uint32_t me = set[k] <= full ? W.node[set[k]] : 0xFFu;
+    if (me != 0xFFu) {
+      uint32_t node = p;
+#pragma unroll
+      for (int q = 1; q < kTreeletLeaves - 1; ++q)
+        if ((uint32_t)q == me) node = inner[q];
+#pragma unroll
+      for (int a = 0; a < 6; ++a) L.box[node][a] = box[k][a];
+      L.area[node] = area[k];
+      L.cost[node] = own[k];
+      L.count[node] = (uint16_t)cnt[k];
+    }
+  }
+  lds_order();
+}
+
 template <int NS>
 __global__ void __launch_bounds__(NS) k_treelet(int64_t m, const uint32_t* __restrict__ roots,
-                                                            const uint32_t* __restrict__ n_roots,
-                                                            unsigned int* __restrict__ queue,
-                                                            const uint2* __restrict__ range, uint32_t* child,
-                                                            uint32_t* parent, float* boxes, float* cost,
-                                                            uint32_t* count, uint32_t min_leaves) {
-  __shared__ TreeletLds<NS> L;
-  __shared__ uint32_t s_item;
-  __shared__ uint32_t s_arrive[NS];
+                                                const uint32_t* __restrict__ n_roots, const uint2* __restrict__ range,
+                                                uint32_t* __restrict__ child, uint32_t* __restrict__ parent,
+                                                float* __restrict__ boxes, float* __restrict__ cost,
+                                                uint32_t* __restrict__ count, int passes) {
+  __shared__ SubtreeLds<NS> L;
   const int64_t nint = m - 1;
   const uint32_t nr = *n_roots;
-  const int tid = threadIdx.x;
-  while (true) {
-    if (tid == 0) s_item = atomicAdd(queue, 1u);
-    __syncthreads();
-    const uint32_t item = s_item;
-    __syncthreads();
-    if (item >= nr) return;
+  const int tid = threadIdx.x, tl = tid & (kTeam - 1), team = tid / kTeam;
+  for (uint32_t item = blockIdx.x; item < nr; item += gridDim.x) {
     const uint32_t r = roots[item];
-    const int64_t lo = (int64_t)r < nint ? (int64_t)range[r].x : (int64_t)r - nint;
-    const int64_t n = (int64_t)r < nint ? (int64_t)range[r].y - range[r].x + 1 : 1;
-    s_arrive[tid] = 0u;
-    __syncthreads();
-    if ((int64_t)tid < n) {
-      const uint32_t u = (uint32_t)(nint + lo + tid);
-      cost[u] = kCostLeaf * half_area(boxes + 6 * (int64_t)u);
-      if (u != r) {
-        uint32_t p = parent[u];
-        while (true) {
-          // the first thread to arrive leaves; the second sees both subtrees
-          if ((uint64_t)((int64_t)p - lo) >= (uint64_t)NS) break;  // outside the run: never
-          __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-          if (atomicAdd(&s_arrive[p - lo], 1u) == 0u) break;
-          __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
-          if (min_leaves == 0u || count[p] >= min_leaves) {
-            restructure(p, nint, child, parent, boxes, cost, count, L, tid);
-          } else {
-            // kept as it is; its cost follows its children's
-            cost[p] = kCostNode * half_area(boxes + 6 * (int64_t)p) + cost[node_of(child[2 * (int64_t)p], nint)] +
-                      cost[node_of(child[2 * (int64_t)p + 1], nint)];
-          }
-          if (p == r) break;
-          p = parent[p];
-        }
+    const bool inner_root = (int64_t)r < nint;
+    const int64_t lo = inner_root ? (int64_t)range[r].x : (int64_t)r - nint;
+    const int n = inner_root ? (int)(range[r].y - range[r].x + 1u) : 1;
+    const int64_t first = (int64_t)r == lo ? lo : lo + 1;  // internal node 0 of the subtree
+    __syncthreads();  // (the subtree before this one is written back)
+    if (tid < n) {
+      const int64_t u = nint + lo + tid;
+      const int v = n - 1 + tid;
+      float b[6];
+#pragma unroll
+      for (int a = 0; a < 6; ++a) L.box[v][a] = b[a] = boxes[6 * u + a];
+      L.area[v] = half_area(b);
+      L.cost[v] = kCostLeaf * L.area[v];
+      L.count[v] = 1;
+      if (cost) cost[u] = L.cost[v];
+    }
+    if (tid < n - 1) {
+      const int64_t u = first + tid;
+      float b[6];
+#pragma unroll
+      for (int a = 0; a < 6; ++a) L.box[tid][a] = b[a] = boxes[6 * u + a];
+      L.area[tid] = half_area(b);
+      L.count[tid] = (uint16_t)count[u];
+#pragma unroll
+      for (int k = 0; k < 2; ++k) {
+        const uint32_t c = child[2 * u + k];
+        L.kid[tid][k] = (uint16_t)((c & kLeafFlag) ? (int64_t)(c & ~kLeafFlag) - lo + n - 1 : (int64_t)c - first);
       }
     }
     __syncthreads();
+    if (n < 3) {
+      if (n == 2 && tid == 0 && cost) cost[first] = kCostNode * L.area[0] + (L.cost[1] + L.cost[2]);
+      continue;
+    }
+    const uint32_t root = (uint32_t)((int64_t)r - first);
+    for (int pass = 0; pass < passes; ++pass) {
+      const uint32_t min_leaves = pass == 0 ? 0u : kLaterPassLeaves << (pass - 1);
+      // heights (internal nodes on the longest path down), and the nodes listed by them
+      if (tid < n - 1) {
+        L.par[L.kid[tid][0]] = (uint16_t)tid;
+        L.par[L.kid[tid][1]] = (uint16_t)tid;
+        L.height[tid] = 0u;
+      }
+      for (int i = tid; i < NS + 1; i += NS) L.first[i] = 0u;
+      __syncthreads();
+      if (tid == 0) L.par[root] = kNoLocal;
+      __syncthreads();
+      if (tid < n) {
+        uint32_t q = L.par[n - 1 + tid], d = 1u;
+        while (q != kNoLocal && atomicMax(&L.height[q], d) < d) {
+          ++d;
+          q = L.par[q];
+        }
+      }
+      __syncthreads();
+      if (tid < n - 1) {
+        atomicAdd(&L.first[L.height[tid]], 1u);
+        if (tid == (int)root) L.max_height = L.height[tid];
+      }
+      __syncthreads();
+      const uint32_t top = L.max_height;
+      if (tid == 0) {
+        uint32_t run = 0u;
+        for (uint32_t h = 1u; h <= top; ++h) {
+          const uint32_t c = L.first[h];
+          L.first[h] = run;
+          run += c;
+        }
+      }
+      __syncthreads();
+      if (tid < n - 1) L.list[atomicAdd(&L.first[L.height[tid]], 1u)] = (uint16_t)tid;
+      __syncthreads();
+      // (first[h] is now the end of height h, so the start of height h + 1)
+      for (uint32_t h = 1u; h <= top; ++h) {
+        const uint32_t beg = h == 1u ? 0u : L.first[h - 1], end = L.first[h];
+        for (uint32_t i = beg + (uint32_t)tid; i < end; i += NS) {
+          const uint32_t p = L.list[i];
+          const float c0 = L.cost[L.kid[p][0]], c1 = L.cost[L.kid[p][1]];
+          if (min_leaves != 0u && L.count[p] < min_leaves) L.cost[p] = kCostNode * L.area[p] + c0 + c1;
+          else if (L.count[p] == 2u) L.cost[p] = kCostNode * L.area[p] + (c0 + c1);
+        }
+        for (uint32_t i = beg + (uint32_t)team; i < end; i += NS / kTeam) {
+          const uint32_t p = L.list[i];
+          const uint32_t c = L.count[p];
+          if (c > 2u && c >= min_leaves) team_restructure<NS>(L, L.team[team], n, p, tl);
+        }
+        __syncthreads();
+      }
+    }
+    if (tid < n - 1) {
+      const int64_t u = first + tid;
+#pragma unroll
+      for (int k = 0; k < 2; ++k) {
+        const uint32_t c = L.kid[tid][k];
+        const bool is_leaf = c >= (uint32_t)(n - 1);
+        child[2 * u + k] = is_leaf ? kLeafFlag | (uint32_t)(lo + c - (uint32_t)(n - 1)) : (uint32_t)(first + c);
+        parent[is_leaf ? nint + lo + c - (uint32_t)(n - 1) : first + c] = (uint32_t)u;
+      }
+#pragma unroll
+      for (int a = 0; a < 6; ++a) boxes[6 * u + a] = L.box[tid][a];
+      count[u] = L.count[tid];
+      if (cost) cost[u] = L.cost[tid];
+    }
   }
 }
 
@@ -1671,30 +1969,22 @@ grtx_status build_bvh(const grtx_gaussians* g, grtx_bvh_kind kind, float alpha_m
       GRTX_TRY(sc.get(&rflag, nn));
       GRTX_TRY(sc.get(&rpos, nn));
       GRTX_TRY(sc.get(&roots, m));
-      GRTX_TRY(sc.get(&nroots, 2));  // count, then the work queue
+      GRTX_TRY(sc.get(&nroots, 1));
       const int ns = subtree_leaves(m);
       hipLaunchKernelGGL(k_cut_flags, dim3(grid_for(nn)), dim3(kBlock), 0, s, nn, nint, b->parent, count,
                          (uint32_t)ns, rflag);
       GRTX_TRY(exclusive_scan_u32(rflag, rpos, nn, s));
       hipLaunchKernelGGL(k_subtree_roots, dim3(grid_for(nn)), dim3(kBlock), 0, s, nn, rflag, rpos, roots, nroots);
-      hipLaunchKernelGGL(k_fill_u32, dim3(1), dim3(kBlock), 0, s, nroots + 1, 1, 0u);
-      int dev = 0, cus = 0;
-      GRTX_HIP(hipGetDevice(&dev));
-      GRTX_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
-      // workgroups: four per CU at 256 threads, eight at 128 (the queue hands out subtrees)
-      const unsigned groups = (unsigned)std::max(1, 4 * cus * (256 / ns));
-      // a subtree keeps its root, its leaves and its set of internal nodes through a pass, so
-      // later passes take the same roots (the queue is reset for each)
-      for (int pass = 0; pass < treelet_passes(m); ++pass) {
-        const uint32_t min_leaves = pass == 0 ? 0u : kLaterPassLeaves << (pass - 1);
-        if (pass > 0) hipLaunchKernelGGL(k_fill_u32, dim3(1), dim3(kBlock), 0, s, nroots + 1, 1, 0u);
-        if (ns == 256)
-          hipLaunchKernelGGL(k_treelet<256>, dim3(groups), dim3(256), 0, s, m, roots, nroots, nroots + 1, range,
-                             b->child, b->parent, b->boxes, sah, count, min_leaves);
-        else
-          hipLaunchKernelGGL(k_treelet<128>, dim3(groups), dim3(128), 0, s, m, roots, nroots, nroots + 1, range,
-                             b->child, b->parent, b->boxes, sah, count, min_leaves);
-      }
+      // a workgroup per subtree, which mostly hold more than half of `ns` leaves (a stride over
+      // the list takes any more); the costs are kept where the nodes above them need them
+      const unsigned groups = (unsigned)std::min<int64_t>(m / (ns / 2) + 1, 1 << 16);
+      float* const costs = m > kTopPassLeaves ? sah : nullptr;
+      if (ns == 256)
+        hipLaunchKernelGGL(k_treelet<256>, dim3(groups), dim3(256), 0, s, m, roots, nroots, range, b->child, b->parent,
+                           b->boxes, costs, count, treelet_passes(m));
+      else
+        hipLaunchKernelGGL(k_treelet<128>, dim3(groups), dim3(128), 0, s, m, roots, nroots, range, b->child, b->parent,
+                           b->boxes, costs, count, treelet_passes(m));
       if (m > kTopPassLeaves) {
         hipLaunchKernelGGL(k_fill_u32, dim3(grid_for(nint + 1)), dim3(kBlock), 0, s, arrivals, nint + 1, 0u);
         const unsigned top_groups = (unsigned)((m + ns - 1) / ns);
