@@ -6,14 +6,14 @@
 //   63-bit Morton codes (binary32 quantisation with fp contraction off, so the codes are
 //     an exact integer function of the inputs)
 //   stable LSD radix sort of (code, index), 8 passes of 8 bits
-//   radix tree over the sorted (code, position) keys (Karras 2012, one thread per node)
-//   leaf records and leaf boxes in sorted order
-//   bottom-up refit with per-node arrival counters (exact min/max)
+//   leaf records and leaf boxes in sorted order, and the boxes of 2, 4, 8, ... leaves
+//   radix tree over the sorted (code, position) keys (Karras 2012, one thread per node, which
+//   also forms its box: exact min/max), with the subtrees of the next step and a subtree cut
+//   kept for the trace's per-tile cost estimates
 //   treelet restructuring by surface-area cost (5-leaf treelets, one workgroup per subtree
 //     of at most 256 leaves; beyond a million leaves three passes over the subtrees and
 //     one over the nodes above them), unless the plain radix tree is asked for
-//   collapse to four-wide quantised node records, and a subtree cut kept for the trace's
-//     per-tile cost estimates
+//   collapse to four-wide quantised node records, laid out in subtree blocks
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -32,8 +32,13 @@ constexpr int kBlock = 256;
 
 // ------------------------------------------------------------------ centroid bounds
 
+// (It also clears what later kernels count in: the density grid and a few counters.)
 __global__ void __launch_bounds__(kBlock) k_bounds_partial(const float* __restrict__ pts, int64_t n,
-                                                           float* __restrict__ partial) {
+                                                           float* __restrict__ partial, uint4* __restrict__ grid,
+                                                           uint32_t* __restrict__ counters, int n_counters) {
+  for (int i = blockIdx.x * kBlock + threadIdx.x; i < kDensityCells / 4; i += gridDim.x * kBlock)
+    grid[i] = make_uint4(0u, 0u, 0u, 0u);
+  if (blockIdx.x == 0 && (int)threadIdx.x < n_counters) counters[threadIdx.x] = 0u;
   float lo[3] = {INFINITY, INFINITY, INFINITY}, hi[3] = {-INFINITY, -INFINITY, -INFINITY};
   for (int64_t i = blockIdx.x * (int64_t)kBlock + threadIdx.x; i < n; i += (int64_t)gridDim.x * kBlock) {
     for (int a = 0; a < 3; ++a) {
@@ -60,7 +65,7 @@ __global__ void __launch_bounds__(kBlock) k_bounds_partial(const float* __restri
 }
 
 __global__ void __launch_bounds__(kBlock) k_bounds_final(const float* __restrict__ partial, int nparts,
-                                                         float* __restrict__ out) {
+                                                         float* __restrict__ out, float* __restrict__ dbox) {
   __shared__ float s[6][kBlock];
   float v[6] = {INFINITY, INFINITY, INFINITY, -INFINITY, -INFINITY, -INFINITY};
   for (int i = threadIdx.x; i < nparts; i += kBlock)
@@ -78,7 +83,7 @@ __global__ void __launch_bounds__(kBlock) k_bounds_final(const float* __restrict
       }
     __syncthreads();
   }
-  if (threadIdx.x < 6) out[threadIdx.x] = s[threadIdx.x][0];
+  if (threadIdx.x < 6) out[threadIdx.x] = dbox[threadIdx.x] = s[threadIdx.x][0];
 }
 
 // ------------------------------------------------------------------ Morton codes
@@ -320,54 +325,6 @@ __device__ __forceinline__ int prefix_len(const uint64_t* __restrict__ codes, in
   return 64 + __clz((uint32_t)i ^ (uint32_t)j);
 }
 
-__global__ void __launch_bounds__(kBlock) k_karras(const uint64_t* __restrict__ codes, int64_t n,
-                                                   uint32_t* __restrict__ child, uint32_t* __restrict__ parent,
-                                                   uint2* __restrict__ range, uint32_t* __restrict__ count,
-                                                   uint32_t* __restrict__ arrivals) {
-  int64_t i = blockIdx.x * (int64_t)kBlock + threadIdx.x;
-  if (i >= n - 1) return;
-  // the refit's arrival counters (n - 1 nodes, then the ready-list length) start at zero
-  arrivals[i] = 0u;
-  if (i == 0) arrivals[n - 1] = 0u;
-  int d = prefix_len(codes, n, i, i + 1) - prefix_len(codes, n, i, i - 1) > 0 ? 1 : -1;
-  int dmin = prefix_len(codes, n, i, i - d);
-  int64_t lmax = 2;
-  while (prefix_len(codes, n, i, i + lmax * d) > dmin) lmax <<= 1;
-  int64_t l = 0;
-  for (int64_t t = lmax >> 1; t >= 1; t >>= 1)
-    if (prefix_len(codes, n, i, i + (l + t) * d) > dmin) l += t;
-  int64_t j = i + l * d;
-  int dnode = prefix_len(codes, n, i, j);
-  int64_t s = 0;
-  int64_t t = l;
-  do {
-    t = (t + 1) >> 1;
-    if (prefix_len(codes, n, i, i + (s + t) * d) > dnode) s += t;
-  } while (t > 1);
-  int64_t gamma = i + s * d + (d < 0 ? -1 : 0);
-  int64_t lo = i < j ? i : j, hi = i < j ? j : i;
-  uint32_t left, right;
-  if (lo == gamma) {
-    left = kLeafFlag | (uint32_t)gamma;
-    parent[(n - 1) + gamma] = (uint32_t)i;
-  } else {
-    left = (uint32_t)gamma;
-    parent[gamma] = (uint32_t)i;
-  }
-  if (hi == gamma + 1) {
-    right = kLeafFlag | (uint32_t)(gamma + 1);
-    parent[(n - 1) + gamma + 1] = (uint32_t)i;
-  } else {
-    right = (uint32_t)(gamma + 1);
-    parent[gamma + 1] = (uint32_t)i;
-  }
-  child[2 * i] = left;
-  child[2 * i + 1] = right;
-  range[i] = make_uint2((uint32_t)lo, (uint32_t)hi);
-  count[i] = (uint32_t)(hi - lo + 1);  // leaves below the node
-  if (i == 0) parent[0] = kNoParent;
-}
-
 // ------------------------------------------------------------------ leaves
 
 struct GaussIn {
@@ -426,13 +383,32 @@ __device__ __forceinline__ void gauss_box(const GaussIn& g, int64_t i, const Gau
   }
 }
 
+// Counts a wave's leaves (in sorted order, so that neighbours mostly share a cell) in the
+// density grid over `bounds`: one atomic per run of equal cells. Every lane of the wave calls it;
+// `in`: the lane has a leaf.
+__device__ __forceinline__ void count_density(bool in, float x, float y, float z, const float* __restrict__ bounds,
+                                              uint32_t* __restrict__ grid) {
+  const int cell = in ? density_cell(x, y, z, bounds) : -1;
+  const int lane = threadIdx.x & 63;
+  const int before = __shfl_up(cell, 1);
+  const bool head = in && (lane == 0 || before != cell);
+  const uint64_t heads = __ballot(head), live = __ballot(in);
+  if (head) {
+    const uint64_t later = lane == 63 ? 0ull : heads >> (lane + 1) << (lane + 1);
+    const int end = later ? __ffsll((unsigned long long)later) - 1 : __popcll(live);
+    atomicAdd(grid + cell, (uint32_t)(end - lane));
+  }
+}
+
 // Sphere leaves: instance record and box for sorted position p.
 __global__ void __launch_bounds__(kBlock) k_sphere_leaves(GaussIn g, const uint32_t* __restrict__ perm, int64_t n,
                                                           float alpha_min, float box_scale, float4* __restrict__ inst,
-                                                          float* __restrict__ boxes) {
+                                                          float* __restrict__ boxes, const float* __restrict__ bounds,
+                                                          uint32_t* __restrict__ grid) {
   int64_t p = blockIdx.x * (int64_t)kBlock + threadIdx.x;
+  const uint32_t i = p < n ? perm[p] : 0u;
+  count_density(p < n, g.means[3 * (int64_t)i], g.means[3 * (int64_t)i + 1], g.means[3 * (int64_t)i + 2], bounds, grid);
   if (p >= n) return;
-  uint32_t i = perm[p];
   GaussGeom G = gauss_geom(g, i, alpha_min);
   float4 r[4];
   float* rr = reinterpret_cast<float*>(r);
@@ -529,100 +505,179 @@ __global__ void __launch_bounds__(kBlock) k_proxy_setup(GaussIn g, int64_t n, fl
 __global__ void __launch_bounds__(kBlock) k_proxy_leaves(const uint32_t* __restrict__ perm, int64_t m,
                                                          const float4* __restrict__ tri_in,
                                                          const float* __restrict__ box_in,
-                                                         float4* __restrict__ tri_out, float* __restrict__ boxes) {
+                                                         float4* __restrict__ tri_out, float* __restrict__ boxes,
+                                                         const float* __restrict__ cent, const float* __restrict__ bounds,
+                                                         uint32_t* __restrict__ grid) {
   int64_t p = blockIdx.x * (int64_t)kBlock + threadIdx.x;
+  const uint32_t t = p < m ? perm[p] : 0u;
+  count_density(p < m, cent[3 * (int64_t)t], cent[3 * (int64_t)t + 1], cent[3 * (int64_t)t + 2], bounds, grid);
   if (p >= m) return;
-  uint32_t t = perm[p];
   for (int q = 0; q < 3; ++q) tri_out[3 * p + q] = tri_in[3 * (int64_t)t + q];
   float* bx = boxes + ((m - 1) + p) * 6;
   for (int a = 0; a < 6; ++a) bx[a] = box_in[6 * (int64_t)t + a];
 }
 
-// ------------------------------------------------------------------ refit
+// ------------------------------------------------------------------ boxes of leaf ranges
+// Every internal node of the radix tree covers a run of sorted leaves, so its box needs no
+// bottom-up pass over the tree: unions of 2, 4, 8, ... consecutive leaves (aligned; the last of
+// each level may be short) are formed eight levels per launch, and a node takes its run as at
+// most two of them per level. The unions are exact minima and maxima, so the boxes are those of
+// any other order. (At 100k leaves the two launches and the node's look-ups replace 17 + 39 us
+// of bottom-up refit; at 3M 577 + 103 us.)
+constexpr int kBoxLevels = 32;
+struct BoxLevels {
+  const float* leaves;      // level 0
+  float* up;                // the levels above, one after the other
+  int64_t at[kBoxLevels];   // first entry of each level in `up`
+  int64_t size[kBoxLevels];
+  int count;                // levels, the leaves' included
+};
 
-// Refit in two phases. An internal node of the radix tree covers a contiguous range of
-// sorted leaves. "Small" nodes (at most `small` leaves) take their children's boxes
-// straight from the leaf boxes of the two sub-ranges: no ordering between threads is
-// needed. The few "top" nodes above them are refitted bottom-up by one workgroup, which
-// orders its threads with workgroup-scope atomics; a grid-wide bottom-up pass would need a
-// device-scope fence per node, which on a multi-XCD part writes back the whole L2.
-// The limit grows with the tree: 128 leaves up to a million leaves; 1024 above, where the
-// top phase would otherwise walk tens of thousands of nodes in one workgroup (at 3M leaves
-// the two phases took 0.24 + 0.71 ms with 128, 0.58 + 0.10 ms with 1024).
-inline int64_t refit_small_limit(int64_t m) { return m > ((int64_t)1 << 20) ? 1024 : 128; }
-constexpr int kTopBlock = 1024;
-
-__device__ __forceinline__ bool is_small(uint32_t c, const uint2* __restrict__ range, int64_t small) {
-  if (c & kLeafFlag) return true;
-  uint2 r = range[c];
-  return (int64_t)r.y - r.x + 1 <= small;
+__device__ __forceinline__ const float* level_box(const BoxLevels& B, int level, int64_t i) {
+  return level == 0 ? B.leaves + 6 * i : B.up + 6 * (B.at[level] + i);
 }
 
-__device__ __forceinline__ void range_box(const float* __restrict__ leaf_boxes, uint32_t lo, uint32_t hi, float b[6]) {
-  b[0] = b[1] = b[2] = INFINITY;
-  b[3] = b[4] = b[5] = -INFINITY;
-  uint32_t q = lo;
-  for (; q + 3 <= hi; q += 4) {
-    float v[4][6];
+__device__ __forceinline__ void join_box(float (&b)[6], const float* __restrict__ v) {
 #pragma unroll
-    for (int u = 0; u < 4; ++u)
-#pragma unroll
-      for (int a = 0; a < 6; ++a) v[u][a] = leaf_boxes[(int64_t)(q + u) * 6 + a];
-#pragma unroll
-    for (int u = 0; u < 4; ++u)
-#pragma unroll
-      for (int a = 0; a < 3; ++a) {
-        b[a] = fminf(b[a], v[u][a]);
-        b[3 + a] = fmaxf(b[3 + a], v[u][3 + a]);
-      }
-  }
-  for (; q <= hi; ++q)
-#pragma unroll
-    for (int a = 0; a < 3; ++a) {
-      b[a] = fminf(b[a], leaf_boxes[(int64_t)q * 6 + a]);
-      b[3 + a] = fmaxf(b[3 + a], leaf_boxes[(int64_t)q * 6 + 3 + a]);
-    }
-}
-
-__device__ __forceinline__ void write_box(float* __restrict__ boxes, uint32_t node, const float (&b0)[6],
-                                          const float (&b1)[6]) {
-  float* nb = boxes + (int64_t)node * 6;
   for (int a = 0; a < 3; ++a) {
-    nb[a] = fminf(b0[a], b1[a]);
-    nb[3 + a] = fmaxf(b0[3 + a], b1[3 + a]);
+    b[a] = fminf(b[a], v[a]);
+    b[3 + a] = fmaxf(b[3 + a], v[3 + a]);
   }
 }
 
-// Phase 1: every small internal node; also lists the top nodes whose children are both
-// small (the top phase starts there).
-__global__ void __launch_bounds__(kBlock) k_refit_small(int64_t n, const uint32_t* __restrict__ child,
-                                                        const uint2* __restrict__ range, float* __restrict__ boxes,
-                                                        uint32_t* __restrict__ ready,
-                                                        uint32_t* __restrict__ n_ready, int64_t small) {
-  const int64_t i = blockIdx.x * (int64_t)kBlock + threadIdx.x;
-  bool top_ready = false;
-  if (i < n - 1) {
-    const uint2 r = range[i];
-    const uint32_t c0 = child[2 * i], c1 = child[2 * i + 1];
-    if ((int64_t)r.y - r.x + 1 <= small) {
-      const uint32_t split = c0 & ~kLeafFlag;  // last leaf of the left child
-      float b0[6], b1[6];
-      const float* leaf_boxes = boxes + (n - 1) * 6;
-      range_box(leaf_boxes, r.x, split, b0);
-      range_box(leaf_boxes, split + 1, r.y, b1);
-      write_box(boxes, (uint32_t)i, b0, b1);
-    } else {
-      top_ready = is_small(c0, range, small) && is_small(c1, range, small);
-    }
+// Levels from+1 .. from+8 over 256 entries of level `from` per workgroup.
+__global__ void __launch_bounds__(kBlock) k_box_levels(BoxLevels B, int from) {
+  __shared__ float s_box[kBlock][6];
+  const int t = threadIdx.x;
+  int64_t i = blockIdx.x * (int64_t)kBlock + t;
+  if (i < B.size[from]) {
+    const float* v = level_box(B, from, i);
+    for (int a = 0; a < 6; ++a) s_box[t][a] = v[a];
   }
-  const uint64_t m = __ballot(top_ready);
-  if (m) {
-    const int lane = threadIdx.x & 63;
-    const int leader = __ffsll((unsigned long long)m) - 1;
-    uint32_t base = 0;
-    if (lane == leader) base = atomicAdd(n_ready, (uint32_t)__popcll(m));
-    base = __shfl(base, leader);
-    if (top_ready) ready[base + __popcll(m & ((1ull << lane) - 1))] = (uint32_t)i;
+  for (int k = 1; k <= 8 && from + k < B.count; ++k) {
+    __syncthreads();
+    const int64_t j = (blockIdx.x * (int64_t)kBlock >> k) + t;
+    float b[6];
+    const bool mine = t < (kBlock >> k) && j < B.size[from + k];
+    if (mine) {
+      for (int a = 0; a < 6; ++a) b[a] = s_box[2 * t][a];
+      if (2 * j + 1 < B.size[from + k - 1]) join_box(b, s_box[2 * t + 1]);
+      float* dst = B.up + 6 * (B.at[from + k] + j);
+      for (int a = 0; a < 6; ++a) dst[a] = b[a];
+    }
+    __syncthreads();
+    if (mine)
+      for (int a = 0; a < 6; ++a) s_box[t][a] = b[a];
+  }
+}
+
+// Box of the leaves lo..hi.
+__device__ __forceinline__ void run_box(const BoxLevels& B, uint32_t lo, uint32_t hi, float (&b)[6]) {
+  for (int a = 0; a < 3; ++a) b[a] = INFINITY, b[3 + a] = -INFINITY;
+  uint32_t l = lo, r = hi + 1u;
+  for (int level = 0; l < r; ++level) {
+    if (l & 1u) join_box(b, level_box(B, level, l++));
+    if (r & 1u) join_box(b, level_box(B, level, --r));
+    l >>= 1;
+    r >>= 1;
+  }
+}
+
+// ------------------------------------------------------------------ the radix tree (Karras)
+// One thread per internal node: its range of sorted leaves, its children, its box and leaf
+// count. A node of more than `ns` leaves lists its children of at most that many as subtrees of
+// the restructuring pass, and one of more than `cut` leaves its children of at most that many
+// for the trace's per-tile cost estimates (lo, leaf count) (hi, 0), up to kCutCap; 0: neither.
+// The lists' order follows the threads' and nothing depends on it. With `depth` the kernel
+// does its work only where the restructured tree measured there is deeper than max_depth: it
+// puts the plain tree back (and clears the heights that are then measured again).
+struct TopologyOut {
+  uint32_t* child;
+  uint32_t* parent;
+  uint2* range;
+  uint32_t* count;
+  float* boxes;
+  uint32_t* roots;
+  uint32_t* n_roots;
+  float4* cut;
+  uint32_t* n_cut;
+  uint32_t* heights;  // cleared, or null
+};
+
+__device__ __forceinline__ uint32_t list_place(bool want, uint32_t* counter) {
+  const uint64_t m = __ballot(want);
+  if (!m) return 0u;
+  const int lane = threadIdx.x & 63, leader = __ffsll((unsigned long long)m) - 1;
+  uint32_t base = 0u;
+  if (lane == leader) base = atomicAdd(counter, (uint32_t)__popcll(m));
+  return __shfl(base, leader) + (uint32_t)__popcll(m & ((1ull << lane) - 1ull));
+}
+
+__global__ void __launch_bounds__(kBlock) k_topology(const uint64_t* __restrict__ codes, int64_t n, BoxLevels B,
+                                                     TopologyOut O, uint32_t ns, uint32_t cut,
+                                                     const uint32_t* __restrict__ depth, int max_depth) {
+  if (depth && *depth <= (uint32_t)max_depth) return;
+  const int64_t i = blockIdx.x * (int64_t)kBlock + threadIdx.x;
+  const bool mine = i < n - 1;
+  int64_t gamma = 0, lo = 0, hi = 0;
+  if (mine) {
+    const int d = prefix_len(codes, n, i, i + 1) - prefix_len(codes, n, i, i - 1) > 0 ? 1 : -1;
+    const int dmin = prefix_len(codes, n, i, i - d);
+    int64_t lmax = 2;
+    while (prefix_len(codes, n, i, i + lmax * d) > dmin) lmax <<= 1;
+    int64_t l = 0;
+    for (int64_t t = lmax >> 1; t >= 1; t >>= 1)
+      if (prefix_len(codes, n, i, i + (l + t) * d) > dmin) l += t;
+    const int64_t j = i + l * d;
+    const int dnode = prefix_len(codes, n, i, j);
+    int64_t s = 0;
+    int64_t t = l;
+    do {
+      t = (t + 1) >> 1;
+      if (prefix_len(codes, n, i, i + (s + t) * d) > dnode) s += t;
+    } while (t > 1);
+    gamma = i + s * d + (d < 0 ? -1 : 0);
+    lo = i < j ? i : j;
+    hi = i < j ? j : i;
+    const uint32_t left = lo == gamma ? kLeafFlag | (uint32_t)gamma : (uint32_t)gamma;
+    const uint32_t right = hi == gamma + 1 ? kLeafFlag | (uint32_t)(gamma + 1) : (uint32_t)(gamma + 1);
+    O.parent[lo == gamma ? (n - 1) + gamma : gamma] = (uint32_t)i;
+    O.parent[hi == gamma + 1 ? (n - 1) + gamma + 1 : gamma + 1] = (uint32_t)i;
+    O.child[2 * i] = left;
+    O.child[2 * i + 1] = right;
+    O.range[i] = make_uint2((uint32_t)lo, (uint32_t)hi);
+    O.count[i] = (uint32_t)(hi - lo + 1);  // leaves below the node
+    if (i == 0) O.parent[0] = kNoParent;
+    if (O.heights) O.heights[i] = 0u;
+    float b[6];
+    run_box(B, (uint32_t)lo, (uint32_t)hi, b);
+    for (int a = 0; a < 6; ++a) O.boxes[6 * i + a] = b[a];
+  }
+  const uint32_t own = mine ? (uint32_t)(hi - lo + 1) : 0u;
+  if (ns) {
+    const bool whole = mine && i == 0 && own <= ns;
+    const uint32_t at = list_place(whole, O.n_roots);
+    if (whole) O.roots[at] = 0u;
+  }
+#pragma unroll
+  for (int k = 0; k < 2; ++k) {
+    const int64_t a = k == 0 ? lo : gamma + 1, e = k == 0 ? gamma : hi;
+    const uint32_t cnt = (uint32_t)(e - a + 1);
+    if (ns) {
+      const bool sub = own > ns && cnt <= ns;
+      const uint32_t at = list_place(sub, O.n_roots);
+      if (sub) O.roots[at] = cnt == 1u ? (uint32_t)(n - 1 + a) : (uint32_t)(k == 0 ? gamma : gamma + 1);
+    }
+    if (cut) {
+      const bool piece = own > cut && cnt <= cut;
+      const uint32_t at = list_place(piece, O.n_cut);
+      if (piece && at < (uint32_t)kCutCap) {
+        float b[6];
+        run_box(B, (uint32_t)a, (uint32_t)e, b);
+        O.cut[2 * (int64_t)at] = make_float4(b[0], b[1], b[2], (float)cnt);
+        O.cut[2 * (int64_t)at + 1] = make_float4(b[3], b[4], b[5], 0.f);
+      }
+    }
   }
 }
 
@@ -630,35 +685,6 @@ __device__ __forceinline__ void child_box(const float* boxes, int64_t n, uint32_
   const int64_t idx = (c & kLeafFlag) ? (n - 1) + (c & ~kLeafFlag) : c;
 #pragma unroll
   for (int a = 0; a < 6; ++a) b[a] = boxes[idx * 6 + a];
-}
-
-// Phase 2: one workgroup. A thread starts at a ready top node and climbs; at a parent with
-// two top children the first arrival stops and the second continues.
-__global__ void __launch_bounds__(kTopBlock) k_refit_top(int64_t n, const uint32_t* __restrict__ child,
-                                                         const uint32_t* __restrict__ parent,
-                                                         const uint2* __restrict__ range, float* boxes,
-                                                         const uint32_t* __restrict__ ready,
-                                                         const uint32_t* __restrict__ n_ready,
-                                                         uint32_t* __restrict__ arrivals, int64_t small) {
-  const uint32_t cnt = *n_ready;
-  for (uint32_t w = threadIdx.x; w < cnt; w += kTopBlock) {
-    uint32_t node = ready[w];
-    while (true) {
-      const uint32_t c0 = child[2 * (int64_t)node], c1 = child[2 * (int64_t)node + 1];
-      float b0[6], b1[6];
-      child_box(boxes, n, c0, b0);
-      child_box(boxes, n, c1, b1);
-      write_box(boxes, node, b0, b1);
-      const uint32_t p = parent[node];
-      if (p == kNoParent) break;
-      const bool two =
-          !is_small(child[2 * (int64_t)p], range, small) && !is_small(child[2 * (int64_t)p + 1], range, small);
-      // release this node's box to the sibling's thread; acquire the sibling's box
-      if (two && __hip_atomic_fetch_add(&arrivals[p], 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_WORKGROUP) == 0u)
-        break;
-      node = p;
-    }
-  }
 }
 
 // Four-wide node records (layout in grtx_internal.h), written once every box is final.
@@ -879,32 +905,6 @@ __global__ void __launch_bounds__(kBlock) k_layout_tasks(const float4* __restric
       begin = nbeg;
     }
   }
-}
-
-// ------------------------------------------------------------------ density grid
-// Leaves per cell of a kDensityRes^3 grid over the leaf centres' bounds. A thread counts
-// kDensityRun consecutive sorted leaves and adds each run of equal cells with one atomic.
-constexpr int kDensityRun = 16;
-__global__ void __launch_bounds__(kBlock) k_density(const float* __restrict__ pts, const uint32_t* __restrict__ perm,
-                                                    int64_t m, const float* __restrict__ bounds,
-                                                    uint32_t* __restrict__ grid) {
-  const int64_t i0 = (blockIdx.x * (int64_t)kBlock + threadIdx.x) * kDensityRun;
-  if (i0 >= m) return;
-  int cur = -1;
-  uint32_t run = 0;
-  const int64_t i1 = i0 + kDensityRun < m ? i0 + kDensityRun : m;
-  for (int64_t i = i0; i < i1; ++i) {
-    const float* p = pts + 3 * (int64_t)perm[i];
-    const int c = density_cell(p[0], p[1], p[2], bounds);
-    if (c == cur) {
-      ++run;
-    } else {
-      if (run) atomicAdd(grid + cur, run);
-      cur = c;
-      run = 1;
-    }
-  }
-  if (run) atomicAdd(grid + cur, run);
 }
 
 // ------------------------------------------------------------------ pinhole rays
@@ -1455,7 +1455,7 @@ __global__ void __launch_bounds__(NS) k_treelet(int64_t m, const uint32_t* __res
                                                 const uint32_t* __restrict__ n_roots, const uint2* __restrict__ range,
                                                 uint32_t* __restrict__ child, uint32_t* __restrict__ parent,
                                                 float* __restrict__ boxes, float* __restrict__ cost,
-                                                uint32_t* __restrict__ count, int passes) {
+                                                uint32_t* __restrict__ count, int passes, uint32_t* depth) {
   __shared__ SubtreeLds<NS> L;
   const int64_t nint = m - 1;
   const uint32_t nr = *n_roots;
@@ -1492,20 +1492,24 @@ __global__ void __launch_bounds__(NS) k_treelet(int64_t m, const uint32_t* __res
       }
     }
     __syncthreads();
+    // the depth of the whole tree: this subtree's height below the nodes above it
+    auto measure = [&](uint32_t h) __attribute__((always_inline)) {
+      for (uint32_t q = parent[r]; q != kNoParent; q = parent[q]) ++h;
+      atomicMax(depth, h);
+    };
     if (n < 3) {
       if (n == 2 && tid == 0 && cost) cost[first] = kCostNode * L.area[0] + (L.cost[1] + L.cost[2]);
+      if (tid == 0 && depth) measure((uint32_t)n - 1u);
       continue;
     }
     const uint32_t root = (uint32_t)((int64_t)r - first);
-    for (int pass = 0; pass < passes; ++pass) {
-      const uint32_t min_leaves = pass == 0 ? 0u : kLaterPassLeaves << (pass - 1);
-      // heights (internal nodes on the longest path down), and the nodes listed by them
+    // heights: internal nodes on the longest path down from each node, itself included
+    auto find_heights = [&]() __attribute__((always_inline)) {
       if (tid < n - 1) {
         L.par[L.kid[tid][0]] = (uint16_t)tid;
         L.par[L.kid[tid][1]] = (uint16_t)tid;
         L.height[tid] = 0u;
       }
-      for (int i = tid; i < NS + 1; i += NS) L.first[i] = 0u;
       __syncthreads();
       if (tid == 0) L.par[root] = kNoLocal;
       __syncthreads();
@@ -1517,6 +1521,12 @@ __global__ void __launch_bounds__(NS) k_treelet(int64_t m, const uint32_t* __res
         }
       }
       __syncthreads();
+    };
+    for (int pass = 0; pass < passes; ++pass) {
+      const uint32_t min_leaves = pass == 0 ? 0u : kLaterPassLeaves << (pass - 1);
+      // the nodes listed by height
+      for (int i = tid; i < NS + 1; i += NS) L.first[i] = 0u;
+      find_heights();
       if (tid < n - 1) {
         atomicAdd(&L.first[L.height[tid]], 1u);
         if (tid == (int)root) L.max_height = L.height[tid];
@@ -1565,6 +1575,10 @@ __global__ void __launch_bounds__(NS) k_treelet(int64_t m, const uint32_t* __res
       count[u] = L.count[tid];
       if (cost) cost[u] = L.cost[tid];
     }
+    if (depth) {
+      find_heights();
+      if (tid == 0) measure(L.height[root]);
+    }
   }
 }
 
@@ -1593,52 +1607,6 @@ __global__ void __launch_bounds__(NS) k_treelet_top(int64_t m, const uint32_t* _
   }
 }
 
-// Subtree roots for the restructuring pass: nodes of at most `limit` leaves whose parent
-// has more (or that are the root), listed in node order.
-__global__ void k_subtree_roots(int64_t nn, const uint32_t* __restrict__ flag, const uint32_t* __restrict__ pos,
-                                uint32_t* __restrict__ roots, uint32_t* __restrict__ n_roots) {
-  const int64_t i = blockIdx.x * (int64_t)kBlock + threadIdx.x;
-  if (i >= nn) return;
-  if (i == nn - 1) *n_roots = pos[i] + flag[i];
-  if (flag[i]) roots[pos[i]] = (uint32_t)i;
-}
-
-
-// Cut of the tree for per-tile cost estimates of image traces (the trace takes the
-// heaviest tiles first): every node of at most `cut` leaves whose parent has more (or that
-// is the root). Nodes are numbered internal first, then leaves, as in `parent`.
-__device__ __forceinline__ uint32_t leaves_below(int64_t i, int64_t nint, const uint32_t* __restrict__ count) {
-  return i < nint ? count[i] : 1u;
-}
-
-__global__ void k_cut_flags(int64_t nn, int64_t nint, const uint32_t* __restrict__ parent,
-                            const uint32_t* __restrict__ range, uint32_t cut, uint32_t* __restrict__ flag) {
-  const int64_t i = blockIdx.x * (int64_t)kBlock + threadIdx.x;
-  if (i >= nn) return;
-  const uint32_t p = parent[i];
-  const bool big_parent = p == kNoParent || leaves_below(p, nint, range) > cut;
-  flag[i] = leaves_below(i, nint, range) <= cut && big_parent ? 1u : 0u;
-}
-
-// Records (lo xyz, leaf count) (hi xyz, 0) of the cut nodes, in node order, up to kCutCap.
-__global__ void k_cut_write(int64_t nn, int64_t nint, const uint32_t* __restrict__ flag,
-                            const uint32_t* __restrict__ pos, const uint32_t* __restrict__ range,
-                            const float* __restrict__ boxes, float4* __restrict__ cutrec, uint32_t* __restrict__ n_cut) {
-  const int64_t i = blockIdx.x * (int64_t)kBlock + threadIdx.x;
-  if (i >= nn) return;
-  if (i == nn - 1) *n_cut = pos[i] + flag[i];
-  if (!flag[i] || pos[i] >= (uint32_t)kCutCap) return;
-  const float* bx = boxes + 6 * i;
-  cutrec[2 * (int64_t)pos[i]] = make_float4(bx[0], bx[1], bx[2], (float)leaves_below(i, nint, range));
-  cutrec[2 * (int64_t)pos[i] + 1] = make_float4(bx[3], bx[4], bx[5], 0.f);
-}
-
-__global__ void k_write_root(const float* __restrict__ box, uint32_t ref, float* __restrict__ roots) {
-  if (threadIdx.x < 6) roots[threadIdx.x] = box[threadIdx.x];
-  if (threadIdx.x == 6) roots[6] = __uint_as_float(ref);
-  if (threadIdx.x == 7) roots[7] = 0.f;
-}
-
 __global__ void __launch_bounds__(kBlock) k_fill_u32(uint32_t* p, int64_t n, uint32_t v) {
   int64_t i = blockIdx.x * (int64_t)kBlock + threadIdx.x;
   if (i < n) p[i] = v;
@@ -1651,11 +1619,12 @@ __global__ void __launch_bounds__(kBlock) k_fill_u32(uint32_t* p, int64_t n, uin
 // nodes below it on its path and raises the per-node maximum `h`; it stops where a path at
 // least as long has already been recorded, so most climbs end after a few steps. The
 // root is node 0. A climb longer than `cap` stops there and records cap + 1 at the root
-// (the tree is then too deep whatever its exact depth).
+// (the tree is then too deep whatever its exact depth). With `depth` it runs only where that
+// is beyond max_depth. (Up to 2^20 leaves the restructuring pass measures its tree itself.)
 __global__ void __launch_bounds__(kBlock) k_tree_height(int64_t m, const uint32_t* __restrict__ parent,
                                                         uint32_t* __restrict__ h, int cap,
-                                                        const uint32_t* __restrict__ only_if) {
-  if (only_if && *only_if == 0u) return;
+                                                        const uint32_t* __restrict__ depth, int max_depth) {
+  if (depth && *depth <= (uint32_t)max_depth) return;
   const int64_t i = blockIdx.x * (int64_t)kBlock + threadIdx.x;
   if (i >= m) return;
   uint32_t p = parent[(m - 1) + i];
@@ -1671,44 +1640,22 @@ __global__ void __launch_bounds__(kBlock) k_tree_height(int64_t m, const uint32_
   }
 }
 
-// Saved topology of the plain radix tree, put back when the restructured tree is deeper
-// than `max_depth` (the plain tree over distinct 95-bit keys is at most 96 deep): child,
-// parent, the internal boxes and leaf counts. `deep[0]` records the decision for the
-// later kernels, which also recompute the depth of the tree put back into `h2`.
-struct PlainTree {
-  const uint32_t* child;
-  const uint32_t* parent;
-  const float* boxes;
-  const uint32_t* count;
-};
-__global__ void __launch_bounds__(kBlock) k_restore_plain(int64_t m, const uint32_t* __restrict__ h, int max_depth,
-                                                          PlainTree saved, uint32_t* __restrict__ child,
-                                                          uint32_t* __restrict__ parent, float* __restrict__ boxes,
-                                                          uint32_t* __restrict__ count, uint32_t* __restrict__ h2,
-                                                          uint32_t* __restrict__ deep) {
-  const bool too_deep = h[0] > (uint32_t)max_depth;
-  const int64_t i = blockIdx.x * (int64_t)kBlock + threadIdx.x;
-  if (i == 0) deep[0] = too_deep ? 1u : 0u;
-  if (!too_deep) return;
-  const int64_t nint = m - 1;
-  if (i < nint) {
-    child[2 * i] = saved.child[2 * i];
-    child[2 * i + 1] = saved.child[2 * i + 1];
-    for (int a = 0; a < 6; ++a) boxes[6 * i + a] = saved.boxes[6 * i + a];
-    count[i] = saved.count[i];
-    h2[i] = 0u;
+// Root entry: the root's box and reference (internal node 0, or leaf 0 for one leaf); and the
+// final depth and kind of the tree: out[0] = depth, out[1] = 1 if a restructured tree was
+// kept. `tree` is the restructured tree's depth (null: none was made), `plain` the plain one's
+// where it counts (null: a single leaf).
+__global__ void k_finish(const float* __restrict__ box, uint32_t ref, float* __restrict__ roots,
+                         const uint32_t* __restrict__ tree, int max_depth, const uint32_t* __restrict__ plain,
+                         uint32_t* __restrict__ out) {
+  if (threadIdx.x < 6) roots[threadIdx.x] = box[threadIdx.x];
+  if (threadIdx.x == 6) roots[6] = __uint_as_float(ref);
+  if (threadIdx.x == 7) {
+    roots[7] = 0.f;
+    const bool kept = tree && *tree <= (uint32_t)max_depth;
+    const uint32_t d = kept ? *tree : plain ? *plain : 0u;
+    out[0] = d;
+    out[1] = kept ? 1u : 0u;
   }
-  if (i < 2 * m - 1) parent[i] = saved.parent[i];
-}
-
-// Final depth and kind of the tree: out[0] = depth, out[1] = 1 if the restructured tree
-// was kept. `deep` and `h2` are null when no restructuring ran.
-__global__ void k_depth_store(const uint32_t* __restrict__ h, const uint32_t* __restrict__ deep,
-                              const uint32_t* __restrict__ h2, uint32_t* __restrict__ out) {
-  if (threadIdx.x != 0) return;
-  const bool restored = deep && deep[0] != 0u;
-  out[0] = restored ? h2[0] : h[0];
-  out[1] = deep && !restored ? 1u : 0u;
 }
 
 }  // namespace
@@ -1865,8 +1812,7 @@ grtx_status build_bvh(const grtx_gaussians* g, grtx_bvh_kind kind, float alpha_m
     if (proxy) put(&b->tris, 3 * m);
     put(&b->roots, 8);
     put(&b->cut, 2 * (int64_t)kCutCap);
-    put(&b->n_cut, 1);
-    put(&b->depth, 2);
+    put(&b->depth, 4);  // depth and kind, then the cut's length and a counter of the build's
     put(&b->density, kDensityCells);
     put(&b->dbox, 6);
   };
@@ -1885,26 +1831,27 @@ grtx_status build_bvh(const grtx_gaussians* g, grtx_bvh_kind kind, float alpha_m
     *p = reinterpret_cast<std::remove_reference_t<decltype(*p)>>(static_cast<char*>(block) + off);
     off += (size_t)std::max<int64_t>(count, 1) * sizeof(**p);
   });
+  b->n_cut = b->depth + 2;
   b->root_box = b->boxes;  // node 0: the root, or the only leaf when m == 1
 
   Scratch sc(s);
   float *partial = nullptr, *bounds = nullptr, *cent = nullptr, *tbox = nullptr;
   float4* ttmp = nullptr;
   uint64_t* tkeys = nullptr;
-  uint32_t *tvals = nullptr, *arrivals = nullptr;
+  uint32_t* tvals = nullptr;
   int nparts = (int)std::min<int64_t>(1024, (m + kBlock - 1) / kBlock);
   GRTX_TRY(sc.get(&partial, 6 * nparts));
   GRTX_TRY(sc.get(&bounds, 6));
   GRTX_TRY(sc.get(&tkeys, m));
   GRTX_TRY(sc.get(&tvals, m));
   uint2* range = nullptr;
-  uint32_t* ready = nullptr;
   uint32_t* count = nullptr;  // leaves below each internal node
-  float* sah = nullptr;       // surface-area cost of each node's subtree (restructuring)
-  GRTX_TRY(sc.get(&arrivals, nint + 1));  // per internal node, then the ready-list length
   GRTX_TRY(sc.get(&range, std::max<int64_t>(nint, 1)));
-  GRTX_TRY(sc.get(&ready, std::max<int64_t>(nint, 1)));
   GRTX_TRY(sc.get(&count, std::max<int64_t>(nint, 1)));
+  // cleared with the first kernel: the tree's depth (two words), the cut's length, and the
+  // number of subtrees the restructuring pass takes
+  uint32_t* const counters = b->depth;
+  uint32_t* const n_roots = b->depth + 3;
   const float* points = g->means;
   if (proxy) {
     GRTX_TRY(sc.get(&cent, 3 * m));
@@ -1915,21 +1862,15 @@ grtx_status build_bvh(const grtx_gaussians* g, grtx_bvh_kind kind, float alpha_m
                        tbox, cent);
     points = cent;
   }
-  hipLaunchKernelGGL(k_bounds_partial, dim3(nparts), dim3(kBlock), 0, s, points, m, partial);
-  hipLaunchKernelGGL(k_bounds_final, dim3(1), dim3(kBlock), 0, s, partial, nparts, bounds);
+  hipLaunchKernelGGL(k_bounds_partial, dim3(nparts), dim3(kBlock), 0, s, points, m, partial,
+                     reinterpret_cast<uint4*>(b->density), counters, 4);
+  hipLaunchKernelGGL(k_bounds_final, dim3(1), dim3(kBlock), 0, s, partial, nparts, bounds, b->dbox);
   hipLaunchKernelGGL(k_morton, dim3(grid_for(m)), dim3(kBlock), 0, s, points, m, bounds, b->codes, b->perm);
   GRTX_LAUNCH_CHECK();
   GRTX_TRY(radix_sort(b->codes, b->perm, tkeys, tvals, m, sc, s));
-  // leaves per cell of the density grid, over the leaf centres' bounds (in sorted order, so
-  // that a thread's leaves mostly share a cell)
-  GRTX_HIP(hipMemcpyAsync(b->dbox, bounds, 6 * sizeof(float), hipMemcpyDeviceToDevice, s));
-  hipLaunchKernelGGL(k_fill_u32, dim3(grid_for(kDensityCells)), dim3(kBlock), 0, s, b->density, (int64_t)kDensityCells,
-                     0u);
-  hipLaunchKernelGGL(k_density, dim3(grid_for((m + kDensityRun - 1) / kDensityRun)), dim3(kBlock), 0, s, points,
-                     b->perm, m, bounds, b->density);
   if (proxy) {
     hipLaunchKernelGGL(k_proxy_leaves, dim3(grid_for(m)), dim3(kBlock), 0, s, b->perm, m, ttmp, tbox, b->tris,
-                       b->boxes);
+                       b->boxes, cent, bounds, b->density);
   } else {
     float box_scale = 1.f;
     if (kind == GRTX_BVH_ICO_INSTANCE) {
@@ -1937,79 +1878,79 @@ grtx_status build_bvh(const grtx_gaussians* g, grtx_bvh_kind kind, float alpha_m
       box_scale = std::sqrt(ico.v[0][0] * ico.v[0][0] + ico.v[0][1] * ico.v[0][1] + ico.v[0][2] * ico.v[0][2]);
     }
     hipLaunchKernelGGL(k_sphere_leaves, dim3(grid_for(m)), dim3(kBlock), 0, s, gi, b->perm, m, alpha_min, box_scale,
-                       b->inst, b->boxes);
+                       b->inst, b->boxes, bounds, b->density);
   }
+  const uint32_t* tree_depth = nullptr;   // of the restructured tree
+  const uint32_t* plain_depth = nullptr;
   if (nint > 0) {
-    hipLaunchKernelGGL(k_karras, dim3(grid_for(nint)), dim3(kBlock), 0, s, b->codes, m, b->child, b->parent,
-                       range, count, arrivals);
-    hipLaunchKernelGGL(k_refit_small, dim3(grid_for(nint)), dim3(kBlock), 0, s, m, b->child, range, b->boxes,
-                       ready, arrivals + nint, refit_small_limit(m));
-    hipLaunchKernelGGL(k_refit_top, dim3(1), dim3(kTopBlock), 0, s, m, b->child, b->parent, range, b->boxes,
-                       ready, arrivals + nint, arrivals, refit_small_limit(m));
-    const bool restructure = restructure_tree && nint > 1 && 2 * m - 1 <= (int64_t)kScanChunk * kScanChunk;
-    PlainTree saved{};
-    if (restructure) {
-      // keep the plain tree in case the restructured one comes out too deep
-      uint32_t *sc_child = nullptr, *sc_parent = nullptr, *sc_count = nullptr;
-      float* sc_boxes = nullptr;
-      GRTX_TRY(sc.get(&sc_child, 2 * nint));
-      GRTX_TRY(sc.get(&sc_parent, 2 * m - 1));
-      GRTX_TRY(sc.get(&sc_boxes, 6 * nint));
-      GRTX_TRY(sc.get(&sc_count, nint));
-      GRTX_HIP(hipMemcpyAsync(sc_child, b->child, sizeof(uint32_t) * 2 * nint, hipMemcpyDeviceToDevice, s));
-      GRTX_HIP(hipMemcpyAsync(sc_parent, b->parent, sizeof(uint32_t) * (2 * m - 1), hipMemcpyDeviceToDevice, s));
-      GRTX_HIP(hipMemcpyAsync(sc_boxes, b->boxes, sizeof(float) * 6 * nint, hipMemcpyDeviceToDevice, s));
-      GRTX_HIP(hipMemcpyAsync(sc_count, count, sizeof(uint32_t) * nint, hipMemcpyDeviceToDevice, s));
-      saved = PlainTree{sc_child, sc_parent, sc_boxes, sc_count};
+    // boxes of 2, 4, 8, ... leaves
+    BoxLevels lv{};
+    lv.leaves = b->boxes + 6 * nint;
+    lv.size[0] = m;
+    lv.count = 1;
+    int64_t total_up = 0;
+    while (lv.size[lv.count - 1] > 1) {
+      lv.at[lv.count] = total_up;
+      lv.size[lv.count] = (lv.size[lv.count - 1] + 1) / 2;
+      total_up += lv.size[lv.count++];
     }
+    GRTX_TRY(sc.get(&lv.up, 6 * total_up));
+    for (int from = 0; from + 1 < lv.count; from += 8)
+      hipLaunchKernelGGL(k_box_levels, dim3(grid_for(lv.size[from])), dim3(kBlock), 0, s, lv, from);
+    // (beyond one scan's reach neither restructuring nor the cut: the plain tree, and the trace
+    // keeps its centre-out order)
+    const bool reach = 2 * m - 1 <= (int64_t)kScanChunk * kScanChunk;
+    const bool restructure = restructure_tree && nint > 1 && reach;
+    const int ns = subtree_leaves(m);
+    TopologyOut to{b->child, b->parent, range, count, b->boxes, nullptr, n_roots, b->cut, b->n_cut, nullptr};
+    if (restructure) GRTX_TRY(sc.get(&to.roots, m));
+    hipLaunchKernelGGL(k_topology, dim3(grid_for(nint)), dim3(kBlock), 0, s, b->codes, m, lv, to,
+                       restructure ? (uint32_t)ns : 0u, reach ? (uint32_t)std::max<int64_t>(1, m / kCutDiv) : 0u,
+                       (const uint32_t*)nullptr, 0);
+    uint32_t* heights = nullptr;
     if (restructure) {
-      const int64_t nn = 2 * m - 1;
-      uint32_t *rflag = nullptr, *rpos = nullptr, *roots = nullptr, *nroots = nullptr;
-      GRTX_TRY(sc.get(&sah, nn));
-      GRTX_TRY(sc.get(&rflag, nn));
-      GRTX_TRY(sc.get(&rpos, nn));
-      GRTX_TRY(sc.get(&roots, m));
-      GRTX_TRY(sc.get(&nroots, 1));
-      const int ns = subtree_leaves(m);
-      hipLaunchKernelGGL(k_cut_flags, dim3(grid_for(nn)), dim3(kBlock), 0, s, nn, nint, b->parent, count,
-                         (uint32_t)ns, rflag);
-      GRTX_TRY(exclusive_scan_u32(rflag, rpos, nn, s));
-      hipLaunchKernelGGL(k_subtree_roots, dim3(grid_for(nn)), dim3(kBlock), 0, s, nn, rflag, rpos, roots, nroots);
       // a workgroup per subtree, which mostly hold more than half of `ns` leaves (a stride over
       // the list takes any more); the costs are kept where the nodes above them need them
       const unsigned groups = (unsigned)std::min<int64_t>(m / (ns / 2) + 1, 1 << 16);
-      float* const costs = m > kTopPassLeaves ? sah : nullptr;
+      const bool top_pass = m > kTopPassLeaves;
+      float* costs = nullptr;
+      if (top_pass) GRTX_TRY(sc.get(&costs, 2 * m - 1));
       if (ns == 256)
-        hipLaunchKernelGGL(k_treelet<256>, dim3(groups), dim3(256), 0, s, m, roots, nroots, range, b->child, b->parent,
-                           b->boxes, costs, count, treelet_passes(m));
+        hipLaunchKernelGGL(k_treelet<256>, dim3(groups), dim3(256), 0, s, m, to.roots, n_roots, range, b->child,
+                           b->parent, b->boxes, costs, count, treelet_passes(m), top_pass ? nullptr : b->depth);
       else
-        hipLaunchKernelGGL(k_treelet<128>, dim3(groups), dim3(128), 0, s, m, roots, nroots, range, b->child, b->parent,
-                           b->boxes, costs, count, treelet_passes(m));
-      if (m > kTopPassLeaves) {
-        hipLaunchKernelGGL(k_fill_u32, dim3(grid_for(nint + 1)), dim3(kBlock), 0, s, arrivals, nint + 1, 0u);
+        hipLaunchKernelGGL(k_treelet<128>, dim3(groups), dim3(128), 0, s, m, to.roots, n_roots, range, b->child,
+                           b->parent, b->boxes, costs, count, treelet_passes(m), top_pass ? nullptr : b->depth);
+      tree_depth = b->depth;
+      if (top_pass) {
+        uint32_t *arrivals = nullptr, *th = nullptr;
+        GRTX_TRY(sc.get(&arrivals, nint));
+        GRTX_TRY(sc.get(&th, nint));
+        hipLaunchKernelGGL(k_fill_u32, dim3(grid_for(nint)), dim3(kBlock), 0, s, arrivals, nint, 0u);
+        hipLaunchKernelGGL(k_fill_u32, dim3(grid_for(nint)), dim3(kBlock), 0, s, th, nint, 0u);
         const unsigned top_groups = (unsigned)((m + ns - 1) / ns);
         if (ns == 256)
-          hipLaunchKernelGGL(k_treelet_top<256>, dim3(top_groups), dim3(256), 0, s, m, roots, nroots, b->child,
-                             b->parent, b->boxes, sah, count, arrivals);
+          hipLaunchKernelGGL(k_treelet_top<256>, dim3(top_groups), dim3(256), 0, s, m, to.roots, n_roots, b->child,
+                             b->parent, b->boxes, costs, count, arrivals);
         else
-          hipLaunchKernelGGL(k_treelet_top<128>, dim3(top_groups), dim3(128), 0, s, m, roots, nroots, b->child,
-                             b->parent, b->boxes, sah, count, arrivals);
+          hipLaunchKernelGGL(k_treelet_top<128>, dim3(top_groups), dim3(128), 0, s, m, to.roots, n_roots, b->child,
+                             b->parent, b->boxes, costs, count, arrivals);
+        hipLaunchKernelGGL(k_tree_height, dim3(grid_for(m)), dim3(kBlock), 0, s, m, b->parent, th, max_depth,
+                           (const uint32_t*)nullptr, 0);
+        tree_depth = th;
       }
+      // too deep: the plain tree again
+      GRTX_TRY(sc.get(&heights, nint));
+      to.heights = heights;
+      hipLaunchKernelGGL(k_topology, dim3(grid_for(nint)), dim3(kBlock), 0, s, b->codes, m, lv, to, 0u, 0u, tree_depth,
+                         max_depth);
+    } else {
+      GRTX_TRY(sc.get(&heights, nint));
+      hipLaunchKernelGGL(k_fill_u32, dim3(grid_for(nint)), dim3(kBlock), 0, s, heights, nint, 0u);
     }
-    // depth of the tree (the refit's arrival counters are free again and hold the heights)
-    hipLaunchKernelGGL(k_fill_u32, dim3(grid_for(nint)), dim3(kBlock), 0, s, arrivals, nint, 0u);
-    hipLaunchKernelGGL(k_tree_height, dim3(grid_for(m)), dim3(kBlock), 0, s, m, b->parent, arrivals,
-                       restructure ? max_depth : GRTX_MAX_TREE_DEPTH, (const uint32_t*)nullptr);
-    uint32_t *deep = nullptr, *h2 = nullptr;
-    if (restructure) {
-      GRTX_TRY(sc.get(&deep, 1));
-      GRTX_TRY(sc.get(&h2, nint));
-      hipLaunchKernelGGL(k_restore_plain, dim3(grid_for(2 * m - 1)), dim3(kBlock), 0, s, m, arrivals, max_depth, saved,
-                         b->child, b->parent, b->boxes, count, h2, deep);
-      hipLaunchKernelGGL(k_tree_height, dim3(grid_for(m)), dim3(kBlock), 0, s, m, b->parent, h2, GRTX_MAX_TREE_DEPTH,
-                         deep);
-    }
-    hipLaunchKernelGGL(k_depth_store, dim3(1), dim3(64), 0, s, arrivals, deep, h2, b->depth);
+    hipLaunchKernelGGL(k_tree_height, dim3(grid_for(m)), dim3(kBlock), 0, s, m, b->parent, heights, GRTX_MAX_TREE_DEPTH,
+                       tree_depth, max_depth);
+    plain_depth = heights;
     // four-wide records of every internal node, then the reachable ones laid out
     float4* wide = nullptr;
     uint32_t *qold = nullptr, *ctr = nullptr;
@@ -2026,23 +1967,9 @@ grtx_status build_bvh(const grtx_gaussians* g, grtx_bvh_kind kind, float alpha_m
                        dim3(kBlock), 0, s, wide, tasks, ctr, b->nodes);
   } else {
     hipLaunchKernelGGL(k_fill_u32, dim3(1), dim3(kBlock), 0, s, b->parent, 1, kNoParent);
-    hipLaunchKernelGGL(k_fill_u32, dim3(1), dim3(kBlock), 0, s, b->depth, 2, 0u);
   }
-  hipLaunchKernelGGL(k_write_root, dim3(1), dim3(64), 0, s, b->root_box, m == 1 ? (kLeafFlag | 0u) : 0u, b->roots);
-  if (2 * m - 1 > (int64_t)kScanChunk * kScanChunk) {
-    // beyond one scan's reach: no cut, the trace keeps its centre-out order
-    hipLaunchKernelGGL(k_fill_u32, dim3(1), dim3(kBlock), 0, s, b->n_cut, 1, 0u);
-  } else {
-    const int64_t nn = 2 * m - 1;
-    uint32_t *cflag = nullptr, *cpos = nullptr;
-    GRTX_TRY(sc.get(&cflag, nn));
-    GRTX_TRY(sc.get(&cpos, nn));
-    const uint32_t cut = (uint32_t)std::max<int64_t>(1, m / kCutDiv);
-    hipLaunchKernelGGL(k_cut_flags, dim3(grid_for(nn)), dim3(kBlock), 0, s, nn, nint, b->parent, count, cut, cflag);
-    GRTX_TRY(exclusive_scan_u32(cflag, cpos, nn, s));
-    hipLaunchKernelGGL(k_cut_write, dim3(grid_for(nn)), dim3(kBlock), 0, s, nn, nint, cflag, cpos, count, b->boxes,
-                       b->cut, b->n_cut);
-  }
+  hipLaunchKernelGGL(k_finish, dim3(1), dim3(64), 0, s, b->root_box, m == 1 ? (kLeafFlag | 0u) : 0u, b->roots,
+                     tree_depth, max_depth, plain_depth, b->depth);
   GRTX_LAUNCH_CHECK();
   return GRTX_OK;
 }
