@@ -256,63 +256,137 @@ __global__ void __launch_bounds__(kBlock) k_scan_loop(const uint32_t* __restrict
 // `offsets` is either the scanned histogram table ([digit][workgroup], exclusive), or, with
 // `fused`, the raw counts in workgroup-major rows: then thread d adds digit d's counts of the
 // workgroups before this one, and a block scan over the 256 digit totals gives the digit's
-// start.
+// start. A wave takes ITEMS x 64 consecutive keys and ranks them against its own counters, with
+// no barrier between rounds; then the waves' counts are added up once. Bound by latency at 100k
+// keys (10 us a pass), by memory at 3M (28 us for 72 MB; 53 before, with four barriers a round
+// and the keys written where they stood; 61 without the barriers but not through LDS).
+template <int ITEMS>
 __global__ void __launch_bounds__(kBlock) k_radix_scatter(const uint64_t* __restrict__ keys_in,
                                                           const uint32_t* __restrict__ vals_in, int64_t n, int shift,
-                                                          int items, const uint32_t* __restrict__ offsets,
-                                                          int nblocks, bool fused, uint64_t* __restrict__ keys_out,
+                                                          const uint32_t* __restrict__ offsets, int nblocks, bool fused,
+                                                          uint64_t* __restrict__ keys_out,
                                                           uint32_t* __restrict__ vals_out,
-                                                          const uint32_t* __restrict__ n_dev) {
+                                                          const uint32_t* __restrict__ n_dev,
+                                                          uint32_t* __restrict__ next_hist) {
   if (n_dev) n = min(n, (int64_t)*n_dev);
-  if ((int64_t)blockIdx.x * kBlock * items >= n) return;  // the whole workgroup is past the keys
-  __shared__ uint32_t s_off[256];
-  __shared__ uint32_t s_wcnt[kBlock / 64][256];
+  if ((int64_t)blockIdx.x * kBlock * ITEMS >= n) return;  // the whole workgroup is past the keys
+  __shared__ uint32_t s_cnt[kBlock / 64][256];
+  __shared__ uint32_t s_tmp[kBlock];
+  __shared__ uint64_t s_key[ITEMS == kRadixItems ? kBlock * ITEMS : 1];
+  __shared__ uint32_t s_val[ITEMS == kRadixItems ? kBlock * ITEMS : 1];
   const int lane = threadIdx.x & 63;
   const int wave = threadIdx.x >> 6;
   const uint64_t lt_mask = lane ? (~0ull >> (64 - lane)) : 0ull;
+  const int64_t first = (int64_t)blockIdx.x * kBlock * ITEMS + wave * (64 * ITEMS) + lane;
+  uint64_t key[ITEMS];
+#pragma unroll
+  for (int r = 0; r < ITEMS; ++r) key[r] = first + r * 64 < n ? keys_in[first + r * 64] : 0ull;
+  uint32_t val[ITEMS];
+#pragma unroll
+  for (int r = 0; r < ITEMS; ++r) val[r] = first + r * 64 < n ? vals_in[first + r * 64] : 0u;
+  uint32_t off;
   if (fused) {
+    // (32 rows' loads in flight together: the rows come from beyond this XCD's L2)
     uint32_t before = 0, total = 0;
+    int b = 0;
+    for (; b + 32 <= nblocks; b += 32) {
+      uint32_t c[32];
+#pragma unroll
+      for (int u = 0; u < 32; ++u) c[u] = offsets[(size_t)(b + u) * 256 + threadIdx.x];
+#pragma unroll
+      for (int u = 0; u < 32; ++u) {
+        total += c[u];
+        before += b + u < (int)blockIdx.x ? c[u] : 0u;
+      }
+    }
 #pragma unroll 8
-    for (int b = 0; b < nblocks; ++b) {
+    for (; b < nblocks; ++b) {
       const uint32_t c = offsets[(size_t)b * 256 + threadIdx.x];
       total += c;
       before += b < (int)blockIdx.x ? c : 0u;
     }
     uint32_t all;
-    const uint32_t start = block_exclusive_scan(total, &s_wcnt[0][0], &all);
-    s_off[threadIdx.x] = start + before;
+    off = block_exclusive_scan(total, s_tmp, &all) + before;
   } else {
-    s_off[threadIdx.x] = offsets[(size_t)threadIdx.x * nblocks + blockIdx.x];
+    off = offsets[(size_t)threadIdx.x * nblocks + blockIdx.x];
   }
-  int64_t base = (int64_t)blockIdx.x * kBlock * items;
-  for (int r = 0; r < items; ++r) {
-    for (int w = 0; w < kBlock / 64; ++w) s_wcnt[w][threadIdx.x] = 0u;
-    __syncthreads();
-    int64_t i = base + r * kBlock + threadIdx.x;
-    bool valid = i < n;
-    uint64_t key = valid ? keys_in[i] : 0ull;
-    uint32_t val = valid ? vals_in[i] : 0u;
-    uint32_t digit = (uint32_t)(key >> shift) & 255u;
+  for (int w = 0; w < kBlock / 64; ++w) s_cnt[w][threadIdx.x] = 0u;
+  __syncthreads();
+  uint32_t rank[ITEMS];
+#pragma unroll
+  for (int r = 0; r < ITEMS; ++r) {
+    const bool valid = first + r * 64 < n;
+    const uint32_t digit = (uint32_t)(key[r] >> shift) & 255u;
     uint64_t peers = __ballot(valid);
+#pragma unroll
     for (int b = 0; b < 8; ++b) {
-      bool bit = (digit >> b) & 1u;
-      uint64_t m = __ballot(valid && bit);
+      const bool bit = (digit >> b) & 1u;
+      const uint64_t m = __ballot(valid && bit);
       peers &= bit ? m : ~m;
     }
-    uint32_t rank = __popcll(peers & lt_mask);
-    if (valid && rank == 0) s_wcnt[wave][digit] = (uint32_t)__popcll(peers);
-    __syncthreads();
-    if (valid) {
-      uint32_t pos = s_off[digit] + rank;
-      for (int w = 0; w < wave; ++w) pos += s_wcnt[w][digit];
-      keys_out[pos] = key;
-      vals_out[pos] = val;
+    const uint32_t in_round = (uint32_t)__popcll(peers & lt_mask);
+    const uint32_t before = s_cnt[wave][digit];
+    rank[r] = before + in_round;
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    if (valid && in_round == 0) s_cnt[wave][digit] = before + (uint32_t)__popcll(peers);
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+  }
+  __syncthreads();
+  if constexpr (ITEMS == kRadixItems) {
+    // large sorts go through LDS in their new order, so that runs of a digit are written
+    // together
+    uint32_t mine = 0;
+#pragma unroll
+    for (int w = 0; w < kBlock / 64; ++w) mine += s_cnt[w][threadIdx.x];
+    uint32_t all;
+    uint32_t at = block_exclusive_scan(mine, s_tmp, &all);
+    s_tmp[threadIdx.x] = off - at;  // from a place here to its place in the result
+#pragma unroll
+    for (int w = 0; w < kBlock / 64; ++w) {
+      const uint32_t c = s_cnt[w][threadIdx.x];
+      s_cnt[w][threadIdx.x] = at;
+      at += c;
     }
     __syncthreads();
-    uint32_t add = 0;
-    for (int w = 0; w < kBlock / 64; ++w) add += s_wcnt[w][threadIdx.x];
-    s_off[threadIdx.x] += add;
+#pragma unroll
+    for (int r = 0; r < ITEMS; ++r)
+      if (first + r * 64 < n) {
+        const uint32_t i = s_cnt[wave][(uint32_t)(key[r] >> shift) & 255u] + rank[r];
+        s_key[i] = key[r];
+        s_val[i] = val[r];
+      }
     __syncthreads();
+#pragma unroll
+    for (int r = 0; r < ITEMS; ++r) {
+      const uint32_t i = (uint32_t)(r * kBlock) + threadIdx.x;
+      if (i < all) {
+        const uint64_t k = s_key[i];
+        const uint32_t pos = s_tmp[(uint32_t)(k >> shift) & 255u] + i;
+        keys_out[pos] = k;
+        vals_out[pos] = s_val[i];
+      }
+    }
+  } else {
+#pragma unroll
+    for (int w = 0; w < kBlock / 64; ++w) {
+      const uint32_t c = s_cnt[w][threadIdx.x];
+      s_cnt[w][threadIdx.x] = off;
+      off += c;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < ITEMS; ++r) {
+      if (first + r * 64 < n) {
+        const uint32_t pos = s_cnt[wave][(uint32_t)(key[r] >> shift) & 255u] + rank[r];
+        keys_out[pos] = key[r];
+        vals_out[pos] = val[r];
+        // counted for the next pass, in the row of the workgroup that will read the key
+        if (next_hist)
+          atomicAdd(next_hist + (size_t)(pos / (uint32_t)(kBlock * ITEMS)) * 256 + ((key[r] >> (shift + 8)) & 255u), 1u);
+      }
+    }
   }
 }
 
@@ -925,6 +999,11 @@ __global__ void __launch_bounds__(kBlock) k_pinhole(CameraFrame cf, int W, int H
   dirs[3 * i + 2] = dz;
 }
 
+__global__ void __launch_bounds__(kBlock) k_fill_u32(uint32_t* p, int64_t n, uint32_t v) {
+  int64_t i = blockIdx.x * (int64_t)kBlock + threadIdx.x;
+  if (i < n) p[i] = v;
+}
+
 inline unsigned grid_for(int64_t n) { return (unsigned)std::max<int64_t>(1, (n + kBlock - 1) / kBlock); }
 
 
@@ -950,10 +1029,20 @@ grtx_status radix_sort(uint64_t* keys, uint32_t* vals, uint64_t* tkeys, uint32_t
   uint32_t* vin = vals;
   uint64_t* kout = tkeys;
   uint32_t* vout = tvals;
+  // Small fused sorts count the next pass's digits in the scatter (cleared rows of their own per
+  // pass), so that only the first pass has a counting kernel: 12 against 14 us a pass at 100k
+  // keys; at a million the atomics cost more than the kernel (51 against 38 us).
+  uint32_t* rows = nullptr;
+  const bool counts_next = fused && items == kRadixItemsSmall && passes > 1;
+  if (counts_next) {
+    GRTX_TRY(sc.get(&rows, hn * (passes - 1)));
+    hipLaunchKernelGGL(k_fill_u32, dim3(grid_for(hn * (passes - 1))), dim3(kBlock), 0, s, rows, hn * (passes - 1), 0u);
+  }
   for (int pass = 0; pass < passes; ++pass) {
     int shift = 8 * pass;
-    hipLaunchKernelGGL(k_radix_hist, dim3(nblocks), dim3(kBlock), 0, s, kin, n, shift, items, hist, nblocks, fused,
-                       n_dev);
+    if (!counts_next || pass == 0)
+      hipLaunchKernelGGL(k_radix_hist, dim3(nblocks), dim3(kBlock), 0, s, kin, n, shift, items, hist, nblocks, fused,
+                         n_dev);
     if (fused) {
       // the scatter turns the counts into offsets itself
     } else if (nparts > 1 && nparts <= kScanLoopChunks) {
@@ -965,8 +1054,14 @@ grtx_status radix_sort(uint64_t* keys, uint32_t* vals, uint64_t* tkeys, uint32_t
     } else {
       hipLaunchKernelGGL(k_scan_down, dim3(1), dim3(kBlock), 0, s, hist, hn, (const uint32_t*)nullptr, offs);
     }
-    hipLaunchKernelGGL(k_radix_scatter, dim3(nblocks), dim3(kBlock), 0, s, kin, vin, n, shift, items,
-                       fused ? hist : offs, nblocks, fused, kout, vout, n_dev);
+    const uint32_t* counts = !fused ? offs : !counts_next || pass == 0 ? hist : rows + hn * (pass - 1);
+    if (items == kRadixItemsSmall)
+      hipLaunchKernelGGL(k_radix_scatter<kRadixItemsSmall>, dim3(nblocks), dim3(kBlock), 0, s, kin, vin, n, shift, counts,
+                         nblocks, fused, kout, vout, n_dev,
+                         counts_next && pass + 1 < passes ? rows + hn * pass : nullptr);
+    else
+      hipLaunchKernelGGL(k_radix_scatter<kRadixItems>, dim3(nblocks), dim3(kBlock), 0, s, kin, vin, n, shift, counts,
+                         nblocks, fused, kout, vout, n_dev, (uint32_t*)nullptr);
     GRTX_LAUNCH_CHECK();
     std::swap(kin, kout);
     std::swap(vin, vout);
@@ -1607,10 +1702,6 @@ __global__ void __launch_bounds__(NS) k_treelet_top(int64_t m, const uint32_t* _
   }
 }
 
-__global__ void __launch_bounds__(kBlock) k_fill_u32(uint32_t* p, int64_t n, uint32_t v) {
-  int64_t i = blockIdx.x * (int64_t)kBlock + threadIdx.x;
-  if (i < n) p[i] = v;
-}
 
 // ------------------------------------------------------------------ tree depth
 // Depth of the tree in internal nodes on the longest root-to-leaf path, which bounds the
