@@ -17,12 +17,14 @@
 //   dL/dM = g_u f^T + g_v d^T, dL/dmu = -M^T g_u, dL/ds_i = -(1/s_i) sum_j g_M[i][j] M[i][j],
 //   dL/dR[j][i] = g_M[i][j] / s_i, then through R(q/|q|) to q; dL/do = dL/da * a / o;
 //   dL/dsh[l,m,ch] = dL/dc_ch * [c_ch > 0] * Y_lm(d).
-// The sum over rays is done without atomics and in a fixed order: a first kernel writes
-// one 64-byte record per (ray, blended hit) with the hit's gradients of mean, scale,
-// rotation and opacity and the three colour factors dL/dc * T a [c > 0]; the records
-// are sorted by Gaussian (stable radix sort, so ray order is kept inside a Gaussian);
-// one wave per Gaussian then sums its records (dL/dsh = colour factor x Y(ray direction))
-// and adds the totals to the caller's arrays. Results are deterministic.
+// The sum over rays is done without atomics and in a fixed order, in three kernels. k_bwd_hits
+// replays each ray and writes one 32-byte record per (ray, blended hit): dL/da, dL/dt and the
+// colour factors dL/dc * T a [c > 0]; the records' positions are sorted by Gaussian (stable, so
+// ray order is kept inside a Gaussian); k_bwd_sums walks the sorted records in equal shares,
+// forms each record's gradients of mean, scale, rotation, opacity and SH (colour factor x
+// Y(ray direction)), adds them up per Gaussian and, for a Gaussian whose records lie within the
+// share, adds the totals to the caller's arrays; k_bwd_join adds up the Gaussians that reach
+// over the end of a share. Results are deterministic.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -34,7 +36,7 @@
 namespace grtx {
 namespace {
 
-constexpr int kBlock = 128;
+constexpr int kBlock = 256;
 
 constexpr double cx_sqrt(double x) {
   double r = x > 1.0 ? x : 1.0;
@@ -94,20 +96,20 @@ struct BwdArgs {
   const int32_t* hit_ids;
   const int32_t* hit_counts;
   int hit_cap;
-  float bg0, bg1, bg2;
   const float* g_rgb;
   const float* g_depth;
   const float* g_opacity;
   int64_t n_gauss;
-  const uint32_t* pair_off;  // per ray: first record
-  float4* rec;               // per (ray, hit): 4 x float4
-  uint64_t* key;             // per record: Gaussian index
-  uint32_t* val;             // per record: its own index (permuted by the sort)
-  unsigned int* truncated;
+  float4* gauss;             // per Gaussian: 4 x float4
+  const uint32_t* pair_off;  // per ray: records of the rays before it
+  float4* rec;               // per (ray, hit): 2 x float4
+  uint32_t* key;             // per record: Gaussian index (n_gauss: of no Gaussian)
 };
 
-// Record layout: q0 = (dmu.xyz, ds.x), q1 = (ds.yz, dq.wx), q2 = (dq.yz, do, gc.r),
-// q3 = (gc.g, gc.b, ray index bits, 0).
+// Record layout: (dL/da, dL/dt, gc.r, gc.g), (gc.b, ray index bits, G, t). The records of four
+// neighbouring rays are interleaved by hit number: rays side by side meet a Gaussian at about
+// the same one, and the sums below, which take the records by Gaussian, find some of them in
+// one 128-byte line.
 
 // Records per ray (the blended hits the forward pass listed, at most hit_cap).
 __global__ void __launch_bounds__(kBlock) k_bwd_count(const int32_t* __restrict__ hit_counts, int64_t n, int cap,
@@ -122,18 +124,149 @@ __global__ void __launch_bounds__(kBlock) k_bwd_count(const int32_t* __restrict_
   cnt[r] = (uint32_t)(c < 0 ? 0 : c);
 }
 
-__global__ void __launch_bounds__(kBlock) k_bwd_pairs(BwdArgs A) {
-  const int64_t r = blockIdx.x * (int64_t)kBlock + threadIdx.x;
-  if (r >= A.n_rays) return;
-  const float ox = A.ray_o[3 * r], oy = A.ray_o[3 * r + 1], oz = A.ray_o[3 * r + 2];
-  const float dx = A.ray_d[3 * r], dy = A.ray_d[3 * r + 1], dz = A.ray_d[3 * r + 2];
+// What of a Gaussian does not depend on the ray, once for all its hits (13 divisions and a square
+// root): M = S^-1 R^T by rows, mean, opacity.
+struct Shape {
+  float M[3][3], mu[3], opac;
+};
+
+__device__ __forceinline__ Shape load_shape(const float4* gauss, int64_t i) {
+  const float4 a = gauss[4 * i], b = gauss[4 * i + 1], c = gauss[4 * i + 2], e = gauss[4 * i + 3];
+  return Shape{{{a.x, a.y, a.z}, {a.w, b.x, b.y}, {b.z, b.w, c.x}}, {c.y, c.z, c.w}, e.x};
+}
+
+__global__ void __launch_bounds__(kBlock) k_bwd_shapes(BwdArgs A) {
+  const int64_t i = blockIdx.x * (int64_t)kBlock + threadIdx.x;
+  if (i >= A.n_gauss) return;
+  const float4 q4 = reinterpret_cast<const float4*>(A.quats)[i];
+  const float qn = sqrtf(q4.x * q4.x + q4.y * q4.y + q4.z * q4.z + q4.w * q4.w);
+  const float w = q4.x / qn, x = q4.y / qn, y = q4.z / qn, z = q4.w / qn;
+  float R[3][3];
+  R[0][0] = 1.f - 2.f * (y * y + z * z); R[0][1] = 2.f * (x * y - w * z);       R[0][2] = 2.f * (x * z + w * y);
+  R[1][0] = 2.f * (x * y + w * z);       R[1][1] = 1.f - 2.f * (x * x + z * z); R[1][2] = 2.f * (y * z - w * x);
+  R[2][0] = 2.f * (x * z - w * y);       R[2][1] = 2.f * (y * z + w * x);       R[2][2] = 1.f - 2.f * (x * x + y * y);
+  float M[9];
+#pragma unroll
+  for (int a = 0; a < 3; ++a) {
+    const float s = A.scales[3 * i + a];
+#pragma unroll
+    for (int b = 0; b < 3; ++b) M[3 * a + b] = R[b][a] / s;
+  }
+  A.gauss[4 * i] = make_float4(M[0], M[1], M[2], M[3]);
+  A.gauss[4 * i + 1] = make_float4(M[4], M[5], M[6], M[7]);
+  A.gauss[4 * i + 2] = make_float4(M[8], A.means[3 * i], A.means[3 * i + 1], A.means[3 * i + 2]);
+  A.gauss[4 * i + 3] = make_float4(A.opac[i], 0.f, 0.f, 0.f);
+}
+
+// A hit's geometry: f = o - mu, u = M f, v = M d and v.v.
+struct Geom {
+  float f[3], u[3], v[3], vv;
+};
+
+__device__ __forceinline__ Geom geometry(const Shape& g, const float* o, const float* d) {
+  Geom h;
+#pragma unroll
+  for (int a = 0; a < 3; ++a) h.f[a] = o[a] - g.mu[a];
+#pragma unroll
+  for (int a = 0; a < 3; ++a) {
+    h.u[a] = g.M[a][0] * h.f[0] + g.M[a][1] * h.f[1] + g.M[a][2] * h.f[2];
+    h.v[a] = g.M[a][0] * d[0] + g.M[a][1] * d[1] + g.M[a][2] * d[2];
+  }
+  h.vv = h.v[0] * h.v[0] + h.v[1] * h.v[1] + h.v[2] * h.v[2];
+  return h;
+}
+
+// Lane J of the row of 16, for all its lanes.
+template <int J>
+__device__ __forceinline__ float row_lane(float v) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x150 + J, 0xF, 0xF, true));
+}
+
+// Lane M of the quad, for all its lanes; and the sum over the quad.
+template <int M>
+__device__ __forceinline__ int quad_lane(int v) {
+  return __builtin_amdgcn_update_dpp(0, v, M * 0x55, 0xF, 0xF, true);
+}
+__device__ __forceinline__ float quad_sum(float v) {
+  v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0xB1, 0xF, 0xF, true));
+  return v + __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x4E, 0xF, 0xF, true));
+}
+
+// The SH sums of the quad's four hits, degree 3: its lanes read each hit's 48 coefficients
+// together, 64 neighbouring bytes at a time (a lane that reads its own hit's in 16-byte pieces
+// takes a cache access for each: 12 a hit instead of 3). Lane m holds pieces m, m + 4 and m + 8;
+// piece q's element k belongs to channel (q + k) mod 3 and coefficient (4 q + k) / 3, whose
+// basis values are the lane's `weight`.
+template <int I>
+__device__ __forceinline__ void quad_colours(const float4* sh, int own, int m, const float* weight, float* c) {
+  if constexpr (I < 4) {
+    const float4* sp = sh + (int64_t)quad_lane<I>(own) * 12 + m;
+    float part[3] = {0.f, 0.f, 0.f};
+#pragma unroll
+    for (int p = 0; p < 3; ++p) {
+      const float4 v = sp[4 * p];
+      const float e[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+      for (int k = 0; k < 4; ++k) part[(p + k) % 3] += weight[4 * p + k] * e[k];
+    }
+#pragma unroll
+    for (int ch = 0; ch < 3; ++ch) {
+      const float x = m == 1 ? part[(ch + 2) % 3] : m == 2 ? part[(ch + 1) % 3] : part[ch];
+      const float all = quad_sum(x);
+      c[ch] = m == I ? all : c[ch];
+    }
+    quad_colours<I + 1>(sh, own, m, weight, c);
+  }
+}
+
+// The compositing of up to 16 hits, one per lane of the row, in their order: a lane runs the
+// ray's sums up to its own hit (T before it, C and D with it).
+struct Sums {
+  float T, C[3], D;
+};
+template <int J>
+__device__ __forceinline__ void replay(int sub, int most, float alpha, const float* c, float t, Sums& s) {
+  if constexpr (J < 16) {
+    if (J % 4 == 0 && J >= most) return;  // (no row of the wave has a hit there)
+    const float a = row_lane<J>(alpha), t_j = row_lane<J>(t);
+    const float c0 = row_lane<J>(c[0]), c1 = row_lane<J>(c[1]), c2 = row_lane<J>(c[2]);
+    if (sub >= J) {
+      const float w = s.T * a;
+      s.C[0] += w * c0;
+      s.C[1] += w * c1;
+      s.C[2] += w * c2;
+      s.D += w * t_j;
+      if (sub > J) s.T *= 1.f - a;
+    }
+    replay<J + 1>(sub, most, alpha, c, t, s);
+  }
+}
+
+// Replays the rays: sixteen lanes per ray, a hit per lane. Bound by issue (199 of its 316 us) and
+// the latency of a hit's loads (id, then shape and SH); a lane per ray, hit after hit, has the
+// longest ray set the end. 10.7M hits of 262144 rays, degree 3: 1266 us by lane, 316 us so (375
+// when each lane reads its own hit's SH, bound by cache accesses). The sums along the ray stay in hit order (the suffix C - sum cancels against the
+// forward's, which was added up in that order).
+constexpr int kLanes = 16;
+template <bool DEG3>
+__global__ void __launch_bounds__(kBlock) k_bwd_hits(BwdArgs A) {
+  const int64_t r0 = (blockIdx.x * (int64_t)kBlock + threadIdx.x) / kLanes;
+  const int sub = threadIdx.x & (kLanes - 1);
+  const int64_t r = min(r0, A.n_rays - 1);
   int n = A.hit_counts[r];
-  n = n > A.hit_cap ? A.hit_cap : n;
-  if (n <= 0) return;
-  const uint32_t base = A.pair_off[r];
+  n = r0 >= A.n_rays ? 0 : n > A.hit_cap ? A.hit_cap : n;
+  if (!__any(n > 0)) return;
+  const float o[3] = {A.ray_o[3 * r], A.ray_o[3 * r + 1], A.ray_o[3 * r + 2]};
+  const float d[3] = {A.ray_d[3 * r], A.ray_d[3 * r + 1], A.ray_d[3 * r + 2]};
+  n = max(n, 0);
+  int nr[4];  // the hits of the wave's rays
+#pragma unroll
+  for (int k = 0; k < 4; ++k) nr[k] = __builtin_amdgcn_readlane(n, 16 * k);
+  const int row = (threadIdx.x & 63) / kLanes;
+  const uint32_t base = __builtin_amdgcn_readfirstlane(A.pair_off[r]);  // of the wave's first ray
   const float TN = 1.f - A.opacity[r];
-  const float bg[3] = {A.bg0, A.bg1, A.bg2};
   float Cf[3], gC[3];
+#pragma unroll
   for (int ch = 0; ch < 3; ++ch) {
     Cf[ch] = A.rgb[3 * r + ch];  // includes T_N * bg
     gC[ch] = A.g_rgb ? A.g_rgb[3 * r + ch] : 0.f;
@@ -141,144 +274,86 @@ __global__ void __launch_bounds__(kBlock) k_bwd_pairs(BwdArgs A) {
   const float Df = A.depth[r];
   const float gD = A.g_depth ? A.g_depth[r] : 0.f;
   const float gO = A.g_opacity ? A.g_opacity[r] : 0.f;
-  const float dn = rsqrtf(dx * dx + dy * dy + dz * dz);
+  const float dn = rsqrtf(d[0] * d[0] + d[1] * d[1] + d[2] * d[2]);
   float Y[16];
-  basis(dx * dn, dy * dn, dz * dn, A.sh_degree, Y);
+  basis(d[0] * dn, d[1] * dn, d[2] * dn, A.sh_degree, Y);
   const int ncoef = (A.sh_degree + 1) * (A.sh_degree + 1);
+  const int m = threadIdx.x & 3;
+  float weight[12];
+  if constexpr (DEG3) {
+#pragma unroll
+    for (int e = 0; e < 12; ++e) {  // element e of the lane's three pieces: coefficient (4 m + at) / 3
+      const int at = 16 * (e / 4) + e % 4;
+      weight[e] = m == 0 ? Y[at / 3] : m == 1 ? Y[(at + 4) / 3] : m == 2 ? Y[(at + 8) / 3] : Y[(at + 12) / 3];
+    }
+  }
+  const int32_t* ids = A.hit_ids + r * A.hit_cap;
 
-  float T = 1.f, Cacc[3] = {0.f, 0.f, 0.f}, Dacc = 0.f;
-  // The hits of a ray are replayed in order, one at a time, and the longest ray sets the
-  // kernel's end: each step reads the next hit's id ahead and issues all of its own hit's
-  // parameter loads (SH included) together, so fewer memory latencies separate two steps.
-  int32_t i_cur = A.hit_ids[r * A.hit_cap];
-  asm volatile("" ::"v"(i_cur));  // (in hand on entry too: the loop head then waits for nothing)
-  for (int h = 0; h < n; ++h) {
-    const int32_t i_ahead = A.hit_ids[r * A.hit_cap + (h + 1 < n ? h + 1 : h)];  // (the last re-reads its own)
-    const int64_t i = i_cur;
-    if (i < 0 || i >= A.n_gauss) {  // not a Gaussian of this scene: an empty record, sorted last
-      const uint32_t pi = base + (uint32_t)h;
-      for (int q = 0; q < 4; ++q) A.rec[4 * (int64_t)pi + q] = make_float4(0.f, 0.f, 0.f, 0.f);
-      A.key[pi] = (uint64_t)A.n_gauss;
-      A.val[pi] = pi;
-      i_cur = i_ahead;
-      continue;
-    }
-    float4 shv[12];
-    if (A.sh_degree == 3) {
-      const float4* sp4 = reinterpret_cast<const float4*>(A.sh + i * 48);
+  Sums run = {1.f, {0.f, 0.f, 0.f}, 0.f};
+  int32_t ahead = sub < n ? ids[sub] : -1;
+  for (int h0 = 0; __any(h0 < n); h0 += kLanes) {
+    const int h = h0 + sub;
+    const int32_t id = ahead;
+    ahead = h + kLanes < n ? ids[h + kLanes] : -1;
+    const bool hit = h < n && id >= 0 && id < A.n_gauss;
+    float alpha = 0.f, G = 0.f, ta = 0.f, c[3] = {0.f, 0.f, 0.f};
+    bool pos[3] = {false, false, false};
+    float col[3] = {0.f, 0.f, 0.f};
+    if constexpr (DEG3) quad_colours<0>(reinterpret_cast<const float4*>(A.sh), hit ? id : 0, m, weight, col);
+    if (hit) {
+      const int64_t i = id;
+      const Shape shape = load_shape(A.gauss, i);
+      float acc[3] = {0.5f, 0.5f, 0.5f};
+      if constexpr (DEG3) {
 #pragma unroll
-      for (int q = 0; q < 12; ++q) shv[q] = sp4[q];
-    }
-    // ---- recompute the hit
-    const float4 q4 = reinterpret_cast<const float4*>(A.quats)[i];
-    const float qn = sqrtf(q4.x * q4.x + q4.y * q4.y + q4.z * q4.z + q4.w * q4.w);
-    const float w = q4.x / qn, x = q4.y / qn, y = q4.z / qn, z = q4.w / qn;
-    float R[3][3];
-    R[0][0] = 1.f - 2.f * (y * y + z * z); R[0][1] = 2.f * (x * y - w * z);       R[0][2] = 2.f * (x * z + w * y);
-    R[1][0] = 2.f * (x * y + w * z);       R[1][1] = 1.f - 2.f * (x * x + z * z); R[1][2] = 2.f * (y * z - w * x);
-    R[2][0] = 2.f * (x * z - w * y);       R[2][1] = 2.f * (y * z + w * x);       R[2][2] = 1.f - 2.f * (x * x + y * y);
-    const float s[3] = {A.scales[3 * i], A.scales[3 * i + 1], A.scales[3 * i + 2]};
-    float M[3][3];  // S^-1 R^T
-    for (int a = 0; a < 3; ++a)
-      for (int b = 0; b < 3; ++b) M[a][b] = R[b][a] / s[a];
-    const float f[3] = {ox - A.means[3 * i], oy - A.means[3 * i + 1], oz - A.means[3 * i + 2]};
-    const float dv[3] = {dx, dy, dz};
-    float u[3], v[3];
-    for (int a = 0; a < 3; ++a) {
-      u[a] = M[a][0] * f[0] + M[a][1] * f[1] + M[a][2] * f[2];
-      v[a] = M[a][0] * dv[0] + M[a][1] * dv[1] + M[a][2] * dv[2];
-    }
-    const float vv = v[0] * v[0] + v[1] * v[1] + v[2] * v[2];
-    const float uv = u[0] * v[0] + u[1] * v[1] + u[2] * v[2];
-    const float ta = -uv / vv;
-    const float p[3] = {u[0] + ta * v[0], u[1] + ta * v[1], u[2] + ta * v[2]};
-    const float m2 = p[0] * p[0] + p[1] * p[1] + p[2] * p[2];
-    const float o = A.opac[i];
-    const float G = expf(-0.5f * m2);
-    const float alpha = o * G;
-    float c[3];
-    bool pos[3];
-    float acc[3] = {0.5f, 0.5f, 0.5f};
-    if (A.sh_degree == 3) {
-      // the 48 coefficients, loaded above as twelve 16-B loads
+        for (int ch = 0; ch < 3; ++ch) acc[ch] += col[ch];
+      } else {
+        const float* shp = A.sh + i * 3 * ncoef;
 #pragma unroll
-      for (int q = 0; q < 12; ++q) {
-        const float* vv = reinterpret_cast<const float*>(&shv[q]);
+        for (int k = 0; k < 9; ++k)
+          if (k < ncoef)
 #pragma unroll
-        for (int e = 0; e < 4; ++e) acc[(4 * q + e) % 3] += Y[(4 * q + e) / 3] * vv[e];
+            for (int ch = 0; ch < 3; ++ch) acc[ch] += Y[k] * shp[3 * k + ch];
       }
-    } else {
-      const float* shp = A.sh + i * 3 * ncoef;
-      for (int ch = 0; ch < 3; ++ch)
-        for (int k = 0; k < 16; ++k)
-          if (k < ncoef) acc[ch] += Y[k] * shp[3 * k + ch];
-    }
-    for (int ch = 0; ch < 3; ++ch) {
-      pos[ch] = acc[ch] > 0.f;
-      c[ch] = pos[ch] ? acc[ch] : 0.f;
-    }
-    // ---- compositing derivatives
-    const float wgt = T * alpha;
-    for (int ch = 0; ch < 3; ++ch) Cacc[ch] += wgt * c[ch];
-    Dacc += wgt * ta;
-    const float inv1ma = 1.f / (1.f - alpha);
-    float gA = 0.f;
-    for (int ch = 0; ch < 3; ++ch) {
-      const float behind = Cf[ch] - Cacc[ch];  // S_i (includes T_N bg)
-      gA += gC[ch] * (T * c[ch] - behind * inv1ma);
-    }
-    gA += gD * (T * ta - (Df - Dacc) * inv1ma);
-    gA += gO * (TN * inv1ma);
-    const float gT = gD * wgt;  // dL/dt_alpha
-    T *= (1.f - alpha);
-    // ---- SH: the colour factors (dL/dsh = factor x Y is formed per Gaussian)
-    float gcol[3];
-    for (int ch = 0; ch < 3; ++ch) gcol[ch] = pos[ch] ? gC[ch] * wgt : 0.f;
-    (void)bg;
-    // ---- alpha -> opacity, m2
-    const float g_op = gA * G;
-    const float gm2 = gA * (-0.5f * alpha);
-    float gu[3], gv[3];
-    for (int a = 0; a < 3; ++a) {
-      gu[a] = gm2 * 2.f * p[a] - gT * v[a] / vv;
-      gv[a] = gm2 * 2.f * ta * p[a] - gT * (u[a] + 2.f * ta * v[a]) / vv;
-    }
-    // ---- u = M f, v = M d
-    float gM[3][3];
-    for (int a = 0; a < 3; ++a)
-      for (int b = 0; b < 3; ++b) gM[a][b] = gu[a] * f[b] + gv[a] * dv[b];
-    float g_mu[3], g_s[3];
-    for (int b = 0; b < 3; ++b) g_mu[b] = -(M[0][b] * gu[0] + M[1][b] * gu[1] + M[2][b] * gu[2]);
-    float gR[3][3];
-    for (int a = 0; a < 3; ++a) {
-      float gs = 0.f;
-      for (int b = 0; b < 3; ++b) {
-        gs += gM[a][b] * M[a][b];
-        gR[b][a] = gM[a][b] / s[a];
+#pragma unroll
+      for (int ch = 0; ch < 3; ++ch) {
+        pos[ch] = acc[ch] > 0.f;
+        c[ch] = pos[ch] ? acc[ch] : 0.f;
       }
-      g_s[a] = -gs / s[a];
+      const Geom g = geometry(shape, o, d);
+      ta = -(g.u[0] * g.v[0] + g.u[1] * g.v[1] + g.u[2] * g.v[2]) / g.vv;
+      const float p[3] = {g.u[0] + ta * g.v[0], g.u[1] + ta * g.v[1], g.u[2] + ta * g.v[2]};
+      G = expf(-0.5f * (p[0] * p[0] + p[1] * p[1] + p[2] * p[2]));
+      alpha = shape.opac * G;
     }
-    // ---- R(qhat) -> qhat -> q
-    const float gw = 2.f * (-z * gR[0][1] + y * gR[0][2] + z * gR[1][0] - x * gR[1][2] - y * gR[2][0] + x * gR[2][1]);
-    const float gx = 2.f * (y * gR[0][1] + z * gR[0][2] + y * gR[1][0] - 2.f * x * gR[1][1] - w * gR[1][2] +
-                            z * gR[2][0] + w * gR[2][1] - 2.f * x * gR[2][2]);
-    const float gy = 2.f * (-2.f * y * gR[0][0] + x * gR[0][1] + w * gR[0][2] + x * gR[1][0] + z * gR[1][2] -
-                            w * gR[2][0] + z * gR[2][1] - 2.f * y * gR[2][2]);
-    const float gz = 2.f * (-2.f * z * gR[0][0] - w * gR[0][1] + x * gR[0][2] + w * gR[1][0] - 2.f * z * gR[1][1] +
-                            y * gR[1][2] + x * gR[2][0] + y * gR[2][1]);
-    const float dot = w * gw + x * gx + y * gy + z * gz;
-    // the id read ahead is in hand before this step's stores go out (an empty asm that
-    // takes it as an input), so the next step does not wait for them
-    asm volatile("" ::"v"(i_ahead));
-    const uint32_t pi = base + (uint32_t)h;
-    float4* rp = A.rec + 4 * (int64_t)pi;
-    rp[0] = make_float4(g_mu[0], g_mu[1], g_mu[2], g_s[0]);
-    rp[1] = make_float4(g_s[1], g_s[2], (gw - w * dot) / qn, (gx - x * dot) / qn);
-    rp[2] = make_float4((gy - y * dot) / qn, (gz - z * dot) / qn, g_op, gcol[0]);
-    rp[3] = make_float4(gcol[1], gcol[2], __uint_as_float((uint32_t)r), 0.f);
-    A.key[pi] = (uint64_t)i;
-    A.val[pi] = pi;
-    i_cur = i_ahead;
+    const int most = max(max(nr[0], nr[1]), max(nr[2], nr[3])) - h0;  // hits of the fullest row here
+    Sums own = run;
+    replay<0>(sub, most, alpha, c, ta, own);
+    // the ray's sums so far, for its next 16 hits: those of its last lane
+    run.T = row_lane<15>(own.T * (1.f - alpha));
+#pragma unroll
+    for (int ch = 0; ch < 3; ++ch) run.C[ch] = row_lane<15>(own.C[ch]);
+    run.D = row_lane<15>(own.D);
+    if (h < n) {
+      // ---- compositing derivatives
+      const float wgt = own.T * alpha;
+      const float inv1ma = 1.f / (1.f - alpha);
+      float gA = 0.f;
+#pragma unroll
+      for (int ch = 0; ch < 3; ++ch) {
+        const float behind = Cf[ch] - own.C[ch];  // S_i (includes T_N bg)
+        gA += gC[ch] * (own.T * c[ch] - behind * inv1ma);
+      }
+      gA += gD * (own.T * ta - (Df - own.D) * inv1ma);
+      gA += gO * (TN * inv1ma);
+      uint32_t pi = base;
+#pragma unroll
+      for (int k = 0; k < 4; ++k) pi += (uint32_t)(min(nr[k], h) + (k < row && nr[k] > h ? 1 : 0));
+      float4* rp = A.rec + 2 * (int64_t)pi;
+      rp[0] = make_float4(gA, gD * wgt, pos[0] ? gC[0] * wgt : 0.f, pos[1] ? gC[1] * wgt : 0.f);
+      rp[1] = make_float4(pos[2] ? gC[2] * wgt : 0.f, __uint_as_float((uint32_t)r), G, ta);
+      A.key[pi] = hit ? (uint32_t)id : (uint32_t)A.n_gauss;  // not a Gaussian of this scene: sorted last
+    }
   }
 }
 
@@ -288,28 +363,20 @@ __global__ void k_bwd_total(const uint32_t* __restrict__ off, const uint32_t* __
   if (threadIdx.x == 0) *total = off[R - 1] + cnt[R - 1];
 }
 
-// Per Gaussian: [first[g], last[g]) in the sorted records (empty when untouched). The
-// number of records is read on the device; a fixed grid strides over them.
-__global__ void __launch_bounds__(kBlock) k_bwd_segments(const uint64_t* __restrict__ key,
-                                                         const uint32_t* __restrict__ total, int64_t n_gauss,
-                                                         uint32_t* __restrict__ first, uint32_t* __restrict__ last) {
-  const int64_t P = *total;
-  for (int64_t p = blockIdx.x * (int64_t)kBlock + threadIdx.x; p < P; p += (int64_t)gridDim.x * kBlock) {
-    const uint64_t k = key[p];
-    if (k >= (uint64_t)n_gauss) continue;
-    if (p == 0 || key[p - 1] != k) first[k] = (uint32_t)p;
-    if (p == P - 1 || key[p + 1] != k) last[k] = (uint32_t)(p + 1);
-  }
+// The sorted records in kShares equal shares of whole tiles of 64, a wave for each: an even
+// split however the records lie among the Gaussians (from none to a hundred thousand each).
+constexpr int kShares = 4096;
+__device__ __forceinline__ int64_t share_size(int64_t P) {
+  return max((int64_t)64, (P + (int64_t)kShares * 64 - 1) / ((int64_t)kShares * 64) * 64);
 }
 
-struct ReduceArgs {
-  const float4* rec;
+struct SumArgs {
+  BwdArgs in;
+  const uint32_t* key;    // sorted
   const uint32_t* order;  // sorted position -> record
-  const uint32_t* first;
-  const uint32_t* last;
-  const float* ray_d;
-  int sh_degree;
-  int64_t n_gauss;
+  const uint32_t* total;
+  float* part;  // [kShares][2][64]: sums of the Gaussian that a share begins inside of, and of
+                // the one that it ends inside of
   float* d_means;
   float* d_scales;
   float* d_quats;
@@ -317,75 +384,198 @@ struct ReduceArgs {
   float* d_sh;
 };
 
-__device__ __forceinline__ float wave_sum(float v) {
-  // fixed butterfly: the same order on every run
+// A record's row in LDS (an odd stride: no bank conflicts): g_u, dL/dM and dL/do, which add up to
+// the gradients of mean, scale, rotation and opacity (the rest is linear and the same for all
+// records of a Gaussian), three colour factors, the basis at its ray and a one.
+constexpr int kTotals = 13;
+constexpr int kRow = kTotals + 3 + 16 + 1;
+__device__ __forceinline__ void record_row(const BwdArgs& A, uint32_t id, uint32_t rec, float* row) {
+  const float4 a = A.rec[2 * (int64_t)rec], b = A.rec[2 * (int64_t)rec + 1];
+  const Shape shape = load_shape(A.gauss, id);
+  const float gA = a.x, gT = a.y, G = b.z, ta = b.w;
+  const int64_t r = __float_as_uint(b.y);
+  const float o[3] = {A.ray_o[3 * r], A.ray_o[3 * r + 1], A.ray_o[3 * r + 2]};
+  const float d[3] = {A.ray_d[3 * r], A.ray_d[3 * r + 1], A.ray_d[3 * r + 2]};
+  const Geom g = geometry(shape, o, d);
+  // ---- alpha -> opacity, m2, t
+  const float gm2 = gA * (-0.5f * (shape.opac * G));
+  const float gTv = gT / g.vv;
 #pragma unroll
-  for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
-  return v;
+  for (int k = 0; k < 3; ++k) {
+    const float p = g.u[k] + ta * g.v[k];
+    const float gu = gm2 * 2.f * p - gTv * g.v[k];
+    const float gv = gm2 * 2.f * ta * p - gTv * (g.u[k] + 2.f * ta * g.v[k]);
+    // ---- u = M f, v = M d
+    row[k] = gu;
+#pragma unroll
+    for (int j = 0; j < 3; ++j) row[3 + 3 * k + j] = gu * g.f[j] + gv * d[j];
+  }
+  row[12] = gA * G;
+  // ---- SH: dL/dsh = colour factor x Y
+  row[kTotals] = a.z;
+  row[kTotals + 1] = a.w;
+  row[kTotals + 2] = b.x;
+  const float dn = rsqrtf(d[0] * d[0] + d[1] * d[1] + d[2] * d[2]);
+  float Y[16];
+#pragma unroll
+  for (int k = 0; k < 16; ++k) Y[k] = 0.f;
+  basis(d[0] * dn, d[1] * dn, d[2] * dn, A.sh_degree, Y);
+#pragma unroll
+  for (int k = 0; k < 16; ++k) row[kTotals + 3 + k] = Y[k];
+  row[kRow - 1] = 1.f;
 }
 
-// One wave per Gaussian: lanes take the Gaussian's records in sorted order with stride 64,
-// sum them, and the wave adds the totals to the caller's arrays (no other wave writes
-// them, so plain read-add-write).
-__global__ void __launch_bounds__(kBlock) k_bwd_reduce(ReduceArgs A) {
-  const int64_t g = (blockIdx.x * (int64_t)kBlock + threadIdx.x) >> 6;
-  const int lane = threadIdx.x & 63;
-  if (g >= A.n_gauss) return;
-  const uint32_t b = A.first[g], e = A.last[g];
-  if (e <= b) return;
-  const int ncoef = (A.sh_degree + 1) * (A.sh_degree + 1);
-  float acc[11];
-  float sh[16][3];
+// From a Gaussian's totals to its gradients.
+__device__ __forceinline__ void add_shape(const SumArgs& A, int64_t i, const float* total) {
+  const Shape shape = load_shape(A.in.gauss, i);
+  const float4 q4 = reinterpret_cast<const float4*>(A.in.quats)[i];
+  const float qn = sqrtf(q4.x * q4.x + q4.y * q4.y + q4.z * q4.z + q4.w * q4.w);
+  const float w = q4.x / qn, x = q4.y / qn, y = q4.z / qn, z = q4.w / qn;
+  float gR[3][3];
 #pragma unroll
-  for (int q = 0; q < 11; ++q) acc[q] = 0.f;
+  for (int k = 0; k < 3; ++k) {
+    A.d_means[3 * i + k] += -(shape.M[0][k] * total[0] + shape.M[1][k] * total[1] + shape.M[2][k] * total[2]);
+    const float s = A.in.scales[3 * i + k];
+    float gs = 0.f;
 #pragma unroll
-  for (int k = 0; k < 16; ++k) sh[k][0] = sh[k][1] = sh[k][2] = 0.f;
-  for (uint32_t p = b + lane; p < e; p += 64) {
-    const float4* rp = A.rec + 4 * (int64_t)A.order[p];
-    const float4 q0 = rp[0], q1 = rp[1], q2 = rp[2], q3 = rp[3];
-    acc[0] += q0.x; acc[1] += q0.y; acc[2] += q0.z; acc[3] += q0.w;
-    acc[4] += q1.x; acc[5] += q1.y; acc[6] += q1.z; acc[7] += q1.w;
-    acc[8] += q2.x; acc[9] += q2.y; acc[10] += q2.z;
-    const int64_t r = __float_as_uint(q3.z);
-    const float dx = A.ray_d[3 * r], dy = A.ray_d[3 * r + 1], dz = A.ray_d[3 * r + 2];
-    const float dn = rsqrtf(dx * dx + dy * dy + dz * dz);
-    float Y[16];
-    basis(dx * dn, dy * dn, dz * dn, A.sh_degree, Y);
-    const float gc[3] = {q2.w, q3.x, q3.y};
-#pragma unroll
-    for (int k = 0; k < 16; ++k)
-      if (k < ncoef) {
-        sh[k][0] += gc[0] * Y[k];
-        sh[k][1] += gc[1] * Y[k];
-        sh[k][2] += gc[2] * Y[k];
-      }
-  }
-#pragma unroll
-  for (int q = 0; q < 11; ++q) acc[q] = wave_sum(acc[q]);
-#pragma unroll
-  for (int k = 0; k < 16; ++k)
-    if (k < ncoef) {
-      sh[k][0] = wave_sum(sh[k][0]);
-      sh[k][1] = wave_sum(sh[k][1]);
-      sh[k][2] = wave_sum(sh[k][2]);
+    for (int j = 0; j < 3; ++j) {
+      gs += total[3 + 3 * k + j] * shape.M[k][j];
+      gR[j][k] = total[3 + 3 * k + j] / s;
     }
-  if (lane == 0) {
-    for (int a = 0; a < 3; ++a) A.d_means[3 * g + a] += acc[a];
-    for (int a = 0; a < 3; ++a) A.d_scales[3 * g + a] += acc[3 + a];
-    for (int a = 0; a < 4; ++a) A.d_quats[4 * g + a] += acc[6 + a];
-    A.d_opac[g] += acc[10];
-    for (int k = 0; k < 16; ++k)
-      if (k < ncoef)
-        for (int ch = 0; ch < 3; ++ch) A.d_sh[g * 3 * ncoef + 3 * k + ch] += sh[k][ch];
+    A.d_scales[3 * i + k] += -gs / s;
   }
+  // ---- R(qhat) -> qhat -> q
+  const float gw = 2.f * (-z * gR[0][1] + y * gR[0][2] + z * gR[1][0] - x * gR[1][2] - y * gR[2][0] + x * gR[2][1]);
+  const float gx = 2.f * (y * gR[0][1] + z * gR[0][2] + y * gR[1][0] - 2.f * x * gR[1][1] - w * gR[1][2] +
+                          z * gR[2][0] + w * gR[2][1] - 2.f * x * gR[2][2]);
+  const float gy = 2.f * (-2.f * y * gR[0][0] + x * gR[0][1] + w * gR[0][2] + x * gR[1][0] + z * gR[1][2] -
+                          w * gR[2][0] + z * gR[2][1] - 2.f * y * gR[2][2]);
+  const float gz = 2.f * (-2.f * z * gR[0][0] - w * gR[0][1] + x * gR[0][2] + w * gR[1][0] - 2.f * z * gR[1][1] +
+                          y * gR[1][2] + x * gR[2][0] + y * gR[2][1]);
+  const float dot = w * gw + x * gx + y * gy + z * gz;
+  A.d_quats[4 * i] += (gw - w * dot) / qn;
+  A.d_quats[4 * i + 1] += (gx - x * dot) / qn;
+  A.d_quats[4 * i + 2] += (gy - y * dot) / qn;
+  A.d_quats[4 * i + 3] += (gz - z * dot) / qn;
+  A.d_opac[i] += total[12];
+}
+
+// One share of the sorted records, 64 at a time: a lane turns one into its row, then every lane
+// adds up one of the 61 totals over the rows, four partial sums at a time, and passes it on when
+// the Gaussian changes: SH at once, 48 neighbouring floats, the others by a lane per Gaussian,
+// kWaiting of them at a time. Two LDS reads and one fma per record for all 61 (a wave per
+// Gaussian that ended in 59 sums over its lanes spent its time on those: 354 shuffles for some
+// 30 records): 611 us for 10.7M hits, 239 us so, bound by the records' lines (128 bytes
+// fetched for 32).
+constexpr int kWaiting = 24;
+__global__ void __launch_bounds__(64) k_bwd_sums(SumArgs A) {
+  __shared__ float s_row[64 * kRow];
+  __shared__ float s_total[kWaiting][kTotals];
+  __shared__ uint32_t s_id[kWaiting];
+  const int lane = threadIdx.x;
+  const int64_t P = *A.total;
+  const int64_t size = share_size(P);
+  const int64_t begin = blockIdx.x * size;
+  const int64_t end = min(P, begin + size);
+  if (begin >= end) return;
+  const uint32_t none = (uint32_t)A.in.n_gauss;
+  const int nsh = 3 * (A.in.sh_degree + 1) * (A.in.sh_degree + 1);
+  const int ia = lane < 48 ? kTotals + lane % 3 : lane < 48 + kTotals ? lane - 48 : 0;
+  const int ib = lane < 48 ? kTotals + 3 + lane / 3 : kRow - 1;
+  uint32_t cur = A.key[begin];
+  bool inside = begin > 0 && A.key[begin - 1] == cur;  // its first records are another share's
+  float sum[4] = {0.f, 0.f, 0.f, 0.f};
+  int waiting = 0;
+  float sh = lane < nsh && cur < none ? A.d_sh[(int64_t)cur * nsh + lane] : 0.f;  // read ahead
+  auto finish = [&]() {
+    __syncthreads();
+    if (lane < waiting) add_shape(A, s_id[lane], s_total[lane]);
+    __syncthreads();
+    waiting = 0;
+  };
+  auto pass_on = [&](bool goes_on) {
+    const float all = (sum[0] + sum[1]) + (sum[2] + sum[3]);
+    if (inside || goes_on) {
+      A.part[(int64_t)blockIdx.x * 128 + (inside ? 0 : 64) + lane] = all;
+    } else if (cur < none) {
+      if (lane < nsh)
+        A.d_sh[(int64_t)cur * nsh + lane] = sh + all;
+      if (lane >= 48 && lane < 48 + kTotals) s_total[waiting][lane - 48] = all;
+      if (lane == 0) s_id[waiting] = cur;
+      if (++waiting == kWaiting) finish();
+    }
+  };
+  uint32_t k_ahead = A.key[min(begin + lane, end - 1)], p_ahead = A.order[min(begin + lane, end - 1)];
+  for (int64_t t = begin; t < end; t += 64) {
+    const uint32_t k = k_ahead, rec = p_ahead;
+    const int64_t next = min(t + 64 + lane, end - 1);
+    k_ahead = A.key[next];
+    p_ahead = A.order[next];
+    const int n = (int)min((int64_t)64, end - t);
+    if (lane < n && k < none) record_row(A.in, k, rec, s_row + lane * kRow);
+    const uint32_t before = __shfl_up(k, 1);
+    const uint64_t starts = __ballot(lane < n && k != (lane == 0 ? cur : before));
+    __syncthreads();
+    for (int j = 0; j < n;) {
+      if ((starts >> j) & 1) {
+        pass_on(false);
+        inside = false;
+        sum[0] = sum[1] = sum[2] = sum[3] = 0.f;
+        cur = __builtin_amdgcn_readlane(k, j);
+        sh = lane < nsh && cur < none ? A.d_sh[(int64_t)cur * nsh + lane] : 0.f;
+      }
+      const uint64_t rest = j == 63 ? 0 : starts >> (j + 1);
+      const int stop = rest ? min(n, j + 1 + __builtin_ctzll(rest)) : n;
+      if (cur >= none) {
+        j = stop;
+        continue;
+      }
+      for (; j + 4 <= stop; j += 4) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) sum[q] += s_row[(j + q) * kRow + ia] * s_row[(j + q) * kRow + ib];
+      }
+      if (j < stop) sum[0] += s_row[j * kRow + ia] * s_row[j * kRow + ib];
+      if (j + 1 < stop) sum[1] += s_row[(j + 1) * kRow + ia] * s_row[(j + 1) * kRow + ib];
+      if (j + 2 < stop) sum[2] += s_row[(j + 2) * kRow + ia] * s_row[(j + 2) * kRow + ib];
+      j = stop;
+    }
+    __syncthreads();
+  }
+  pass_on(end < P && A.key[end] == cur);
+  finish();
+}
+
+// The Gaussians whose records reach over the end of a share: the share in which one begins adds
+// up its own part and those of the shares that follow.
+__global__ void __launch_bounds__(64) k_bwd_join(SumArgs A) {
+  __shared__ float s_total[kTotals];
+  const int lane = threadIdx.x;
+  const int64_t P = *A.total;
+  const int64_t size = share_size(P);
+  const int64_t begin = blockIdx.x * size;
+  const int64_t end = begin + size;
+  if (end >= P) return;
+  const uint32_t cur = A.key[end];
+  if (cur >= (uint32_t)A.in.n_gauss || A.key[end - 1] != cur) return;
+  if (begin > 0 && A.key[begin - 1] == cur) return;  // it began in an earlier share
+  float all = A.part[(int64_t)blockIdx.x * 128 + 64 + lane];
+  for (int64_t c = blockIdx.x + 1; c * size < P; c += 64) {
+    // how many of the next 64 shares begin inside of it
+    const int64_t at = (c + lane) * size;
+    const uint64_t in = __ballot(at < P && A.key[min(at, P - 1)] == cur);
+    const int n = in == ~0ull ? 64 : __builtin_ctzll(~in);
+#pragma unroll 8
+    for (int j = 0; j < n; ++j) all += A.part[(c + j) * 128 + lane];
+    if (n < 64) break;
+  }
+  const int nsh = 3 * (A.in.sh_degree + 1) * (A.in.sh_degree + 1);
+  if (lane < nsh) A.d_sh[(int64_t)cur * nsh + lane] += all;
+  if (lane >= 48 && lane < 48 + kTotals) s_total[lane - 48] = all;
+  __syncthreads();
+  if (lane == 0) add_shape(A, cur, s_total);
 }
 
 __global__ void k_zero_u32(unsigned int* p) { *p = 0u; }
-
-__global__ void __launch_bounds__(kBlock) k_fill_u32_bwd(uint32_t* p, int64_t n) {
-  const int64_t i = blockIdx.x * (int64_t)kBlock + threadIdx.x;
-  if (i < n) p[i] = 0u;
-}
 
 inline unsigned grid(int64_t n, int per = kBlock) { return (unsigned)std::max<int64_t>(1, (n + per - 1) / per); }
 
@@ -455,50 +645,42 @@ grtx_status trace_backward(const Bvh* bvh, const grtx_gaussians* g, const grtx_r
   a.hit_ids = fo.hit_ids;
   a.hit_counts = fo.hit_counts;
   a.hit_cap = cap;
-  a.bg0 = p->bg[0];
-  a.bg1 = p->bg[1];
-  a.bg2 = p->bg[2];
   a.g_rgb = grad_rgb;
   a.g_depth = grad_depth;
   a.g_opacity = grad_opacity;
   a.n_gauss = N;
   a.pair_off = off;
-  GRTX_TRY(sc.get(&a.rec, 4 * Pmax));
+  GRTX_TRY(sc.get(&a.gauss, 4 * N));
+  hipLaunchKernelGGL(k_bwd_shapes, dim3(grid(N)), dim3(kBlock), 0, s, a);
+  GRTX_TRY(sc.get(&a.rec, 2 * Pmax));
   GRTX_TRY(sc.get(&a.key, Pmax));
-  GRTX_TRY(sc.get(&a.val, Pmax));
-  a.truncated = truncated;
-  hipLaunchKernelGGL(k_bwd_pairs, dim3(grid(R)), dim3(kBlock), 0, s, a);
+  if (g->sh_degree == 3)
+    hipLaunchKernelGGL(k_bwd_hits<true>, dim3(grid(R * kLanes)), dim3(kBlock), 0, s, a);
+  else
+    hipLaunchKernelGGL(k_bwd_hits<false>, dim3(grid(R * kLanes)), dim3(kBlock), 0, s, a);
   GRTX_LAUNCH_CHECK();
   // 3. group by Gaussian, keeping ray order inside a Gaussian
   int bits = 1;  // keys are 0..N (N marks a record of no Gaussian)
-  while (bits < 63 && ((int64_t)1 << bits) <= N) ++bits;
-  uint64_t *tkeys = nullptr, *skey = nullptr;
-  uint32_t *tvals = nullptr, *sval = nullptr;
+  while (bits < 32 && ((int64_t)1 << bits) <= N) ++bits;
+  uint32_t *vals = nullptr, *tkeys = nullptr, *tvals = nullptr, *skey = nullptr, *sval = nullptr;
+  GRTX_TRY(sc.get(&vals, Pmax));
   GRTX_TRY(sc.get(&tkeys, Pmax));
   GRTX_TRY(sc.get(&tvals, Pmax));
-  GRTX_TRY(sort_by_key_into(a.key, a.val, tkeys, tvals, Pmax, bits, s, total, &skey, &sval));
-  // 4. segments and per-Gaussian sums
-  uint32_t *first = nullptr, *last = nullptr;
-  GRTX_TRY(sc.get(&first, N));
-  GRTX_TRY(sc.get(&last, N));
-  hipLaunchKernelGGL(k_fill_u32_bwd, dim3(grid(N)), dim3(kBlock), 0, s, first, N);
-  hipLaunchKernelGGL(k_fill_u32_bwd, dim3(grid(N)), dim3(kBlock), 0, s, last, N);
-  hipLaunchKernelGGL(k_bwd_segments, dim3((unsigned)std::min<int64_t>(4096, grid(Pmax))), dim3(kBlock), 0, s, skey,
-                     total, N, first, last);
-  ReduceArgs ra{};
-  ra.rec = a.rec;
-  ra.order = sval;
-  ra.first = first;
-  ra.last = last;
-  ra.ray_d = r->dirs;
-  ra.sh_degree = g->sh_degree;
-  ra.n_gauss = N;
-  ra.d_means = grads->means;
-  ra.d_scales = grads->scales;
-  ra.d_quats = grads->quats;
-  ra.d_opac = grads->opacities;
-  ra.d_sh = grads->sh;
-  hipLaunchKernelGGL(k_bwd_reduce, dim3(grid(N * 64)), dim3(kBlock), 0, s, ra);
+  GRTX_TRY(sort_positions(a.key, vals, tkeys, tvals, Pmax, bits, s, total, &skey, &sval));
+  // 4. per-Gaussian sums
+  SumArgs sa{};
+  sa.in = a;
+  sa.key = skey;
+  sa.order = sval;
+  sa.total = total;
+  GRTX_TRY(sc.get(&sa.part, (size_t)kShares * 2 * 64));
+  sa.d_means = grads->means;
+  sa.d_scales = grads->scales;
+  sa.d_quats = grads->quats;
+  sa.d_opac = grads->opacities;
+  sa.d_sh = grads->sh;
+  hipLaunchKernelGGL(k_bwd_sums, dim3(kShares), dim3(64), 0, s, sa);
+  hipLaunchKernelGGL(k_bwd_join, dim3(kShares), dim3(64), 0, s, sa);
   GRTX_LAUNCH_CHECK();
   return GRTX_OK;
 }

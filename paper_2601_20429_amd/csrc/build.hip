@@ -5,7 +5,7 @@
 //   bounds of the centroids (two-stage min/max, exact)
 //   63-bit Morton codes (binary32 quantisation with fp contraction off, so the codes are
 //     an exact integer function of the inputs)
-//   stable LSD radix sort of (code, index), 8 passes of 8 bits
+//   stable LSD radix sort of the codes with their positions, 8 passes of 8 bits
 //   leaf records and leaf boxes in sorted order, and the boxes of 2, 4, 8, ... leaves
 //   radix tree over the sorted (code, position) keys (Karras 2012, one thread per node, which
 //   also forms its box: exact min/max), with the subtrees of the next step and a subtree cut
@@ -107,8 +107,7 @@ __device__ __forceinline__ uint32_t quantise(float v, float lo, float scale) {
 }
 
 __global__ void __launch_bounds__(kBlock) k_morton(const float* __restrict__ pts, int64_t n,
-                                                   const float* __restrict__ bounds, uint64_t* __restrict__ codes,
-                                                   uint32_t* __restrict__ idx) {
+                                                   const float* __restrict__ bounds, uint64_t* __restrict__ codes) {
 #pragma clang fp contract(off)
   int64_t i = blockIdx.x * (int64_t)kBlock + threadIdx.x;
   if (i >= n) return;
@@ -120,7 +119,6 @@ __global__ void __launch_bounds__(kBlock) k_morton(const float* __restrict__ pts
     q[a] = quantise(pts[3 * i + a], lo, scale);
   }
   codes[i] = (spread3(q[0]) << 2) | (spread3(q[1]) << 1) | spread3(q[2]);
-  idx[i] = (uint32_t)i;
 }
 
 // ------------------------------------------------------------------ radix sort (stable LSD)
@@ -134,19 +132,38 @@ constexpr int64_t kRadixSmall = (int64_t)256 * kBlock * kRadixItemsSmall;
 // histogram table (a digit's counts over all workgroups), so no scan launch is needed.
 constexpr int kRadixFusedBlocks = 256;
 
+// A sort whose number of keys only the device knows gets a sixteenth of the workgroups that its
+// bound would need (a ray lists far fewer hits than its list holds), within these limits; each
+// takes as many consecutive tiles as the true number asks for. With a workgroup per tile of the
+// bound, the table of counts itself (33 MB for 512x512 rays x 512 hits) took most of the time:
+// 240 us a pass for 10.7M keys, 109 us now.
+constexpr int kRadixDeviceBlocks = 1024;
+
+// Tiles that each of `nblocks` workgroups takes.
+__device__ __forceinline__ int64_t radix_tiles(int64_t n, int64_t tile, int nblocks) {
+  return max((int64_t)1, (n + tile * nblocks - 1) / (tile * nblocks));
+}
+
 // `n_dev` (may be null) holds the number of keys on the device when the host knows only a
-// bound `n` (the grid is sized for the bound; workgroups past the count see no keys).
-__global__ void __launch_bounds__(kBlock) k_radix_hist(const uint64_t* __restrict__ keys, int64_t n, int shift,
-                                                       int items, uint32_t* __restrict__ hist, int nblocks,
-                                                       bool fused, const uint32_t* __restrict__ n_dev) {
+// bound `n` (workgroups past the count see no keys).
+template <class K>
+__global__ void __launch_bounds__(kBlock) k_radix_hist(const K* __restrict__ keys, int64_t n, int shift, int items,
+                                                       uint32_t* __restrict__ hist, int nblocks, bool fused,
+                                                       const uint32_t* __restrict__ n_dev) {
   if (n_dev) n = min(n, (int64_t)*n_dev);
   __shared__ uint32_t s_cnt[256];
   s_cnt[threadIdx.x] = 0;
   __syncthreads();
-  int64_t base = (int64_t)blockIdx.x * kBlock * items;
-  for (int r = 0; r < items; ++r) {
-    int64_t i = base + r * kBlock + threadIdx.x;
-    if (i < n) atomicAdd(&s_cnt[(keys[i] >> shift) & 255u], 1u);
+  const int64_t span = radix_tiles(n, (int64_t)kBlock * items, nblocks) * kBlock * items;
+  const int64_t base = (int64_t)blockIdx.x * span;
+  const int64_t end = min(n, base + span);
+  for (int64_t i0 = base + threadIdx.x; i0 < end; i0 += kBlock * kRadixItems) {
+    K key[kRadixItems];  // (all loads in flight together)
+#pragma unroll
+    for (int r = 0; r < kRadixItems; ++r) key[r] = i0 + r * kBlock < end ? keys[i0 + r * kBlock] : (K)0;
+#pragma unroll
+    for (int r = 0; r < kRadixItems; ++r)
+      if (i0 + r * kBlock < end) atomicAdd(&s_cnt[(uint32_t)(key[r] >> shift) & 255u], 1u);
   }
   __syncthreads();
   // digit-major ([digit][workgroup]) for the scan; workgroup-major rows for the fused scatter
@@ -158,19 +175,26 @@ constexpr int kScanItems = 16;
 constexpr int kScanChunk = kBlock * kScanItems;
 
 __device__ uint32_t block_exclusive_scan(uint32_t v, uint32_t* s_tmp, uint32_t* total) {
-  // Hillis-Steele over kBlock values in LDS.
-  s_tmp[threadIdx.x] = v;
-  __syncthreads();
-  for (int off = 1; off < kBlock; off <<= 1) {
-    uint32_t add = threadIdx.x >= off ? s_tmp[threadIdx.x - off] : 0u;
-    __syncthreads();
-    s_tmp[threadIdx.x] += add;
-    __syncthreads();
+  // A wave by shuffles, then the waves' sums (in s_tmp) by everyone: two barriers.
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  uint32_t incl = v;
+#pragma unroll
+  for (int off = 1; off < 64; off <<= 1) {
+    const uint32_t x = __shfl_up(incl, off);
+    incl += lane >= off ? x : 0u;
   }
-  uint32_t incl = s_tmp[threadIdx.x];
-  *total = s_tmp[kBlock - 1];
+  if (lane == 63) s_tmp[wave] = incl;
   __syncthreads();
-  return incl - v;
+  uint32_t before = 0, all = 0;
+#pragma unroll
+  for (int w = 0; w < kBlock / 64; ++w) {
+    const uint32_t x = s_tmp[w];
+    before += w < wave ? x : 0u;
+    all += x;
+  }
+  *total = all;
+  __syncthreads();
+  return before + incl - v;
 }
 
 __global__ void __launch_bounds__(kBlock) k_scan_reduce(const uint32_t* __restrict__ in, int64_t n,
@@ -260,30 +284,25 @@ __global__ void __launch_bounds__(kBlock) k_scan_loop(const uint32_t* __restrict
 // no barrier between rounds; then the waves' counts are added up once. Bound by latency at 100k
 // keys (10 us a pass), by memory at 3M (28 us for 72 MB; 53 before, with four barriers a round
 // and the keys written where they stood; 61 without the barriers but not through LDS).
-template <int ITEMS>
-__global__ void __launch_bounds__(kBlock) k_radix_scatter(const uint64_t* __restrict__ keys_in,
+template <class K, int ITEMS>
+__global__ void __launch_bounds__(kBlock) k_radix_scatter(const K* __restrict__ keys_in,
                                                           const uint32_t* __restrict__ vals_in, int64_t n, int shift,
                                                           const uint32_t* __restrict__ offsets, int nblocks, bool fused,
-                                                          uint64_t* __restrict__ keys_out,
-                                                          uint32_t* __restrict__ vals_out,
+                                                          K* __restrict__ keys_out, uint32_t* __restrict__ vals_out,
                                                           const uint32_t* __restrict__ n_dev,
                                                           uint32_t* __restrict__ next_hist) {
   if (n_dev) n = min(n, (int64_t)*n_dev);
-  if ((int64_t)blockIdx.x * kBlock * ITEMS >= n) return;  // the whole workgroup is past the keys
+  constexpr int kTile = kBlock * ITEMS;
+  const int64_t span = radix_tiles(n, kTile, nblocks) * kTile;
+  const int64_t begin = (int64_t)blockIdx.x * span;
+  if (begin >= n) return;  // the whole workgroup is past the keys
   __shared__ uint32_t s_cnt[kBlock / 64][256];
   __shared__ uint32_t s_tmp[kBlock];
-  __shared__ uint64_t s_key[ITEMS == kRadixItems ? kBlock * ITEMS : 1];
-  __shared__ uint32_t s_val[ITEMS == kRadixItems ? kBlock * ITEMS : 1];
+  __shared__ K s_key[ITEMS == kRadixItems ? kTile : 1];
+  __shared__ uint32_t s_val[ITEMS == kRadixItems ? kTile : 1];
   const int lane = threadIdx.x & 63;
   const int wave = threadIdx.x >> 6;
   const uint64_t lt_mask = lane ? (~0ull >> (64 - lane)) : 0ull;
-  const int64_t first = (int64_t)blockIdx.x * kBlock * ITEMS + wave * (64 * ITEMS) + lane;
-  uint64_t key[ITEMS];
-#pragma unroll
-  for (int r = 0; r < ITEMS; ++r) key[r] = first + r * 64 < n ? keys_in[first + r * 64] : 0ull;
-  uint32_t val[ITEMS];
-#pragma unroll
-  for (int r = 0; r < ITEMS; ++r) val[r] = first + r * 64 < n ? vals_in[first + r * 64] : 0u;
   uint32_t off;
   if (fused) {
     // (32 rows' loads in flight together: the rows come from beyond this XCD's L2)
@@ -310,83 +329,98 @@ __global__ void __launch_bounds__(kBlock) k_radix_scatter(const uint64_t* __rest
   } else {
     off = offsets[(size_t)threadIdx.x * nblocks + blockIdx.x];
   }
-  for (int w = 0; w < kBlock / 64; ++w) s_cnt[w][threadIdx.x] = 0u;
-  __syncthreads();
-  uint32_t rank[ITEMS];
+  const int64_t stop = min(n, begin + span);
+  for (int64_t tile = begin; tile < stop; tile += kTile) {
+    const int64_t first = tile + wave * (64 * ITEMS) + lane;
+    K key[ITEMS];
 #pragma unroll
-  for (int r = 0; r < ITEMS; ++r) {
-    const bool valid = first + r * 64 < n;
-    const uint32_t digit = (uint32_t)(key[r] >> shift) & 255u;
-    uint64_t peers = __ballot(valid);
+    for (int r = 0; r < ITEMS; ++r) key[r] = first + r * 64 < n ? keys_in[first + r * 64] : (K)0;
+    uint32_t val[ITEMS];
 #pragma unroll
-    for (int b = 0; b < 8; ++b) {
-      const bool bit = (digit >> b) & 1u;
-      const uint64_t m = __ballot(valid && bit);
-      peers &= bit ? m : ~m;
+    for (int r = 0; r < ITEMS; ++r)
+      val[r] = !vals_in ? (uint32_t)(first + r * 64) : first + r * 64 < n ? vals_in[first + r * 64] : 0u;
+    for (int w = 0; w < kBlock / 64; ++w) s_cnt[w][threadIdx.x] = 0u;
+    __syncthreads();
+    uint32_t rank[ITEMS];
+#pragma unroll
+    for (int r = 0; r < ITEMS; ++r) {
+      const bool valid = first + r * 64 < n;
+      const uint32_t digit = (uint32_t)(key[r] >> shift) & 255u;
+      uint64_t peers = __ballot(valid);
+#pragma unroll
+      for (int b = 0; b < 8; ++b) {
+        const bool bit = (digit >> b) & 1u;
+        const uint64_t m = __ballot(valid && bit);
+        peers &= bit ? m : ~m;
+      }
+      const uint32_t in_round = (uint32_t)__popcll(peers & lt_mask);
+      const uint32_t before = s_cnt[wave][digit];
+      rank[r] = before + in_round;
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+      if (valid && in_round == 0) s_cnt[wave][digit] = before + (uint32_t)__popcll(peers);
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+      __builtin_amdgcn_wave_barrier();
     }
-    const uint32_t in_round = (uint32_t)__popcll(peers & lt_mask);
-    const uint32_t before = s_cnt[wave][digit];
-    rank[r] = before + in_round;
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    if (valid && in_round == 0) s_cnt[wave][digit] = before + (uint32_t)__popcll(peers);
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-  }
-  __syncthreads();
-  if constexpr (ITEMS == kRadixItems) {
-    // large sorts go through LDS in their new order, so that runs of a digit are written
-    // together
+    __syncthreads();
     uint32_t mine = 0;
 #pragma unroll
     for (int w = 0; w < kBlock / 64; ++w) mine += s_cnt[w][threadIdx.x];
-    uint32_t all;
-    uint32_t at = block_exclusive_scan(mine, s_tmp, &all);
-    s_tmp[threadIdx.x] = off - at;  // from a place here to its place in the result
+    if constexpr (ITEMS == kRadixItems) {
+      // large sorts go through LDS in their new order, so that runs of a digit are written
+      // together
+      uint32_t all;
+      uint32_t at = block_exclusive_scan(mine, s_tmp, &all);
+      s_tmp[threadIdx.x] = off - at;  // from a place here to its place in the result
 #pragma unroll
-    for (int w = 0; w < kBlock / 64; ++w) {
-      const uint32_t c = s_cnt[w][threadIdx.x];
-      s_cnt[w][threadIdx.x] = at;
-      at += c;
-    }
-    __syncthreads();
-#pragma unroll
-    for (int r = 0; r < ITEMS; ++r)
-      if (first + r * 64 < n) {
-        const uint32_t i = s_cnt[wave][(uint32_t)(key[r] >> shift) & 255u] + rank[r];
-        s_key[i] = key[r];
-        s_val[i] = val[r];
+      for (int w = 0; w < kBlock / 64; ++w) {
+        const uint32_t c = s_cnt[w][threadIdx.x];
+        s_cnt[w][threadIdx.x] = at;
+        at += c;
       }
-    __syncthreads();
+      __syncthreads();
 #pragma unroll
-    for (int r = 0; r < ITEMS; ++r) {
-      const uint32_t i = (uint32_t)(r * kBlock) + threadIdx.x;
-      if (i < all) {
-        const uint64_t k = s_key[i];
-        const uint32_t pos = s_tmp[(uint32_t)(k >> shift) & 255u] + i;
-        keys_out[pos] = k;
-        vals_out[pos] = s_val[i];
+      for (int r = 0; r < ITEMS; ++r)
+        if (first + r * 64 < n) {
+          const uint32_t i = s_cnt[wave][(uint32_t)(key[r] >> shift) & 255u] + rank[r];
+          s_key[i] = key[r];
+          s_val[i] = val[r];
+        }
+      __syncthreads();
+#pragma unroll
+      for (int r = 0; r < ITEMS; ++r) {
+        const uint32_t i = (uint32_t)(r * kBlock) + threadIdx.x;
+        if (i < all) {
+          const K k = s_key[i];
+          const uint32_t pos = s_tmp[(uint32_t)(k >> shift) & 255u] + i;
+          keys_out[pos] = k;
+          vals_out[pos] = s_val[i];
+        }
+      }
+    } else {
+      uint32_t at = off;
+#pragma unroll
+      for (int w = 0; w < kBlock / 64; ++w) {
+        const uint32_t c = s_cnt[w][threadIdx.x];
+        s_cnt[w][threadIdx.x] = at;
+        at += c;
+      }
+      __syncthreads();
+#pragma unroll
+      for (int r = 0; r < ITEMS; ++r) {
+        if (first + r * 64 < n) {
+          const uint32_t pos = s_cnt[wave][(uint32_t)(key[r] >> shift) & 255u] + rank[r];
+          keys_out[pos] = key[r];
+          vals_out[pos] = val[r];
+          // counted for the next pass, in the row of the workgroup that will read the key
+          // (these sorts have a workgroup for each tile)
+          if (next_hist)
+            atomicAdd(next_hist + (size_t)(pos / (uint32_t)kTile) * 256 + ((uint32_t)(key[r] >> (shift + 8)) & 255u), 1u);
+        }
       }
     }
-  } else {
-#pragma unroll
-    for (int w = 0; w < kBlock / 64; ++w) {
-      const uint32_t c = s_cnt[w][threadIdx.x];
-      s_cnt[w][threadIdx.x] = off;
-      off += c;
-    }
-    __syncthreads();
-#pragma unroll
-    for (int r = 0; r < ITEMS; ++r) {
-      if (first + r * 64 < n) {
-        const uint32_t pos = s_cnt[wave][(uint32_t)(key[r] >> shift) & 255u] + rank[r];
-        keys_out[pos] = key[r];
-        vals_out[pos] = val[r];
-        // counted for the next pass, in the row of the workgroup that will read the key
-        if (next_hist)
-          atomicAdd(next_hist + (size_t)(pos / (uint32_t)(kBlock * ITEMS)) * 256 + ((key[r] >> (shift + 8)) & 255u), 1u);
-      }
-    }
+    off += mine;
+    if (tile + kTile < stop) __syncthreads();
   }
 }
 
@@ -1008,26 +1042,31 @@ inline unsigned grid_for(int64_t n) { return (unsigned)std::max<int64_t>(1, (n +
 
 
 
-grtx_status radix_sort(uint64_t* keys, uint32_t* vals, uint64_t* tkeys, uint32_t* tvals, int64_t n, Scratch& sc,
-                       hipStream_t s, int passes = 8, const uint32_t* n_dev = nullptr, uint64_t** kres = nullptr,
+// Sorts `keys`; `vals` receives, for each, the position it came from.
+template <class K>
+grtx_status radix_sort(K* keys, uint32_t* vals, K* tkeys, uint32_t* tvals, int64_t n, Scratch& sc, hipStream_t s,
+                       int passes = 8, const uint32_t* n_dev = nullptr, K** kres = nullptr,
                        uint32_t** vres = nullptr) {
   const int items = n <= kRadixSmall ? kRadixItemsSmall : kRadixItems;
   const int64_t tile = (int64_t)kBlock * items;
-  int nblocks = (int)((n + tile - 1) / tile);
+  const int64_t tiles = (n + tile - 1) / tile;
+  if (tiles > (int64_t)kScanChunk * kScanChunk / 256) {
+    set_error("radix sort: %lld keys exceed the supported size", (long long)n);
+    return GRTX_ERR_INVALID_ARG;
+  }
+  int nblocks = (int)tiles;
+  if (n_dev && nblocks > kRadixFusedBlocks)
+    nblocks = std::max(kRadixFusedBlocks, std::min(kRadixDeviceBlocks, nblocks / 16));
   const bool fused = nblocks <= kRadixFusedBlocks;
   int64_t hn = (int64_t)256 * nblocks;
   uint32_t *hist = nullptr, *offs = nullptr, *part = nullptr;
   int nparts = (int)((hn + kScanChunk - 1) / kScanChunk);
-  if (nparts > kScanChunk) {
-    set_error("radix sort: %lld keys exceed the supported size", (long long)n);
-    return GRTX_ERR_INVALID_ARG;
-  }
   GRTX_TRY(sc.get(&hist, hn));
   GRTX_TRY(sc.get(&offs, hn));
   GRTX_TRY(sc.get(&part, nparts));
-  uint64_t* kin = keys;
+  K* kin = keys;
   uint32_t* vin = vals;
-  uint64_t* kout = tkeys;
+  K* kout = tkeys;
   uint32_t* vout = tvals;
   // Small fused sorts count the next pass's digits in the scatter (cleared rows of their own per
   // pass), so that only the first pass has a counting kernel: 12 against 14 us a pass at 100k
@@ -1041,27 +1080,24 @@ grtx_status radix_sort(uint64_t* keys, uint32_t* vals, uint64_t* tkeys, uint32_t
   for (int pass = 0; pass < passes; ++pass) {
     int shift = 8 * pass;
     if (!counts_next || pass == 0)
-      hipLaunchKernelGGL(k_radix_hist, dim3(nblocks), dim3(kBlock), 0, s, kin, n, shift, items, hist, nblocks, fused,
+      hipLaunchKernelGGL(k_radix_hist<K>, dim3(nblocks), dim3(kBlock), 0, s, kin, n, shift, items, hist, nblocks, fused,
                          n_dev);
     if (fused) {
       // the scatter turns the counts into offsets itself
-    } else if (nparts > 1 && nparts <= kScanLoopChunks) {
-      hipLaunchKernelGGL(k_scan_loop, dim3(1), dim3(kBlock), 0, s, hist, hn, offs);
-    } else if (nparts > 1) {
+    } else {
       hipLaunchKernelGGL(k_scan_reduce, dim3(nparts), dim3(kBlock), 0, s, hist, hn, part);
       hipLaunchKernelGGL(k_scan_partials, dim3(1), dim3(kBlock), 0, s, part, nparts);
       hipLaunchKernelGGL(k_scan_down, dim3(nparts), dim3(kBlock), 0, s, hist, hn, part, offs);
-    } else {
-      hipLaunchKernelGGL(k_scan_down, dim3(1), dim3(kBlock), 0, s, hist, hn, (const uint32_t*)nullptr, offs);
     }
     const uint32_t* counts = !fused ? offs : !counts_next || pass == 0 ? hist : rows + hn * (pass - 1);
+    const uint32_t* from = pass == 0 ? nullptr : vin;  // (at first a key's value is its position)
     if (items == kRadixItemsSmall)
-      hipLaunchKernelGGL(k_radix_scatter<kRadixItemsSmall>, dim3(nblocks), dim3(kBlock), 0, s, kin, vin, n, shift, counts,
-                         nblocks, fused, kout, vout, n_dev,
+      hipLaunchKernelGGL((k_radix_scatter<K, kRadixItemsSmall>), dim3(nblocks), dim3(kBlock), 0, s, kin, from, n, shift,
+                         counts, nblocks, fused, kout, vout, n_dev,
                          counts_next && pass + 1 < passes ? rows + hn * pass : nullptr);
     else
-      hipLaunchKernelGGL(k_radix_scatter<kRadixItems>, dim3(nblocks), dim3(kBlock), 0, s, kin, vin, n, shift, counts,
-                         nblocks, fused, kout, vout, n_dev, (uint32_t*)nullptr);
+      hipLaunchKernelGGL((k_radix_scatter<K, kRadixItems>), dim3(nblocks), dim3(kBlock), 0, s, kin, from, n, shift,
+                         counts, nblocks, fused, kout, vout, n_dev, (uint32_t*)nullptr);
     GRTX_LAUNCH_CHECK();
     std::swap(kin, kout);
     std::swap(vin, vout);
@@ -1070,13 +1106,12 @@ grtx_status radix_sort(uint64_t* keys, uint32_t* vals, uint64_t* tkeys, uint32_t
     *kres = kin;
     *vres = vin;
   } else if (kin != keys) {  // an odd number of passes leaves the result in the temporaries
-    GRTX_HIP(hipMemcpyAsync(keys, kin, sizeof(uint64_t) * n, hipMemcpyDeviceToDevice, s));
+    GRTX_HIP(hipMemcpyAsync(keys, kin, sizeof(K) * n, hipMemcpyDeviceToDevice, s));
     GRTX_HIP(hipMemcpyAsync(vals, vin, sizeof(uint32_t) * n, hipMemcpyDeviceToDevice, s));
   }
   return GRTX_OK;
 }
 
-// Root entry: the root's box and reference (internal node 0, or leaf 0 for one leaf).
 // ------------------------------------------------------------------ treelet restructuring
 // One bottom-up pass over the radix tree that rebuilds, at every internal node, the
 // treelet of the node and its largest descendants (up to kTreeletLeaves treelet leaves,
@@ -1956,7 +1991,7 @@ grtx_status build_bvh(const grtx_gaussians* g, grtx_bvh_kind kind, float alpha_m
   hipLaunchKernelGGL(k_bounds_partial, dim3(nparts), dim3(kBlock), 0, s, points, m, partial,
                      reinterpret_cast<uint4*>(b->density), counters, 4);
   hipLaunchKernelGGL(k_bounds_final, dim3(1), dim3(kBlock), 0, s, partial, nparts, bounds, b->dbox);
-  hipLaunchKernelGGL(k_morton, dim3(grid_for(m)), dim3(kBlock), 0, s, points, m, bounds, b->codes, b->perm);
+  hipLaunchKernelGGL(k_morton, dim3(grid_for(m)), dim3(kBlock), 0, s, points, m, bounds, b->codes);
   GRTX_LAUNCH_CHECK();
   GRTX_TRY(radix_sort(b->codes, b->perm, tkeys, tvals, m, sc, s));
   if (proxy) {
@@ -2113,13 +2148,13 @@ grtx_status exclusive_scan_u32(const uint32_t* in, uint32_t* out, int64_t n, hip
   return GRTX_OK;
 }
 
-grtx_status sort_by_key_into(uint64_t* keys, uint32_t* vals, uint64_t* tkeys, uint32_t* tvals, int64_t n,
-                             int key_bits, hipStream_t s, const uint32_t* n_dev, uint64_t** kres, uint32_t** vres) {
+grtx_status sort_positions(uint32_t* keys, uint32_t* vals, uint32_t* tkeys, uint32_t* tvals, int64_t n, int key_bits,
+                           hipStream_t s, const uint32_t* n_dev, uint32_t** kres, uint32_t** vres) {
   *kres = keys;
   *vres = vals;
-  if (n <= 1) return GRTX_OK;
+  if (n <= 0) return GRTX_OK;
   Scratch sc(s);
-  const int passes = std::max(1, std::min(8, (key_bits + 7) / 8));
+  const int passes = std::max(1, std::min(4, (key_bits + 7) / 8));
   return radix_sort(keys, vals, tkeys, tvals, n, sc, s, passes, n_dev, kres, vres);
 }
 

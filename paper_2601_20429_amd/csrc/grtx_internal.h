@@ -316,12 +316,12 @@ class Scratch {
 // Device utilities of the build, reused by the backward pass (stream-ordered scratch).
 // Exclusive prefix sum of n uint32 values.
 grtx_status exclusive_scan_u32(const uint32_t* in, uint32_t* out, int64_t n, hipStream_t s);
-// Stable LSD radix sort of (keys, vals) by the low key_bits bits of the keys, with caller-owned
-// temporaries (tkeys, tvals of n entries); *kres / *vres receive the arrays that hold the result
-// (the inputs or the temporaries). With `n_dev` the first *n_dev (at most n) pairs are sorted, n
+// Stable LSD radix sort by the low key_bits bits of the keys, with caller-owned temporaries
+// (vals, tkeys, tvals of n entries); *kres / *vres receive the arrays that hold the sorted keys
+// and the positions they came from. With `n_dev` the first *n_dev (at most n) keys are sorted, n
 // being the host's bound.
-grtx_status sort_by_key_into(uint64_t* keys, uint32_t* vals, uint64_t* tkeys, uint32_t* tvals, int64_t n,
-                             int key_bits, hipStream_t s, const uint32_t* n_dev, uint64_t** kres, uint32_t** vres);
+grtx_status sort_positions(uint32_t* keys, uint32_t* vals, uint32_t* tkeys, uint32_t* tvals, int64_t n, int key_bits,
+                           hipStream_t s, const uint32_t* n_dev, uint32_t** kres, uint32_t** vres);
 
 // Secondary rays (objects.hip).
 grtx_status object_rays(const grtx_objects* obj, const grtx_rays* r, float* t_far, float* next_o, float* next_d,
