@@ -68,7 +68,8 @@ constexpr int kGroupSpill = 1024;
 static_assert(kGroupWide + 3 * kGroup + kMaxStack <= kGroupSpill, "the rows hold any stack");
 constexpr int kGroupLeaves = GRTX_GROUP_LEAFS;
 // Leaves waiting (over the wave's groups) that call for a leaf step (24 to 48 measured alike),
-// and steps a group ready for its finish step waits for a second one (6: 2% slower).
+// and steps a group ready for its finish step waits for a second one (6: 2% slower; for two more:
+// 2% faster at 100k, 3% slower on 1M).
 #ifndef GRTX_GROUP_LEAVES
 #define GRTX_GROUP_LEAVES 32
 #endif
@@ -77,6 +78,12 @@ constexpr int kGroupLeaves = GRTX_GROUP_LEAFS;
 #endif
 constexpr int kGroupLeafLanes = GRTX_GROUP_LEAVES;
 constexpr int kGroupWait = GRTX_GROUP_WAIT;
+// A launch without a queue has one ray per group and waves to spare, so what its steps cost
+// counts by the wave's own chain: a finish step is better shared by all four groups, and none
+// waits long for it. 2,777 rays in 50k Gaussians: 142 us with the waits above, 113 with these
+// (4 steps: 123, 12: 139; at two groups, 4 steps: 125); 64x64 in 1,000: 38.4, 31.0.
+constexpr int kOnceReady = 4;
+constexpr int kOnceWait = 8;
 #ifndef GRTX_GROUP_WAVES
 #define GRTX_GROUP_WAVES 4
 #endif
@@ -458,7 +465,9 @@ __global__ void __launch_bounds__(64)
     const uint64_t readies = __ballot(ready);
     const float tmax_t = key_t(tmax);
     waited = readies ? waited + 1 : 0;
-    if (__popcll(readies) >= 2 * kGroup || (nodes | leaves) == 0 || waited > kGroupWait) {
+    const bool once = !SERVE && !A.counter;
+    if (__popcll(readies) >= (once ? kOnceReady : 2) * kGroup || (nodes | leaves) == 0 ||
+        waited > (once ? kOnceWait : kGroupWait)) {
       // ---------------------------------------------------------- finish step
       waited = 0;
       fresh = true;
@@ -500,6 +509,7 @@ __global__ void __launch_bounds__(64)
         if (n_max <= kGroup) count(std::integral_constant<int, 1>());
         else if (n_max <= 2 * kGroup) count(std::integral_constant<int, 2>());
         else if (n_max <= 3 * kGroup) count(std::integral_constant<int, 3>());
+        else if (n_max <= 4 * kGroup) count(std::integral_constant<int, 4>());
         else count(std::integral_constant<int, kOwn>());
       }
       {
