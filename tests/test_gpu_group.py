@@ -60,6 +60,14 @@ def test_long_lists_and_cut_rounds(opacity, t_min):
     assert opacity > -6.0 or int(ref["hit_counts"].max()) > 160
 
 
+@pytest.mark.parametrize("n,scale,opacity", [(3_000, -2.2, -4.0), (8_000, -3.0, -5.0), (30_000, -3.0, -4.0), (60_000, -3.4, -3.0)])
+def test_lists_that_grow_after_a_cut(n, scale, opacity):
+    # rays with some 50 to 300 hits, in a launch whose waves take new rays as others end: sorted
+    # starts of every length meet from one to 32 new hits, and other groups' first lists
+    ref = check(scene_of(n, n, degree=1, scale=scale, opacity=opacity), *rays_of(70_001, 8), cap=2048)
+    assert int(ref["hit_counts"].max()) > 64
+
+
 def test_stacks_beyond_lds():
     # large overlapping Gaussians around the origins: a ray enters most of 60,000 boxes
     check(scene_of(60_000, 5, spread=0.05, scale=-2.0, opacity=-5.0, degree=1), *rays_of(64, 6, box=0.02), cap=4096)
