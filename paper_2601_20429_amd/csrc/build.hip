@@ -146,13 +146,14 @@ __device__ __forceinline__ int64_t radix_tiles(int64_t n, int64_t tile, int nblo
 
 // `n_dev` (may be null) holds the number of keys on the device when the host knows only a
 // bound `n` (workgroups past the count see no keys).
-template <class K>
+template <class K, int BITS>
 __global__ void __launch_bounds__(kBlock) k_radix_hist(const K* __restrict__ keys, int64_t n, int shift, int items,
                                                        uint32_t* __restrict__ hist, int nblocks, bool fused,
                                                        const uint32_t* __restrict__ n_dev) {
   if (n_dev) n = min(n, (int64_t)*n_dev);
-  __shared__ uint32_t s_cnt[256];
-  s_cnt[threadIdx.x] = 0;
+  constexpr int kBins = 1 << BITS;
+  __shared__ uint32_t s_cnt[kBins];
+  for (int d = threadIdx.x; d < kBins; d += kBlock) s_cnt[d] = 0;
   __syncthreads();
   const int64_t span = radix_tiles(n, (int64_t)kBlock * items, nblocks) * kBlock * items;
   const int64_t base = (int64_t)blockIdx.x * span;
@@ -163,11 +164,12 @@ __global__ void __launch_bounds__(kBlock) k_radix_hist(const K* __restrict__ key
     for (int r = 0; r < kRadixItems; ++r) key[r] = i0 + r * kBlock < end ? keys[i0 + r * kBlock] : (K)0;
 #pragma unroll
     for (int r = 0; r < kRadixItems; ++r)
-      if (i0 + r * kBlock < end) atomicAdd(&s_cnt[(uint32_t)(key[r] >> shift) & 255u], 1u);
+      if (i0 + r * kBlock < end) atomicAdd(&s_cnt[(uint32_t)(key[r] >> shift) & (kBins - 1u)], 1u);
   }
   __syncthreads();
   // digit-major ([digit][workgroup]) for the scan; workgroup-major rows for the fused scatter
-  hist[fused ? (size_t)blockIdx.x * 256 + threadIdx.x : (size_t)threadIdx.x * nblocks + blockIdx.x] = s_cnt[threadIdx.x];
+  for (int d = threadIdx.x; d < kBins; d += kBlock)
+    hist[fused ? (size_t)blockIdx.x * kBins + d : (size_t)d * nblocks + blockIdx.x] = s_cnt[d];
 }
 
 // Exclusive scan of `n` uint32 in chunks of kScanChunk.
@@ -284,7 +286,7 @@ __global__ void __launch_bounds__(kBlock) k_scan_loop(const uint32_t* __restrict
 // no barrier between rounds; then the waves' counts are added up once. Bound by latency at 100k
 // keys (10 us a pass), by memory at 3M (28 us for 72 MB; 53 before, with four barriers a round
 // and the keys written where they stood; 61 without the barriers but not through LDS).
-template <class K, int ITEMS>
+template <class K, int ITEMS, int BITS>
 __global__ void __launch_bounds__(kBlock) k_radix_scatter(const K* __restrict__ keys_in,
                                                           const uint32_t* __restrict__ vals_in, int64_t n, int shift,
                                                           const uint32_t* __restrict__ offsets, int nblocks, bool fused,
@@ -296,38 +298,51 @@ __global__ void __launch_bounds__(kBlock) k_radix_scatter(const K* __restrict__ 
   const int64_t span = radix_tiles(n, kTile, nblocks) * kTile;
   const int64_t begin = (int64_t)blockIdx.x * span;
   if (begin >= n) return;  // the whole workgroup is past the keys
-  __shared__ uint32_t s_cnt[kBlock / 64][256];
-  __shared__ uint32_t s_tmp[kBlock];
+  constexpr int kBins = 1 << BITS;
+  constexpr int kOwn = kBins / kBlock;  // a thread's digits: kOwn of them from kOwn * threadIdx.x on
+  __shared__ uint32_t s_cnt[kBlock / 64][kBins];
+  __shared__ uint32_t s_tmp[kBins];
   __shared__ K s_key[ITEMS == kRadixItems ? kTile : 1];
   __shared__ uint32_t s_val[ITEMS == kRadixItems ? kTile : 1];
   const int lane = threadIdx.x & 63;
   const int wave = threadIdx.x >> 6;
   const uint64_t lt_mask = lane ? (~0ull >> (64 - lane)) : 0ull;
-  uint32_t off;
+  const int d0 = kOwn * threadIdx.x;
+  uint32_t off[kOwn];
   if (fused) {
     // (32 rows' loads in flight together: the rows come from beyond this XCD's L2)
-    uint32_t before = 0, total = 0;
+    uint32_t before[kOwn] = {}, total[kOwn] = {};
+    auto rows = [&](int b, auto some) __attribute__((always_inline)) {
+      constexpr int N = decltype(some)::value;
+      uint32_t c[N][kOwn];
+#pragma unroll
+      for (int u = 0; u < N; ++u)
+#pragma unroll
+        for (int d = 0; d < kOwn; ++d) c[u][d] = offsets[(size_t)(b + u) * kBins + d0 + d];
+#pragma unroll
+      for (int u = 0; u < N; ++u)
+#pragma unroll
+        for (int d = 0; d < kOwn; ++d) {
+          total[d] += c[u][d];
+          before[d] += b + u < (int)blockIdx.x ? c[u][d] : 0u;
+        }
+    };
     int b = 0;
-    for (; b + 32 <= nblocks; b += 32) {
-      uint32_t c[32];
+    for (; b + 32 <= nblocks; b += 32) rows(b, std::integral_constant<int, 32>());
+    for (; b + 8 <= nblocks; b += 8) rows(b, std::integral_constant<int, 8>());
+    for (; b < nblocks; ++b) rows(b, std::integral_constant<int, 1>());
+    uint32_t all, sum = 0;
 #pragma unroll
-      for (int u = 0; u < 32; ++u) c[u] = offsets[(size_t)(b + u) * 256 + threadIdx.x];
+    for (int d = 0; d < kOwn; ++d) sum += total[d];
+    uint32_t at = block_exclusive_scan(sum, s_tmp, &all);
 #pragma unroll
-      for (int u = 0; u < 32; ++u) {
-        total += c[u];
-        before += b + u < (int)blockIdx.x ? c[u] : 0u;
-      }
+    for (int d = 0; d < kOwn; ++d) {
+      off[d] = at + before[d];
+      at += total[d];
     }
-#pragma unroll 8
-    for (; b < nblocks; ++b) {
-      const uint32_t c = offsets[(size_t)b * 256 + threadIdx.x];
-      total += c;
-      before += b < (int)blockIdx.x ? c : 0u;
-    }
-    uint32_t all;
-    off = block_exclusive_scan(total, s_tmp, &all) + before;
   } else {
-    off = offsets[(size_t)threadIdx.x * nblocks + blockIdx.x];
+#pragma unroll
+    for (int d = 0; d < kOwn; ++d) off[d] = offsets[(size_t)(d0 + d) * nblocks + blockIdx.x];
   }
   const int64_t stop = min(n, begin + span);
   for (int64_t tile = begin; tile < stop; tile += kTile) {
@@ -339,16 +354,18 @@ __global__ void __launch_bounds__(kBlock) k_radix_scatter(const K* __restrict__ 
 #pragma unroll
     for (int r = 0; r < ITEMS; ++r)
       val[r] = !vals_in ? (uint32_t)(first + r * 64) : first + r * 64 < n ? vals_in[first + r * 64] : 0u;
-    for (int w = 0; w < kBlock / 64; ++w) s_cnt[w][threadIdx.x] = 0u;
+    for (int w = 0; w < kBlock / 64; ++w)
+#pragma unroll
+      for (int d = 0; d < kOwn; ++d) s_cnt[w][d0 + d] = 0u;
     __syncthreads();
     uint32_t rank[ITEMS];
 #pragma unroll
     for (int r = 0; r < ITEMS; ++r) {
       const bool valid = first + r * 64 < n;
-      const uint32_t digit = (uint32_t)(key[r] >> shift) & 255u;
+      const uint32_t digit = (uint32_t)(key[r] >> shift) & (kBins - 1u);
       uint64_t peers = __ballot(valid);
 #pragma unroll
-      for (int b = 0; b < 8; ++b) {
+      for (int b = 0; b < BITS; ++b) {
         const bool bit = (digit >> b) & 1u;
         const uint64_t m = __ballot(valid && bit);
         peers &= bit ? m : ~m;
@@ -363,26 +380,34 @@ __global__ void __launch_bounds__(kBlock) k_radix_scatter(const K* __restrict__ 
       __builtin_amdgcn_wave_barrier();
     }
     __syncthreads();
-    uint32_t mine = 0;
+    uint32_t mine[kOwn], sum = 0;
 #pragma unroll
-    for (int w = 0; w < kBlock / 64; ++w) mine += s_cnt[w][threadIdx.x];
+    for (int d = 0; d < kOwn; ++d) {
+      mine[d] = 0;
+#pragma unroll
+      for (int w = 0; w < kBlock / 64; ++w) mine[d] += s_cnt[w][d0 + d];
+      sum += mine[d];
+    }
     if constexpr (ITEMS == kRadixItems) {
       // large sorts go through LDS in their new order, so that runs of a digit are written
       // together
       uint32_t all;
-      uint32_t at = block_exclusive_scan(mine, s_tmp, &all);
-      s_tmp[threadIdx.x] = off - at;  // from a place here to its place in the result
+      uint32_t at = block_exclusive_scan(sum, s_tmp, &all);
 #pragma unroll
-      for (int w = 0; w < kBlock / 64; ++w) {
-        const uint32_t c = s_cnt[w][threadIdx.x];
-        s_cnt[w][threadIdx.x] = at;
-        at += c;
+      for (int d = 0; d < kOwn; ++d) {
+        s_tmp[d0 + d] = off[d] - at;  // from a place here to its place in the result
+#pragma unroll
+        for (int w = 0; w < kBlock / 64; ++w) {
+          const uint32_t c = s_cnt[w][d0 + d];
+          s_cnt[w][d0 + d] = at;
+          at += c;
+        }
       }
       __syncthreads();
 #pragma unroll
       for (int r = 0; r < ITEMS; ++r)
         if (first + r * 64 < n) {
-          const uint32_t i = s_cnt[wave][(uint32_t)(key[r] >> shift) & 255u] + rank[r];
+          const uint32_t i = s_cnt[wave][(uint32_t)(key[r] >> shift) & (kBins - 1u)] + rank[r];
           s_key[i] = key[r];
           s_val[i] = val[r];
         }
@@ -392,34 +417,38 @@ __global__ void __launch_bounds__(kBlock) k_radix_scatter(const K* __restrict__ 
         const uint32_t i = (uint32_t)(r * kBlock) + threadIdx.x;
         if (i < all) {
           const K k = s_key[i];
-          const uint32_t pos = s_tmp[(uint32_t)(k >> shift) & 255u] + i;
+          const uint32_t pos = s_tmp[(uint32_t)(k >> shift) & (kBins - 1u)] + i;
           keys_out[pos] = k;
           vals_out[pos] = s_val[i];
         }
       }
     } else {
-      uint32_t at = off;
 #pragma unroll
-      for (int w = 0; w < kBlock / 64; ++w) {
-        const uint32_t c = s_cnt[w][threadIdx.x];
-        s_cnt[w][threadIdx.x] = at;
-        at += c;
+      for (int d = 0; d < kOwn; ++d) {
+        uint32_t at = off[d];
+#pragma unroll
+        for (int w = 0; w < kBlock / 64; ++w) {
+          const uint32_t c = s_cnt[w][d0 + d];
+          s_cnt[w][d0 + d] = at;
+          at += c;
+        }
       }
       __syncthreads();
 #pragma unroll
       for (int r = 0; r < ITEMS; ++r) {
         if (first + r * 64 < n) {
-          const uint32_t pos = s_cnt[wave][(uint32_t)(key[r] >> shift) & 255u] + rank[r];
+          const uint32_t pos = s_cnt[wave][(uint32_t)(key[r] >> shift) & (kBins - 1u)] + rank[r];
           keys_out[pos] = key[r];
           vals_out[pos] = val[r];
           // counted for the next pass, in the row of the workgroup that will read the key
           // (these sorts have a workgroup for each tile)
           if (next_hist)
-            atomicAdd(next_hist + (size_t)(pos / (uint32_t)kTile) * 256 + ((uint32_t)(key[r] >> (shift + 8)) & 255u), 1u);
+            atomicAdd(next_hist + (size_t)(pos / (uint32_t)kTile) * kBins + ((uint32_t)(key[r] >> (shift + BITS)) & (kBins - 1u)), 1u);
         }
       }
     }
-    off += mine;
+#pragma unroll
+    for (int d = 0; d < kOwn; ++d) off[d] += mine[d];
     if (tile + kTile < stop) __syncthreads();
   }
 }
@@ -1043,14 +1072,14 @@ inline unsigned grid_for(int64_t n) { return (unsigned)std::max<int64_t>(1, (n +
 
 
 // Sorts `keys`; `vals` receives, for each, the position it came from.
-template <class K>
+template <class K, int BITS>
 grtx_status radix_sort(K* keys, uint32_t* vals, K* tkeys, uint32_t* tvals, int64_t n, Scratch& sc, hipStream_t s,
-                       int passes = 8, const uint32_t* n_dev = nullptr, K** kres = nullptr,
+                       int passes, const uint32_t* n_dev = nullptr, K** kres = nullptr,
                        uint32_t** vres = nullptr) {
   const int items = n <= kRadixSmall ? kRadixItemsSmall : kRadixItems;
   const int64_t tile = (int64_t)kBlock * items;
   const int64_t tiles = (n + tile - 1) / tile;
-  if (tiles > (int64_t)kScanChunk * kScanChunk / 256) {
+  if (tiles > (int64_t)kScanChunk * kScanChunk / 256) {  // (the table of eight-bit digits must fit a scan)
     set_error("radix sort: %lld keys exceed the supported size", (long long)n);
     return GRTX_ERR_INVALID_ARG;
   }
@@ -1058,7 +1087,7 @@ grtx_status radix_sort(K* keys, uint32_t* vals, K* tkeys, uint32_t* tvals, int64
   if (n_dev && nblocks > kRadixFusedBlocks)
     nblocks = std::max(kRadixFusedBlocks, std::min(kRadixDeviceBlocks, nblocks / 16));
   const bool fused = nblocks <= kRadixFusedBlocks;
-  int64_t hn = (int64_t)256 * nblocks;
+  int64_t hn = (int64_t)nblocks << BITS;
   uint32_t *hist = nullptr, *offs = nullptr, *part = nullptr;
   int nparts = (int)((hn + kScanChunk - 1) / kScanChunk);
   GRTX_TRY(sc.get(&hist, hn));
@@ -1078,9 +1107,9 @@ grtx_status radix_sort(K* keys, uint32_t* vals, K* tkeys, uint32_t* tvals, int64
     hipLaunchKernelGGL(k_fill_u32, dim3(grid_for(hn * (passes - 1))), dim3(kBlock), 0, s, rows, hn * (passes - 1), 0u);
   }
   for (int pass = 0; pass < passes; ++pass) {
-    int shift = 8 * pass;
+    int shift = BITS * pass;
     if (!counts_next || pass == 0)
-      hipLaunchKernelGGL(k_radix_hist<K>, dim3(nblocks), dim3(kBlock), 0, s, kin, n, shift, items, hist, nblocks, fused,
+      hipLaunchKernelGGL((k_radix_hist<K, BITS>), dim3(nblocks), dim3(kBlock), 0, s, kin, n, shift, items, hist, nblocks, fused,
                          n_dev);
     if (fused) {
       // the scatter turns the counts into offsets itself
@@ -1092,11 +1121,11 @@ grtx_status radix_sort(K* keys, uint32_t* vals, K* tkeys, uint32_t* tvals, int64
     const uint32_t* counts = !fused ? offs : !counts_next || pass == 0 ? hist : rows + hn * (pass - 1);
     const uint32_t* from = pass == 0 ? nullptr : vin;  // (at first a key's value is its position)
     if (items == kRadixItemsSmall)
-      hipLaunchKernelGGL((k_radix_scatter<K, kRadixItemsSmall>), dim3(nblocks), dim3(kBlock), 0, s, kin, from, n, shift,
+      hipLaunchKernelGGL((k_radix_scatter<K, kRadixItemsSmall, BITS>), dim3(nblocks), dim3(kBlock), 0, s, kin, from, n, shift,
                          counts, nblocks, fused, kout, vout, n_dev,
                          counts_next && pass + 1 < passes ? rows + hn * pass : nullptr);
     else
-      hipLaunchKernelGGL((k_radix_scatter<K, kRadixItems>), dim3(nblocks), dim3(kBlock), 0, s, kin, from, n, shift,
+      hipLaunchKernelGGL((k_radix_scatter<K, kRadixItems, BITS>), dim3(nblocks), dim3(kBlock), 0, s, kin, from, n, shift,
                          counts, nblocks, fused, kout, vout, n_dev, (uint32_t*)nullptr);
     GRTX_LAUNCH_CHECK();
     std::swap(kin, kout);
@@ -1993,7 +2022,7 @@ grtx_status build_bvh(const grtx_gaussians* g, grtx_bvh_kind kind, float alpha_m
   hipLaunchKernelGGL(k_bounds_final, dim3(1), dim3(kBlock), 0, s, partial, nparts, bounds, b->dbox);
   hipLaunchKernelGGL(k_morton, dim3(grid_for(m)), dim3(kBlock), 0, s, points, m, bounds, b->codes);
   GRTX_LAUNCH_CHECK();
-  GRTX_TRY(radix_sort(b->codes, b->perm, tkeys, tvals, m, sc, s));
+  GRTX_TRY((radix_sort<uint64_t, 8>(b->codes, b->perm, tkeys, tvals, m, sc, s, 8)));
   if (proxy) {
     hipLaunchKernelGGL(k_proxy_leaves, dim3(grid_for(m)), dim3(kBlock), 0, s, b->perm, m, ttmp, tbox, b->tris,
                        b->boxes, cent, bounds, b->density);
@@ -2154,8 +2183,11 @@ grtx_status sort_positions(uint32_t* keys, uint32_t* vals, uint32_t* tkeys, uint
   *vres = vals;
   if (n <= 0) return GRTX_OK;
   Scratch sc(s);
-  const int passes = std::max(1, std::min(4, (key_bits + 7) / 8));
-  return radix_sort(keys, vals, tkeys, tvals, n, sc, s, passes, n_dev, kres, vres);
+  // Nine bits a pass where that saves one (65k to 262k Gaussians: two passes of 115 us instead of
+  // three of 109 us for 10.7M keys); a workgroup's digits then go two to a thread.
+  const int by8 = std::max(1, (key_bits + 7) / 8), by9 = std::max(1, (key_bits + 8) / 9);
+  if (by9 < by8) return radix_sort<uint32_t, 9>(keys, vals, tkeys, tvals, n, sc, s, by9, n_dev, kres, vres);
+  return radix_sort<uint32_t, 8>(keys, vals, tkeys, tvals, n, sc, s, by8, n_dev, kres, vres);
 }
 
 }  // namespace grtx

@@ -43,7 +43,7 @@ def composite(p, o, d, Y, ids, live):
 # rays, Gaussians, list capacity, degree, shortest list, which gradients are given
 CASES = [(1, 1, 1, 3, 1, "rdo"), (3, 5, 4, 0, 0, "rdo"), (64, 7, 16, 1, 16, "r"), (77, 300, 33, 2, 0, "do"),
          (1000, 40, 20, 3, 0, "rdo"), (4099, 3, 40, 3, 10, "rdo"), (6000, 500, 60, 3, 50, "rdo"),
-         (65, 1, 17, 3, 17, "o")]
+         (65, 1, 17, 3, 17, "o"), (3000, 70_000, 24, 0, 0, "rdo"), (15_000, 70_000, 24, 0, 0, "rdo")]
 
 
 @pytest.mark.parametrize("rays,n,cap,degree,least,given", CASES)
