@@ -824,9 +824,15 @@ __device__ __forceinline__ void child_box(const float* boxes, int64_t n, uint32_
   for (int a = 0; a < 6; ++a) b[a] = boxes[idx * 6 + a];
 }
 
-// Four-wide node records (layout in grtx_internal.h), written once every box is final.
+// The largest subtree that one wave lays out (see the record layout below).
+constexpr int64_t kLayoutLeaves = 128;
+constexpr int kLayoutBlock = 1024;
+
+// Four-wide node records (layout in grtx_internal.h), written once every box is final, and for
+// the nodes above kLayoutLeaves leaves their entries' leaf counts.
 __global__ void __launch_bounds__(kBlock) k_wide(int64_t n, const uint32_t* __restrict__ child,
-                                                 const float* __restrict__ boxes, float4* __restrict__ nodes) {
+                                                 const float* __restrict__ boxes, const uint32_t* __restrict__ count,
+                                                 float4* __restrict__ nodes, uint4* __restrict__ counts) {
   const int64_t i = blockIdx.x * (int64_t)kBlock + threadIdx.x;
   if (i >= n - 1) return;
   // Start from the two children and open the internal entry of largest surface area
@@ -878,6 +884,11 @@ __global__ void __launch_bounds__(kBlock) k_wide(int64_t n, const uint32_t* __re
       whi[a] |= (uint32_t)qh << (8 * j);
     }
   }
+  if (count[i] > (uint32_t)kLayoutLeaves) {
+    uint32_t c[4];
+    for (int j = 0; j < 4; ++j) c[j] = ref[j] != kNoChild && !(ref[j] & kLeafFlag) ? count[ref[j]] : 0u;
+    counts[i] = make_uint4(c[0], c[1], c[2], c[3]);
+  }
   float4* r = nodes + (int64_t)kNodeF4 * i;
   r[0] = make_float4(org[0], org[1], org[2], step[0]);
   r[1] = make_float4(step[1], step[2], __uint_as_float(ref[0]), __uint_as_float(ref[1]));
@@ -898,9 +909,6 @@ __global__ void __launch_bounds__(kBlock) k_wide(int64_t n, const uint32_t* __re
 // ray meets near each other lie near each other, and the lines fetched hold live records
 // only. `qold` maps each position of the top levels to the radix-tree node whose record it
 // holds.
-constexpr int64_t kLayoutLeaves = 128;
-constexpr int kLayoutBlock = 1024;
-
 // Reserve and record a task for internal node c (leaf count cnt); returns its position.
 __device__ __forceinline__ uint32_t new_task(uint32_t c, uint32_t cnt, uint32_t top_cap, uint32_t* task_cursor,
                                              uint32_t* n_tasks, uint2* tasks) {
@@ -909,36 +917,20 @@ __device__ __forceinline__ uint32_t new_task(uint32_t c, uint32_t cnt, uint32_t 
   return start;
 }
 
-// Copy the record of radix-tree node `old` to position `pos` with its internal entries
-// replaced by the positions `pos_of` assigns them.
-template <class F>
-__device__ __forceinline__ void place_record(const float4* __restrict__ wide, uint32_t old, uint32_t pos,
-                                             float4* __restrict__ nodes, F&& pos_of) {
-  const float4* src = wide + (int64_t)kNodeF4 * old;
-  float4 q0 = src[0], q1 = src[1], q2 = src[2], q3 = src[3];
-  uint32_t r[4] = {__float_as_uint(q1.z), __float_as_uint(q1.w), __float_as_uint(q2.x), __float_as_uint(q2.y)};
-#pragma unroll
-  for (int j = 0; j < 4; ++j)
-    if (r[j] != kNoChild && !(r[j] & kLeafFlag)) r[j] = pos_of(r[j]);
-  q1.z = __uint_as_float(r[0]);
-  q1.w = __uint_as_float(r[1]);
-  q2.x = __uint_as_float(r[2]);
-  q2.y = __uint_as_float(r[3]);
-  float4* dst = nodes + (int64_t)kNodeF4 * pos;
-  dst[0] = q0;
-  dst[1] = q1;
-  dst[2] = q2;
-  dst[3] = q3;
-}
-
 // The top levels (one workgroup; its counters live in LDS until the end). Root = radix-tree
 // node 0 at position 0; with at most kLayoutLeaves leaves in all, the root itself is the
-// only task (top_cap = 0).
+// only task (top_cap = 0). A level costs the latency of its loads: the record and its entries'
+// counts are read together, and the positions' nodes pass through LDS while they fit there, so
+// that the barrier need not wait for stores to memory (100k leaves: 52 us with the counts read after
+// the records and the nodes in memory, 43 us so;
+// 3M: 425 and 298).
+constexpr uint32_t kLayoutHeld = 8192;  // positions whose nodes LDS holds
 __global__ void __launch_bounds__(kLayoutBlock) k_layout_top(int64_t m, const float4* __restrict__ wide,
-                                                             const uint32_t* __restrict__ count, uint32_t top_cap,
+                                                             const uint4* __restrict__ counts, uint32_t top_cap,
                                                              float4* __restrict__ nodes, uint32_t* __restrict__ qold,
                                                              uint2* __restrict__ tasks, uint32_t* __restrict__ ctr) {
   __shared__ uint32_t s_next, s_cursor, s_tasks;
+  __shared__ uint32_t s_old[kLayoutHeld];
   if (m <= kLayoutLeaves) {
     if (threadIdx.x == 0) {
       ctr[0] = (uint32_t)(m - 1);
@@ -950,27 +942,52 @@ __global__ void __launch_bounds__(kLayoutBlock) k_layout_top(int64_t m, const fl
   if (threadIdx.x == 0) {
     s_cursor = 0u;
     s_tasks = 0u;
-    qold[0] = 0u;
+    s_old[0] = 0u;
     s_next = 1u;
   }
   __syncthreads();
   uint32_t begin = 0, end = 1;
   while (begin < end) {
     for (uint32_t q = begin + threadIdx.x; q < end; q += kLayoutBlock) {
-      place_record(wide, qold[q], q, nodes, [&](uint32_t c) {
-        const uint32_t cnt = count[c];
-        if (cnt > (uint32_t)kLayoutLeaves) {
+      const uint32_t old = q < kLayoutHeld ? s_old[q] : qold[q];
+      const float4* src = wide + (int64_t)kNodeF4 * old;
+      const uint4 c4 = counts[old];
+      float4 q0 = src[0], q1 = src[1], q2 = src[2], q3 = src[3];
+      uint32_t r[4] = {__float_as_uint(q1.z), __float_as_uint(q1.w), __float_as_uint(q2.x), __float_as_uint(q2.y)};
+      const uint32_t cnt[4] = {c4.x, c4.y, c4.z, c4.w};
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        if (r[j] == kNoChild || (r[j] & kLeafFlag)) continue;
+        if (cnt[j] > (uint32_t)kLayoutLeaves) {
           const uint32_t pos = atomicAdd(&s_next, 1u);
-          qold[pos] = c;
-          return pos;
+          if (pos < kLayoutHeld) s_old[pos] = r[j];
+          else qold[pos] = r[j];
+          r[j] = pos;
+        } else {
+          r[j] = new_task(r[j], cnt[j], top_cap, &s_cursor, &s_tasks, tasks);
         }
-        return new_task(c, cnt, top_cap, &s_cursor, &s_tasks, tasks);
-      });
+      }
+      q1.z = __uint_as_float(r[0]);
+      q1.w = __uint_as_float(r[1]);
+      q2.x = __uint_as_float(r[2]);
+      q2.y = __uint_as_float(r[3]);
+      float4* dst = nodes + (int64_t)kNodeF4 * q;
+      dst[0] = q0;
+      dst[1] = q1;
+      dst[2] = q2;
+      dst[3] = q3;
     }
-    __syncthreads();
+    // (a barrier for LDS alone while every position read next is held there)
+    auto meet = [&]() {
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+      __builtin_amdgcn_s_barrier();
+      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+    };
+    meet();
     begin = end;
     end = s_next;
-    __syncthreads();
+    if (end <= kLayoutHeld) meet();
+    else __syncthreads();
   }
   if (threadIdx.x == 0) {
     ctr[0] = s_cursor;
@@ -2114,8 +2131,10 @@ grtx_status build_bvh(const grtx_gaussians* g, grtx_bvh_kind kind, float alpha_m
     GRTX_TRY(sc.get(&qold, node_slots));
     GRTX_TRY(sc.get(&tasks, m));
     GRTX_TRY(sc.get(&ctr, 2));
-    hipLaunchKernelGGL(k_wide, dim3(grid_for(nint)), dim3(kBlock), 0, s, m, b->child, b->boxes, wide);
-    hipLaunchKernelGGL(k_layout_top, dim3(1), dim3(kLayoutBlock), 0, s, m, wide, count, (uint32_t)top_cap, b->nodes,
+    uint4* counts = nullptr;
+    GRTX_TRY(sc.get(&counts, nint));
+    hipLaunchKernelGGL(k_wide, dim3(grid_for(nint)), dim3(kBlock), 0, s, m, b->child, b->boxes, count, wide, counts);
+    hipLaunchKernelGGL(k_layout_top, dim3(1), dim3(kLayoutBlock), 0, s, m, wide, counts, (uint32_t)top_cap, b->nodes,
                        qold, tasks, ctr);
     // a wave per task; the tasks number about m / 64 (a grid-stride loop takes any more)
     hipLaunchKernelGGL(k_layout_tasks, dim3((unsigned)std::min<int64_t>(2048, m / (64 * (kBlock / 64)) + 1)),
