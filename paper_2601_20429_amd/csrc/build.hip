@@ -64,26 +64,30 @@ __global__ void __launch_bounds__(kBlock) k_bounds_partial(const float* __restri
   if (threadIdx.x < 6) partial[blockIdx.x * 6 + threadIdx.x] = s[threadIdx.x][0];
 }
 
-__global__ void __launch_bounds__(kBlock) k_bounds_final(const float* __restrict__ partial, int nparts,
-                                                         float* __restrict__ out, float* __restrict__ dbox) {
-  __shared__ float s[6][kBlock];
+// The workgroups' bounds into one (out: lo xyz, hi xyz, for the whole workgroup).
+__device__ __forceinline__ void final_bounds(const float* __restrict__ partial, int nparts, float (*s)[kBlock],
+                                             float out[6]) {
   float v[6] = {INFINITY, INFINITY, INFINITY, -INFINITY, -INFINITY, -INFINITY};
   for (int i = threadIdx.x; i < nparts; i += kBlock)
     for (int a = 0; a < 3; ++a) {
       v[a] = fminf(v[a], partial[i * 6 + a]);
       v[3 + a] = fmaxf(v[3 + a], partial[i * 6 + 3 + a]);
     }
-  for (int a = 0; a < 6; ++a) s[a][threadIdx.x] = v[a];
+  // a wave by shuffles, then the waves' by everyone
+#pragma unroll
+  for (int w = 32; w > 0; w >>= 1)
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+      v[a] = fminf(v[a], __shfl_xor(v[a], w));
+      v[3 + a] = fmaxf(v[3 + a], __shfl_xor(v[3 + a], w));
+    }
+  if ((threadIdx.x & 63) == 0)
+    for (int a = 0; a < 6; ++a) s[a][threadIdx.x >> 6] = v[a];
   __syncthreads();
-  for (int w = kBlock / 2; w > 0; w >>= 1) {
-    if (threadIdx.x < w)
-      for (int a = 0; a < 3; ++a) {
-        s[a][threadIdx.x] = fminf(s[a][threadIdx.x], s[a][threadIdx.x + w]);
-        s[3 + a][threadIdx.x] = fmaxf(s[3 + a][threadIdx.x], s[3 + a][threadIdx.x + w]);
-      }
-    __syncthreads();
+  for (int a = 0; a < 6; ++a) {
+    out[a] = s[a][0];
+    for (int w = 1; w < kBlock / 64; ++w) out[a] = a < 3 ? fminf(out[a], s[a][w]) : fmaxf(out[a], s[a][w]);
   }
-  if (threadIdx.x < 6) out[threadIdx.x] = dbox[threadIdx.x] = s[threadIdx.x][0];
 }
 
 // ------------------------------------------------------------------ Morton codes
@@ -106,19 +110,27 @@ __device__ __forceinline__ uint32_t quantise(float v, float lo, float scale) {
   return fl <= 0.f ? 0u : (fl >= 2097151.f ? 2097151u : (uint32_t)fl);
 }
 
+// (Every workgroup forms the bounds from the partial ones, 256 of them or fewer, rather than
+// wait for a launch that does it once; the first writes them for the kernels that follow.)
 __global__ void __launch_bounds__(kBlock) k_morton(const float* __restrict__ pts, int64_t n,
-                                                   const float* __restrict__ bounds, uint64_t* __restrict__ codes) {
+                                                   const float* __restrict__ partial, int nparts,
+                                                   float* __restrict__ bounds, float* __restrict__ dbox,
+                                                   uint64_t* __restrict__ codes) {
 #pragma clang fp contract(off)
-  int64_t i = blockIdx.x * (int64_t)kBlock + threadIdx.x;
-  if (i >= n) return;
-  uint32_t q[3];
-  for (int a = 0; a < 3; ++a) {
-    float lo = bounds[a], hi = bounds[3 + a];
-    float ext = hi - lo;
-    float scale = ext > 0.f ? 2097152.f / ext : 0.f;  // correctly rounded division
-    q[a] = quantise(pts[3 * i + a], lo, scale);
+  __shared__ float s[6][kBlock];
+  float box[6];
+  final_bounds(partial, nparts, s, box);
+  if (blockIdx.x == 0 && threadIdx.x < 6) bounds[threadIdx.x] = dbox[threadIdx.x] = box[threadIdx.x];
+  for (int64_t i = blockIdx.x * (int64_t)kBlock + threadIdx.x; i < n; i += (int64_t)gridDim.x * kBlock) {
+    uint32_t q[3];
+    for (int a = 0; a < 3; ++a) {
+      float lo = box[a], hi = box[3 + a];
+      float ext = hi - lo;
+      float scale = ext > 0.f ? 2097152.f / ext : 0.f;  // correctly rounded division
+      q[a] = quantise(pts[3 * i + a], lo, scale);
+    }
+    codes[i] = (spread3(q[0]) << 2) | (spread3(q[1]) << 1) | spread3(q[2]);
   }
-  codes[i] = (spread3(q[0]) << 2) | (spread3(q[1]) << 1) | spread3(q[2]);
 }
 
 // ------------------------------------------------------------------ radix sort (stable LSD)
@@ -149,7 +161,8 @@ __device__ __forceinline__ int64_t radix_tiles(int64_t n, int64_t tile, int nblo
 template <class K, int BITS>
 __global__ void __launch_bounds__(kBlock) k_radix_hist(const K* __restrict__ keys, int64_t n, int shift, int items,
                                                        uint32_t* __restrict__ hist, int nblocks, bool fused,
-                                                       const uint32_t* __restrict__ n_dev) {
+                                                       const uint32_t* __restrict__ n_dev, uint32_t* __restrict__ rows,
+                                                       int n_rows) {
   if (n_dev) n = min(n, (int64_t)*n_dev);
   constexpr int kBins = 1 << BITS;
   __shared__ uint32_t s_cnt[kBins];
@@ -168,6 +181,9 @@ __global__ void __launch_bounds__(kBlock) k_radix_hist(const K* __restrict__ key
   }
   __syncthreads();
   // digit-major ([digit][workgroup]) for the scan; workgroup-major rows for the fused scatter
+  // (and this workgroup's rows of the later passes cleared, which the scatters count in)
+  for (int p = 0; p < n_rows; ++p)
+    for (int d = threadIdx.x; d < kBins; d += kBlock) rows[((size_t)p * nblocks + blockIdx.x) * kBins + d] = 0u;
   for (int d = threadIdx.x; d < kBins; d += kBlock)
     hist[fused ? (size_t)blockIdx.x * kBins + d : (size_t)d * nblocks + blockIdx.x] = s_cnt[d];
 }
@@ -917,6 +933,33 @@ __device__ __forceinline__ uint32_t new_task(uint32_t c, uint32_t cnt, uint32_t 
   return start;
 }
 
+// Root entry: the root's box and reference (internal node 0, or leaf 0 for one leaf); and the
+// final depth and kind of the tree: out[0] = depth, out[1] = 1 if a restructured tree was
+// kept. `tree` is the restructured tree's depth (null: none was made), `plain` the plain one's
+// where it counts (null: a single leaf).
+struct FinishArgs {
+  const float* box;
+  uint32_t ref;
+  float* roots;
+  const uint32_t* tree;
+  int max_depth;
+  const uint32_t* plain;
+  uint32_t* out;
+};
+__device__ __forceinline__ void finish_tree(const FinishArgs& F) {
+  if (threadIdx.x < 6) F.roots[threadIdx.x] = F.box[threadIdx.x];
+  if (threadIdx.x == 6) F.roots[6] = __uint_as_float(F.ref);
+  if (threadIdx.x == 7) {
+    F.roots[7] = 0.f;
+    const bool kept = F.tree && *F.tree <= (uint32_t)F.max_depth;
+    const uint32_t d = kept ? *F.tree : F.plain ? *F.plain : 0u;
+    F.out[0] = d;
+    F.out[1] = kept ? 1u : 0u;
+  }
+}
+// (for a single leaf; trees with nodes are finished by their layout)
+__global__ void k_finish(FinishArgs F) { finish_tree(F); }
+
 // The top levels (one workgroup; its counters live in LDS until the end). Root = radix-tree
 // node 0 at position 0; with at most kLayoutLeaves leaves in all, the root itself is the
 // only task (top_cap = 0). A level costs the latency of its loads: the record and its entries'
@@ -928,7 +971,9 @@ constexpr uint32_t kLayoutHeld = 8192;  // positions whose nodes LDS holds
 __global__ void __launch_bounds__(kLayoutBlock) k_layout_top(int64_t m, const float4* __restrict__ wide,
                                                              const uint4* __restrict__ counts, uint32_t top_cap,
                                                              float4* __restrict__ nodes, uint32_t* __restrict__ qold,
-                                                             uint2* __restrict__ tasks, uint32_t* __restrict__ ctr) {
+                                                             uint2* __restrict__ tasks, uint32_t* __restrict__ ctr,
+                                                             FinishArgs F) {
+  finish_tree(F);
   __shared__ uint32_t s_next, s_cursor, s_tasks;
   __shared__ uint32_t s_old[kLayoutHeld];
   if (m <= kLayoutLeaves) {
@@ -1114,20 +1159,19 @@ grtx_status radix_sort(K* keys, uint32_t* vals, K* tkeys, uint32_t* tvals, int64
   uint32_t* vin = vals;
   K* kout = tkeys;
   uint32_t* vout = tvals;
-  // Small fused sorts count the next pass's digits in the scatter (cleared rows of their own per
-  // pass), so that only the first pass has a counting kernel: 12 against 14 us a pass at 100k
+  // Small fused sorts count the next pass's digits in the scatter (rows of their own per pass,
+  // cleared by the counting kernel), so that only the first pass has a counting kernel: 12 against 14 us a pass at 100k
   // keys; at a million the atomics cost more than the kernel (51 against 38 us).
   uint32_t* rows = nullptr;
   const bool counts_next = fused && items == kRadixItemsSmall && passes > 1;
   if (counts_next) {
     GRTX_TRY(sc.get(&rows, hn * (passes - 1)));
-    hipLaunchKernelGGL(k_fill_u32, dim3(grid_for(hn * (passes - 1))), dim3(kBlock), 0, s, rows, hn * (passes - 1), 0u);
   }
   for (int pass = 0; pass < passes; ++pass) {
     int shift = BITS * pass;
     if (!counts_next || pass == 0)
       hipLaunchKernelGGL((k_radix_hist<K, BITS>), dim3(nblocks), dim3(kBlock), 0, s, kin, n, shift, items, hist, nblocks, fused,
-                         n_dev);
+                         n_dev, rows, counts_next ? passes - 1 : 0);
     if (fused) {
       // the scatter turns the counts into offsets itself
     } else {
@@ -1812,24 +1856,6 @@ __global__ void __launch_bounds__(kBlock) k_tree_height(int64_t m, const uint32_
   }
 }
 
-// Root entry: the root's box and reference (internal node 0, or leaf 0 for one leaf); and the
-// final depth and kind of the tree: out[0] = depth, out[1] = 1 if a restructured tree was
-// kept. `tree` is the restructured tree's depth (null: none was made), `plain` the plain one's
-// where it counts (null: a single leaf).
-__global__ void k_finish(const float* __restrict__ box, uint32_t ref, float* __restrict__ roots,
-                         const uint32_t* __restrict__ tree, int max_depth, const uint32_t* __restrict__ plain,
-                         uint32_t* __restrict__ out) {
-  if (threadIdx.x < 6) roots[threadIdx.x] = box[threadIdx.x];
-  if (threadIdx.x == 6) roots[6] = __uint_as_float(ref);
-  if (threadIdx.x == 7) {
-    roots[7] = 0.f;
-    const bool kept = tree && *tree <= (uint32_t)max_depth;
-    const uint32_t d = kept ? *tree : plain ? *plain : 0u;
-    out[0] = d;
-    out[1] = kept ? 1u : 0u;
-  }
-}
-
 }  // namespace
 
 // Build over `n` points (centroids) whose leaf boxes/records are produced by `leaves`.
@@ -2011,7 +2037,8 @@ grtx_status build_bvh(const grtx_gaussians* g, grtx_bvh_kind kind, float alpha_m
   float4* ttmp = nullptr;
   uint64_t* tkeys = nullptr;
   uint32_t* tvals = nullptr;
-  int nparts = (int)std::min<int64_t>(1024, (m + kBlock - 1) / kBlock);
+  int nparts = (int)std::min<int64_t>(256, (m + kBlock - 1) / kBlock);
+  FinishArgs fin{b->root_box, m == 1 ? kLeafFlag : 0u, b->roots, nullptr, max_depth, nullptr, b->depth};
   GRTX_TRY(sc.get(&partial, 6 * nparts));
   GRTX_TRY(sc.get(&bounds, 6));
   GRTX_TRY(sc.get(&tkeys, m));
@@ -2036,8 +2063,8 @@ grtx_status build_bvh(const grtx_gaussians* g, grtx_bvh_kind kind, float alpha_m
   }
   hipLaunchKernelGGL(k_bounds_partial, dim3(nparts), dim3(kBlock), 0, s, points, m, partial,
                      reinterpret_cast<uint4*>(b->density), counters, 4);
-  hipLaunchKernelGGL(k_bounds_final, dim3(1), dim3(kBlock), 0, s, partial, nparts, bounds, b->dbox);
-  hipLaunchKernelGGL(k_morton, dim3(grid_for(m)), dim3(kBlock), 0, s, points, m, bounds, b->codes);
+  hipLaunchKernelGGL(k_morton, dim3(std::min(grid_for(m), 2048u)), dim3(kBlock), 0, s, points, m, partial, nparts, bounds,
+                     b->dbox, b->codes);
   GRTX_LAUNCH_CHECK();
   GRTX_TRY((radix_sort<uint64_t, 8>(b->codes, b->perm, tkeys, tvals, m, sc, s, 8)));
   if (proxy) {
@@ -2134,16 +2161,17 @@ grtx_status build_bvh(const grtx_gaussians* g, grtx_bvh_kind kind, float alpha_m
     uint4* counts = nullptr;
     GRTX_TRY(sc.get(&counts, nint));
     hipLaunchKernelGGL(k_wide, dim3(grid_for(nint)), dim3(kBlock), 0, s, m, b->child, b->boxes, count, wide, counts);
+    fin.tree = tree_depth;
+    fin.plain = plain_depth;
     hipLaunchKernelGGL(k_layout_top, dim3(1), dim3(kLayoutBlock), 0, s, m, wide, counts, (uint32_t)top_cap, b->nodes,
-                       qold, tasks, ctr);
+                       qold, tasks, ctr, fin);
     // a wave per task; the tasks number about m / 64 (a grid-stride loop takes any more)
     hipLaunchKernelGGL(k_layout_tasks, dim3((unsigned)std::min<int64_t>(2048, m / (64 * (kBlock / 64)) + 1)),
                        dim3(kBlock), 0, s, wide, tasks, ctr, b->nodes);
   } else {
     hipLaunchKernelGGL(k_fill_u32, dim3(1), dim3(kBlock), 0, s, b->parent, 1, kNoParent);
+    hipLaunchKernelGGL(k_finish, dim3(1), dim3(64), 0, s, fin);
   }
-  hipLaunchKernelGGL(k_finish, dim3(1), dim3(64), 0, s, b->root_box, m == 1 ? (kLeafFlag | 0u) : 0u, b->roots,
-                     tree_depth, max_depth, plain_depth, b->depth);
   GRTX_LAUNCH_CHECK();
   return GRTX_OK;
 }

@@ -1102,11 +1102,13 @@ __global__ void __launch_bounds__(256) k_tile_estimate(const float4* __restrict_
 
 // Tiles by bucket: a workgroup takes 256 positions of the base order, ranks them within their
 // buckets and reserves their places with one atomic per bucket it holds (`cursor`, zero
-// before). The places of a bucket's tiles follow the order in which workgroups arrive: an
+// before); the first clears the launch's work counters too. The places of a bucket's tiles follow the order in which workgroups arrive: an
 // order of work, which no result depends on.
 __global__ void __launch_bounds__(256) k_tile_place(const uint32_t* __restrict__ keys, const uint32_t* __restrict__ base,
                                                     int64_t n_tiles, const uint32_t* __restrict__ hist,
-                                                    uint32_t* __restrict__ cursor, uint32_t* __restrict__ order) {
+                                                    uint32_t* __restrict__ cursor, uint32_t* __restrict__ order,
+                                                    unsigned int* __restrict__ counter) {
+  if (blockIdx.x == 0 && threadIdx.x < kChunks) counter[threadIdx.x] = 0u;
   __shared__ uint32_t s_start[256], s_mine[256];
   const int t = threadIdx.x;
   const int64_t i = blockIdx.x * (int64_t)256 + t;
@@ -1611,6 +1613,7 @@ grtx_status launch_trace_in(const TraceScene& b, const grtx_rays* r, const grtx_
   if (!noalloc) order_scratch.reset(new Scratch(s));
   const int64_t F = a.n_free;
   // The order in which work is taken matters only where it waits to be taken.
+  bool counter_clear = false;
   const bool at_once = group && a.n_work <= (int64_t)blocks * kGroupsPerWave;
   if (a.image_w > 0 && !noalloc && !at_once) {
     // Tiles heaviest first, so that the longest rays do not start last: by estimated cost
@@ -1630,7 +1633,8 @@ grtx_status launch_trace_in(const TraceScene& b, const grtx_rays* r, const grtx_
                          b.n_cut, r->origins + 3 * F, r->dirs + 3 * F, a.image_w, a.image_h, a.tiles_x, nt, base,
                          keys, hist);
       hipLaunchKernelGGL(k_tile_place, dim3((unsigned)((nt + 255) / 256)), dim3(256), 0, s, keys, base, nt, hist,
-                         hist + 256, est_order);
+                         hist + 256, est_order, pool->counter);
+      counter_clear = true;
       base = est_order;
     }
     a.tile_order = base;
@@ -1665,7 +1669,7 @@ grtx_status launch_trace_in(const TraceScene& b, const grtx_rays* r, const grtx_
     a.ray_order = order;
   }
   if (at_once) a.counter = nullptr;  // every group has its item from the start
-  else hipLaunchKernelGGL(k_reset_counter, dim3(1), dim3(64), 0, s, pool->counter);
+  else if (!counter_clear) hipLaunchKernelGGL(k_reset_counter, dim3(1), dim3(64), 0, s, pool->counter);
   if (group) {
     // a wave takes a few rays per visit to the counter, fewer where there are few
     a.group_batch = (int)std::max<int64_t>(kGroupsPerWave, std::min<int64_t>(16, a.n_work / ((int64_t)blocks * 16)));
