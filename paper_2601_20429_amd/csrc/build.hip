@@ -1215,9 +1215,16 @@ constexpr int kTreeletLeaves = 5;
 constexpr float kCostNode = 1.2f;  // surface-area cost of visiting an internal node
 constexpr float kCostLeaf = 1.f;   // ... of testing a leaf
 
+// Half the surface area of a box, and that of a set of treelet leaves. They differ in which
+// product is rounded by itself; each is written out, so that a tree is the same whatever kernel
+// builds it.
 __device__ __forceinline__ float half_area(const float* __restrict__ b) {
   const float ex = fmaxf(b[3] - b[0], 0.f), ey = fmaxf(b[4] - b[1], 0.f), ez = fmaxf(b[5] - b[2], 0.f);
-  return ex * ey + ey * ez + ez * ex;
+  return fmaf(ez, ex, fmaf(ex, ey, ey * ez));
+}
+__device__ __forceinline__ float set_area(const float* __restrict__ b) {
+  const float ex = fmaxf(b[3] - b[0], 0.f), ey = fmaxf(b[4] - b[1], 0.f), ez = fmaxf(b[5] - b[2], 0.f);
+  return fmaf(ez, ex, fmaf(ey, ez, ex * ey));
 }
 
 __device__ __forceinline__ uint32_t node_of(uint32_t c, int64_t nint) {
@@ -1288,7 +1295,7 @@ __device__ __forceinline__ void treelet_dp(const float (&lb)[kTreeletLeaves][6],
         bp = P;
       }
     }
-    copt[S] = kCostNode * half_area(b) + best;
+    copt[S] = kCostNode * set_area(b) + best;
     L.copt[S][tid] = copt[S];
     L.split[S][tid] = (uint8_t)bp;
   }
@@ -1556,7 +1563,7 @@ __device__ __forceinline__ void team_restructure(SubtreeLds<NS>& L, typename Sub
           box[k][3 + a] = i == 0 ? bv[3 + a] : fmaxf(box[k][3 + a], bv[3 + a]);
         }
       }
-      area[k] = half_area(box[k]);
+      area[k] = set_area(box[k]);
     }
   }
   // optimal cost of every subset and the split that reaches it: a split is the part that holds
@@ -1615,7 +1622,7 @@ __device__ __forceinline__ void team_restructure(SubtreeLds<NS>& L, typename Sub
     for (int off = 8; off > 0; off >>= 1) least = fminf(least, __shfl_xor(least, off));
     const uint32_t eq = (uint32_t)(__ballot(c == least) >> (threadIdx.x & 48)) & 0xFFFFu;
     full_split = 1u | 2u * (uint32_t)(eq ? __ffs((int)eq) - 1 : 0);
-    if (tl == 0) L.cost[p] = kCostNode * L.area[p] + least;
+    if (tl == 0) L.cost[p] = kCostNode * set_area(L.box[p]) + least;
   }
   // rebuild top-down, reusing the treelet's internal nodes (p stays the root); the subsets still
   // to be split are stacked in one register, eight bits each: the subset and its node's number
@@ -1662,7 +1669,7 @@ __device__ __forceinline__ void team_restructure(SubtreeLds<NS>& L, typename Sub
         if ((uint32_t)q == me) node = inner[q];
 #pragma unroll
       for (int a = 0; a < 6; ++a) L.box[node][a] = box[k][a];
-      L.area[node] = area[k];
+      L.area[node] = half_area(box[k]);
       L.cost[node] = own[k];
       L.count[node] = (uint16_t)cnt[k];
     }
@@ -1718,7 +1725,9 @@ __global__ void __launch_bounds__(NS) k_treelet(int64_t m, const uint32_t* __res
       atomicMax(depth, h);
     };
     if (n < 3) {
-      if (n == 2 && tid == 0 && cost) cost[first] = kCostNode * L.area[0] + (L.cost[1] + L.cost[2]);
+      if (n == 2 && tid == 0 && cost)  // (summed as the last pass below does)
+        cost[first] = passes > 1 ? kCostNode * L.area[0] + L.cost[1] + L.cost[2]
+                                 : kCostNode * set_area(L.box[0]) + (L.cost[1] + L.cost[2]);
       if (tid == 0 && depth) measure((uint32_t)n - 1u);
       continue;
     }
@@ -1771,7 +1780,7 @@ __global__ void __launch_bounds__(NS) k_treelet(int64_t m, const uint32_t* __res
           const uint32_t p = L.list[i];
           const float c0 = L.cost[L.kid[p][0]], c1 = L.cost[L.kid[p][1]];
           if (min_leaves != 0u && L.count[p] < min_leaves) L.cost[p] = kCostNode * L.area[p] + c0 + c1;
-          else if (L.count[p] == 2u) L.cost[p] = kCostNode * L.area[p] + (c0 + c1);
+          else if (L.count[p] == 2u) L.cost[p] = kCostNode * set_area(L.box[p]) + (c0 + c1);
         }
         for (uint32_t i = beg + (uint32_t)team; i < end; i += NS / kTeam) {
           const uint32_t p = L.list[i];
