@@ -44,8 +44,14 @@ class GRTXRender(torch.autograd.Function):
         bvh = grtx.build(scene, kind=settings.kind, alpha_min=settings.alpha_min)
         o = origins.detach().contiguous()
         d = dirs.detach().contiguous()
-        out = grtx.trace(bvh, o, d, k=settings.k, T_min=settings.T_min, mode=settings.mode, bg=settings.bg,
-                         hit_capacity=settings.hit_capacity, image_width=settings.image_width)
+        # the lists are for the backward pass, which reads each ray's first hit_counts entries: left
+        # uncleared (537 MB for 512x512 rays x 512 hits, 75 us of a 3.3 ms pass)
+        n, new = int(o.shape[0]), lambda *shape, dtype=torch.float32: torch.empty(shape, dtype=dtype, device=o.device)
+        out = dict(rgb=new(n, 3), depth=new(n), opacity=new(n))
+        if settings.hit_capacity > 0:
+            out.update(hit_ids=new(n, settings.hit_capacity, dtype=torch.int32), hit_counts=new(n, dtype=torch.int32))
+        grtx.trace(bvh, o, d, k=settings.k, T_min=settings.T_min, mode=settings.mode, bg=settings.bg, out=out,
+                   hit_capacity=settings.hit_capacity, image_width=settings.image_width)
         ctx.bvh = bvh
         ctx.settings = settings
         ctx.save_for_backward(o, d, out["rgb"], out["depth"], out["opacity"], out["hit_ids"], out["hit_counts"])
