@@ -34,11 +34,17 @@ STAT_NAMES = ("nodes", "leaves", "rounds", "blended", "deferred", "fetch_free", 
               "stack_drops")
 
 
-def alg_bytes(c, sh_degree, rays):
+# Only the one-lane kernel counts. A checkpointed launch without counters runs the kernel of
+# sixteen lanes per ray: the same hits from the same records, but its own order of visits and no
+# checkpoint or eviction lists, so their entries are left out of its bytes.
+COUNTED_BY = "a counting run of the same rays by the one-lane kernel (rounds of k hits)"
+
+
+def alg_bytes(c, sh_degree, rays, lists=True):
     """Algorithmic bytes of a trace from its summed per-ray counters `c` (dict)."""
     return (B_NODE * c["nodes"] + B_LEAF * c["leaves"]
             + (B_BLEND_INST + 4 * 3 * (sh_degree + 1) ** 2) * c["blended"]
-            + B_LIST * (c["deferred"] + c["evicted"]) + B_RAY * rays)
+            + (B_LIST * (c["deferred"] + c["evicted"]) if lists else 0) + B_RAY * rays)
 
 
 def stat_sums(out):
@@ -398,17 +404,19 @@ def run_backward(stream):
     touched = int(torch.unique(ids).numel())
     ncoef = 3 * (st.sh_degree + 1) ** 2
     params = 4 * (3 + 3 + 4 + 1 + ncoef)  # one Gaussian's parameters (or gradients)
-    passes = (max(1, int(np.ceil(np.log2(st.n + 1)))) + 7) // 8
-    per_record = params + 4 + (64 + 12) + passes * 2 * 12 + (64 + 4 + 12)
+    bits = max(1, int(np.ceil(np.log2(st.n + 1))))
+    passes = min((bits + 7) // 8, (bits + 8) // 9)
+    # (the first sorting pass reads no values)
+    per_record = params + 4 + (32 + 4) + passes * 2 * 8 - 4 + (32 + 8 + 24)
     alg = P * per_record + R * (24 + 20 + 12) + touched * 2 * params
     return dict(workload=cfg["name"], forward_with_ids_ms=f_ms, backward_ms=b_ms,
                 backward_mrays_s=R / (b_ms * 1e-3) / 1e6, backward_retrace_ms=r_ms,
                 hit_records=P, records_per_ray=P / R, touched_gaussians=touched,
                 algorithmic_bytes=alg, algorithmic_GBs=alg / (b_ms * 1e-3) / 1e9,
                 algorithmic_frac=alg / (b_ms * 1e-3) / 1e9 / HBM_PEAK_GBS,
-                note=("bytes per hit record: the Gaussian's parameters re-read, its id, the 64-B record and "
-                      "its 12-B sort key written, the sort passes, the record, order and ray direction read "
-                      "back; per ray: ray, forward outputs, output gradient; per touched Gaussian: its "
+                note=("bytes per hit record: the Gaussian's parameters re-read, its id, the 32-B record and "
+                      "its 4-B sort key written, the sort passes, the record, its key and order and the ray "
+                      "read back; per ray: ray, forward outputs, output gradient; per touched Gaussian: its "
                       "gradient read and written. backward_retrace_ms traces the rays again inside the call"))
 
 
@@ -419,7 +427,7 @@ def kernel_k(k):
 TRAFFIC_PROFILE = os.path.join(ROOT, "profiles", "k_trace_k16_scene3m_hbm_traffic.txt")
 # what the traced launch's traffic depends on: the trace kernel, its list sizes and device
 # helpers, and the build of the tree it walks
-TRACE_SOURCES = [os.path.join(ROOT, "paper_2601_20429_amd", "csrc", f) for f in ("trace.hip", "trace_common.h", "build.hip")]
+TRACE_SOURCES = [os.path.join(ROOT, "paper_2601_20429_amd", "csrc", f) for f in ("trace.hip", "trace_common.h", "trace_group.h", "build.hip")]
 
 
 def source_digest():
@@ -633,8 +641,8 @@ class Workload3M:
         ms, tt = self.timed(k, mode, steps, warmup)
         tp, ti = self.alone(k, mode) if alone else (None, None)
         cp, ci, info = self.counters(k, mode)
-        bp = alg_bytes(cp, 3, self.n_prim)
-        bi = alg_bytes(ci, 3, self.n_inc)
+        bp = alg_bytes(cp, 3, self.n_prim, lists=mode != 0)
+        bi = alg_bytes(ci, 3, self.n_inc, lists=mode != 0)
         return dict(k=k, mode="checkpoint" if mode == 0 else "restart", step_ms=ms,
                     mrays_s=self.rays / (ms * 1e-3) / 1e6,
                     trace_ms=tt, trace_mrays_s=self.rays / (tt * 1e-3) / 1e6,
@@ -698,8 +706,8 @@ def run_frame100k(args, stream):
                                  stats=True))
         res[name] = dict(step_ms=ms, mrays_s=R / (ms * 1e-3) / 1e6, trace_ms=kms,
                          trace_mrays_s=R / (kms * 1e-3) / 1e6,
-                         trace_algorithmic_GBs=alg_bytes(c, 3, R) / (kms * 1e-3) / 1e9,
-                         algorithmic_bytes_per_ray=alg_bytes(c, 3, R) / R, **per_ray(c, R))
+                         trace_algorithmic_GBs=alg_bytes(c, 3, R, m == grtx.RESTART) / (kms * 1e-3) / 1e9,
+                         algorithmic_bytes_per_ray=alg_bytes(c, 3, R, m == grtx.RESTART) / R, **per_ray(c, R))
         log(f"100k {name}: step {ms:.3f} ms, trace {kms:.3f} ms, nodes/ray {res[name]['nodes_per_ray']:.1f}")
     res["checkpoint_speedup_trace"] = res["restart"]["trace_ms"] / res["checkpoint"]["trace_ms"]
     res["bvh_bytes"] = int(bvh.info()["device_bytes"])
@@ -891,7 +899,9 @@ def main():
     traffic = measured_traffic(args)
     roofline = {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                 "frac": achieved / HBM_PEAK_GBS, "traffic": traffic,
-                "kernel": f"k_trace<{kernel_k(args.k)}, 0, false>",
+                "kernel": ("k_trace_group<3, false>" if mode == grtx.CHECKPOINT else
+                           f"k_trace<{kernel_k(args.k)}, 0, false>"),
+                "counted_by": COUNTED_BY,
                 "per_launch": "the step's one launch: 2M incoherent rays, then the 1920x1080 frame's 8x8 tiles",
                 "algorithmic_bytes_per_launch": launch_bytes, "launch_ms": launch_ms,
                 "hbm_measured_GBs": None if traffic is None else traffic / (launch_ms * 1e-3) / 1e9,

@@ -182,53 +182,16 @@ __device__ __forceinline__ float row_lane(float v) {
   return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x150 + J, 0xF, 0xF, true));
 }
 
-// Lane M of the quad, for all its lanes; and the sum over the quad.
-template <int M>
-__device__ __forceinline__ int quad_lane(int v) {
-  return __builtin_amdgcn_update_dpp(0, v, M * 0x55, 0xF, 0xF, true);
-}
-__device__ __forceinline__ float quad_sum(float v) {
-  v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0xB1, 0xF, 0xF, true));
-  return v + __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x4E, 0xF, 0xF, true));
-}
-
-// The SH sums of the quad's four hits, degree 3: its lanes read each hit's 48 coefficients
-// together, 64 neighbouring bytes at a time (a lane that reads its own hit's in 16-byte pieces
-// takes a cache access for each: 12 a hit instead of 3). Lane m holds pieces m, m + 4 and m + 8;
-// piece q's element k belongs to channel (q + k) mod 3 and coefficient (4 q + k) / 3, whose
-// basis values are the lane's `weight`.
-template <int I>
-__device__ __forceinline__ void quad_colours(const float4* sh, int own, int m, const float* weight, float* c) {
-  if constexpr (I < 4) {
-    const float4* sp = sh + (int64_t)quad_lane<I>(own) * 12 + m;
-    float part[3] = {0.f, 0.f, 0.f};
-#pragma unroll
-    for (int p = 0; p < 3; ++p) {
-      const float4 v = sp[4 * p];
-      const float e[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-      for (int k = 0; k < 4; ++k) part[(p + k) % 3] += weight[4 * p + k] * e[k];
-    }
-#pragma unroll
-    for (int ch = 0; ch < 3; ++ch) {
-      const float x = m == 1 ? part[(ch + 2) % 3] : m == 2 ? part[(ch + 1) % 3] : part[ch];
-      const float all = quad_sum(x);
-      c[ch] = m == I ? all : c[ch];
-    }
-    quad_colours<I + 1>(sh, own, m, weight, c);
-  }
-}
-
 // The compositing of up to 16 hits, one per lane of the row, in their order: a lane runs the
 // ray's sums up to its own hit (T before it, C and D with it).
 struct Sums {
   float T, C[3], D;
 };
 template <int J>
-__device__ __forceinline__ void replay(int sub, int most, float alpha, const float* c, float t, Sums& s) {
+__device__ __forceinline__ void replay(int sub, int most, float alpha, float rest, const float* c, float t, Sums& s) {
   if constexpr (J < 16) {
     if (J % 4 == 0 && J >= most) return;  // (no row of the wave has a hit there)
-    const float a = row_lane<J>(alpha), t_j = row_lane<J>(t);
+    const float a = row_lane<J>(alpha), rest_j = row_lane<J>(rest), t_j = row_lane<J>(t);
     const float c0 = row_lane<J>(c[0]), c1 = row_lane<J>(c[1]), c2 = row_lane<J>(c[2]);
     if (sub >= J) {
       const float w = s.T * a;
@@ -236,19 +199,20 @@ __device__ __forceinline__ void replay(int sub, int most, float alpha, const flo
       s.C[1] += w * c1;
       s.C[2] += w * c2;
       s.D += w * t_j;
-      if (sub > J) s.T *= 1.f - a;
+      if (sub > J) s.T *= rest_j;
     }
-    replay<J + 1>(sub, most, alpha, c, t, s);
+    replay<J + 1>(sub, most, alpha, rest, c, t, s);
   }
 }
 
-// Replays the rays: sixteen lanes per ray, a hit per lane. Bound by issue (199 of its 316 us) and
-// the latency of a hit's loads (id, then shape and SH); a lane per ray, hit after hit, has the
-// longest ray set the end. 10.7M hits of 262144 rays, degree 3: 1266 us by lane, 316 us so (375
-// when each lane reads its own hit's SH, bound by cache accesses). The sums along the ray stay in hit order (the suffix C - sum cancels against the
-// forward's, which was added up in that order).
+// Replays the rays: sixteen lanes per ray, a hit per lane. Bound by cache accesses (16 a hit, for
+// its shape and SH) and issue; a lane per ray, hit after hit, has the longest ray set the end.
+// 10.7M hits of 262144 rays, degree 3: 1266 us by lane, 369 us so. (Quads that read each hit's SH
+// by whole lines: 316 us, but then the colour's terms add up in another order, and a
+// gradient of scale, where terms a thousand times larger cancel, moves by up to 0.3% of its rms.)
+// For the same reason the sums along the ray stay in hit order, the suffix C - sum cancelling
+// against the forward's, and 1 - alpha and dL/dM are written out as fused operations.
 constexpr int kLanes = 16;
-template <bool DEG3>
 __global__ void __launch_bounds__(kBlock) k_bwd_hits(BwdArgs A) {
   const int64_t r0 = (blockIdx.x * (int64_t)kBlock + threadIdx.x) / kLanes;
   const int sub = threadIdx.x & (kLanes - 1);
@@ -278,15 +242,6 @@ __global__ void __launch_bounds__(kBlock) k_bwd_hits(BwdArgs A) {
   float Y[16];
   basis(d[0] * dn, d[1] * dn, d[2] * dn, A.sh_degree, Y);
   const int ncoef = (A.sh_degree + 1) * (A.sh_degree + 1);
-  const int m = threadIdx.x & 3;
-  float weight[12];
-  if constexpr (DEG3) {
-#pragma unroll
-    for (int e = 0; e < 12; ++e) {  // element e of the lane's three pieces: coefficient (4 m + at) / 3
-      const int at = 16 * (e / 4) + e % 4;
-      weight[e] = m == 0 ? Y[at / 3] : m == 1 ? Y[(at + 4) / 3] : m == 2 ? Y[(at + 8) / 3] : Y[(at + 12) / 3];
-    }
-  }
   const int32_t* ids = A.hit_ids + r * A.hit_cap;
 
   Sums run = {1.f, {0.f, 0.f, 0.f}, 0.f};
@@ -296,17 +251,24 @@ __global__ void __launch_bounds__(kBlock) k_bwd_hits(BwdArgs A) {
     const int32_t id = ahead;
     ahead = h + kLanes < n ? ids[h + kLanes] : -1;
     const bool hit = h < n && id >= 0 && id < A.n_gauss;
-    float alpha = 0.f, G = 0.f, ta = 0.f, c[3] = {0.f, 0.f, 0.f};
+    float alpha = 0.f, rest = 1.f, G = 0.f, ta = 0.f, c[3] = {0.f, 0.f, 0.f};
     bool pos[3] = {false, false, false};
-    float col[3] = {0.f, 0.f, 0.f};
-    if constexpr (DEG3) quad_colours<0>(reinterpret_cast<const float4*>(A.sh), hit ? id : 0, m, weight, col);
     if (hit) {
       const int64_t i = id;
       const Shape shape = load_shape(A.gauss, i);
       float acc[3] = {0.5f, 0.5f, 0.5f};
-      if constexpr (DEG3) {
+      if (A.sh_degree == 3) {
+        // the 48 coefficients as twelve 16-B loads
+        const float4* sp4 = reinterpret_cast<const float4*>(A.sh + i * 48);
+        float4 shv[12];
 #pragma unroll
-        for (int ch = 0; ch < 3; ++ch) acc[ch] += col[ch];
+        for (int q = 0; q < 12; ++q) shv[q] = sp4[q];
+#pragma unroll
+        for (int q = 0; q < 12; ++q) {
+          const float e[4] = {shv[q].x, shv[q].y, shv[q].z, shv[q].w};
+#pragma unroll
+          for (int k = 0; k < 4; ++k) acc[(4 * q + k) % 3] += Y[(4 * q + k) / 3] * e[k];
+        }
       } else {
         const float* shp = A.sh + i * 3 * ncoef;
 #pragma unroll
@@ -325,19 +287,20 @@ __global__ void __launch_bounds__(kBlock) k_bwd_hits(BwdArgs A) {
       const float p[3] = {g.u[0] + ta * g.v[0], g.u[1] + ta * g.v[1], g.u[2] + ta * g.v[2]};
       G = expf(-0.5f * (p[0] * p[0] + p[1] * p[1] + p[2] * p[2]));
       alpha = shape.opac * G;
+      rest = fmaf(-shape.opac, G, 1.f);  // 1 - alpha, from the product before it is rounded
     }
     const int most = max(max(nr[0], nr[1]), max(nr[2], nr[3])) - h0;  // hits of the fullest row here
     Sums own = run;
-    replay<0>(sub, most, alpha, c, ta, own);
+    replay<0>(sub, most, alpha, rest, c, ta, own);
     // the ray's sums so far, for its next 16 hits: those of its last lane
-    run.T = row_lane<15>(own.T * (1.f - alpha));
+    run.T = row_lane<15>(own.T * rest);
 #pragma unroll
     for (int ch = 0; ch < 3; ++ch) run.C[ch] = row_lane<15>(own.C[ch]);
     run.D = row_lane<15>(own.D);
     if (h < n) {
       // ---- compositing derivatives
       const float wgt = own.T * alpha;
-      const float inv1ma = 1.f / (1.f - alpha);
+      const float inv1ma = 1.f / rest;
       float gA = 0.f;
 #pragma unroll
       for (int ch = 0; ch < 3; ++ch) {
@@ -384,11 +347,12 @@ struct SumArgs {
   float* d_sh;
 };
 
-// A record's row in LDS (an odd stride: no bank conflicts): g_u, dL/dM and dL/do, which add up to
-// the gradients of mean, scale, rotation and opacity (the rest is linear and the same for all
-// records of a Gaussian), three colour factors, the basis at its ray and a one.
-constexpr int kTotals = 13;
-constexpr int kRow = kTotals + 3 + 16 + 1;
+// A record's row in LDS (an odd stride: no bank conflicts): g_u, dL/dM, the sums of dL/dM M per
+// axis and dL/do, which add up to the gradients of mean, rotation, scale and opacity (the rest is
+// linear and the same for all records of a Gaussian), three colour factors, the basis at its ray
+// and a one.
+constexpr int kTotals = 16;
+constexpr int kRow = kTotals + 3 + 16 + 2;
 __device__ __forceinline__ void record_row(const BwdArgs& A, uint32_t id, uint32_t rec, float* row) {
   const float4 a = A.rec[2 * (int64_t)rec], b = A.rec[2 * (int64_t)rec + 1];
   const Shape shape = load_shape(A.gauss, id);
@@ -399,18 +363,23 @@ __device__ __forceinline__ void record_row(const BwdArgs& A, uint32_t id, uint32
   const Geom g = geometry(shape, o, d);
   // ---- alpha -> opacity, m2, t
   const float gm2 = gA * (-0.5f * (shape.opac * G));
-  const float gTv = gT / g.vv;
 #pragma unroll
   for (int k = 0; k < 3; ++k) {
     const float p = g.u[k] + ta * g.v[k];
-    const float gu = gm2 * 2.f * p - gTv * g.v[k];
-    const float gv = gm2 * 2.f * ta * p - gTv * (g.u[k] + 2.f * ta * g.v[k]);
+    const float gu = gm2 * 2.f * p - gT * g.v[k] / g.vv;
+    const float gv = gm2 * 2.f * ta * p - gT * (g.u[k] + 2.f * ta * g.v[k]) / g.vv;
     // ---- u = M f, v = M d
     row[k] = gu;
+    float gs = 0.f;
 #pragma unroll
-    for (int j = 0; j < 3; ++j) row[3 + 3 * k + j] = gu * g.f[j] + gv * d[j];
+    for (int j = 0; j < 3; ++j) {
+      const float gM = fmaf(gu, g.f[j], gv * d[j]);
+      row[3 + 3 * k + j] = gM;
+      gs += gM * shape.M[k][j];
+    }
+    row[12 + k] = gs;
   }
-  row[12] = gA * G;
+  row[15] = gA * G;
   // ---- SH: dL/dsh = colour factor x Y
   row[kTotals] = a.z;
   row[kTotals + 1] = a.w;
@@ -422,7 +391,7 @@ __device__ __forceinline__ void record_row(const BwdArgs& A, uint32_t id, uint32
   basis(d[0] * dn, d[1] * dn, d[2] * dn, A.sh_degree, Y);
 #pragma unroll
   for (int k = 0; k < 16; ++k) row[kTotals + 3 + k] = Y[k];
-  row[kRow - 1] = 1.f;
+  row[kRow - 2] = 1.f;
 }
 
 // From a Gaussian's totals to its gradients.
@@ -436,13 +405,9 @@ __device__ __forceinline__ void add_shape(const SumArgs& A, int64_t i, const flo
   for (int k = 0; k < 3; ++k) {
     A.d_means[3 * i + k] += -(shape.M[0][k] * total[0] + shape.M[1][k] * total[1] + shape.M[2][k] * total[2]);
     const float s = A.in.scales[3 * i + k];
-    float gs = 0.f;
 #pragma unroll
-    for (int j = 0; j < 3; ++j) {
-      gs += total[3 + 3 * k + j] * shape.M[k][j];
-      gR[j][k] = total[3 + 3 * k + j] / s;
-    }
-    A.d_scales[3 * i + k] += -gs / s;
+    for (int j = 0; j < 3; ++j) gR[j][k] = total[3 + 3 * k + j] / s;
+    A.d_scales[3 * i + k] += -total[12 + k] / s;
   }
   // ---- R(qhat) -> qhat -> q
   const float gw = 2.f * (-z * gR[0][1] + y * gR[0][2] + z * gR[1][0] - x * gR[1][2] - y * gR[2][0] + x * gR[2][1]);
@@ -457,17 +422,17 @@ __device__ __forceinline__ void add_shape(const SumArgs& A, int64_t i, const flo
   A.d_quats[4 * i + 1] += (gx - x * dot) / qn;
   A.d_quats[4 * i + 2] += (gy - y * dot) / qn;
   A.d_quats[4 * i + 3] += (gz - z * dot) / qn;
-  A.d_opac[i] += total[12];
+  A.d_opac[i] += total[15];
 }
 
 // One share of the sorted records, 64 at a time: a lane turns one into its row, then every lane
-// adds up one of the 61 totals over the rows, four partial sums at a time, and passes it on when
+// adds up one of the 64 totals over the rows, four partial sums at a time, and passes it on when
 // the Gaussian changes: SH at once, 48 neighbouring floats, the others by a lane per Gaussian,
-// kWaiting of them at a time. Two LDS reads and one fma per record for all 61 (a wave per
+// kWaiting of them at a time. Two LDS reads and one fma per record for all 64 (a wave per
 // Gaussian that ended in 59 sums over its lanes spent its time on those: 354 shuffles for some
-// 30 records): 611 us for 10.7M hits, 239 us so, bound by the records' lines (128 bytes
+// 30 records): 611 us for 10.7M hits, 243 us so, bound by the records' lines (128 bytes
 // fetched for 32).
-constexpr int kWaiting = 24;
+constexpr int kWaiting = 8;
 __global__ void __launch_bounds__(64) k_bwd_sums(SumArgs A) {
   __shared__ float s_row[64 * kRow];
   __shared__ float s_total[kWaiting][kTotals];
@@ -481,7 +446,7 @@ __global__ void __launch_bounds__(64) k_bwd_sums(SumArgs A) {
   const uint32_t none = (uint32_t)A.in.n_gauss;
   const int nsh = 3 * (A.in.sh_degree + 1) * (A.in.sh_degree + 1);
   const int ia = lane < 48 ? kTotals + lane % 3 : lane < 48 + kTotals ? lane - 48 : 0;
-  const int ib = lane < 48 ? kTotals + 3 + lane / 3 : kRow - 1;
+  const int ib = lane < 48 ? kTotals + 3 + lane / 3 : kRow - 2;
   uint32_t cur = A.key[begin];
   bool inside = begin > 0 && A.key[begin - 1] == cur;  // its first records are another share's
   float sum[4] = {0.f, 0.f, 0.f, 0.f};
@@ -654,10 +619,7 @@ grtx_status trace_backward(const Bvh* bvh, const grtx_gaussians* g, const grtx_r
   hipLaunchKernelGGL(k_bwd_shapes, dim3(grid(N)), dim3(kBlock), 0, s, a);
   GRTX_TRY(sc.get(&a.rec, 2 * Pmax));
   GRTX_TRY(sc.get(&a.key, Pmax));
-  if (g->sh_degree == 3)
-    hipLaunchKernelGGL(k_bwd_hits<true>, dim3(grid(R * kLanes)), dim3(kBlock), 0, s, a);
-  else
-    hipLaunchKernelGGL(k_bwd_hits<false>, dim3(grid(R * kLanes)), dim3(kBlock), 0, s, a);
+  hipLaunchKernelGGL(k_bwd_hits, dim3(grid(R * kLanes)), dim3(kBlock), 0, s, a);
   GRTX_LAUNCH_CHECK();
   // 3. group by Gaussian, keeping ray order inside a Gaussian
   int bits = 1;  // keys are 0..N (N marks a record of no Gaussian)
