@@ -424,7 +424,7 @@ def kernel_k(k):
     return 4 if k <= 4 else 8 if k <= 8 else 16 if k <= 16 else 32 if k <= 32 else 64
 
 
-TRAFFIC_PROFILE = os.path.join(ROOT, "profiles", "k_trace_k16_scene3m_hbm_traffic.txt")
+TRAFFIC_PROFILE = os.path.join(ROOT, "profiles", "k_trace_group_scene3m_hbm_traffic.txt")
 # what the traced launch's traffic depends on: the trace kernel, its list sizes and device
 # helpers, and the build of the tree it walks
 TRACE_SOURCES = [os.path.join(ROOT, "paper_2601_20429_amd", "csrc", f) for f in ("trace.hip", "trace_common.h", "trace_group.h", "build.hip")]

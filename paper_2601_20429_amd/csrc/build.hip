@@ -1246,17 +1246,15 @@ struct TreeletLds {
   uint32_t stack_node[kTreeletLeaves][NS];
 };
 // Subtree size of the per-subtree pass: 256 leaves, 128 above a million leaves. Smaller
-// subtrees give shorter bottom-up chains and twice the workgroups per CU (at 3M leaves the
-// two passes took 1.43 + 0.30 ms against 1.59 + 0.23 ms, trace time unchanged), but leave
-// more nodes above them untouched where no second pass runs (100k: 0.7% more node visits
-// per ray).
+// subtrees give shorter bottom-up chains and twice the workgroups per CU, but leave more nodes
+// above them untouched where no second pass runs (100k: 0.7% more node visits per ray).
 inline int subtree_leaves(int64_t m) { return m > ((int64_t)1 << 20) ? 128 : 256; }
 // Per-subtree passes: one, three above a million leaves. Each further pass rebuilds the
 // treelets the previous one left, and skips treelet roots of fewer than kLaterPassLeaves
 // leaves (doubled per pass), where little is left to gain (after Karras and Aila's
 // repeated passes with a growing minimum). At 3M leaves the three passes cut node visits
-// per ray by 2.6% and trace time by 5%, for 4 ms more build; at 100k the trace gains less
-// than the pass costs.
+// per ray by 2.6% and trace time by 5% (a lane per ray), for about 2 ms more build; at 100k the
+// trace gains less than the pass costs.
 inline int treelet_passes(int64_t m) { return m > ((int64_t)1 << 20) ? 3 : 1; }
 constexpr uint32_t kLaterPassLeaves = 4;
 

@@ -167,7 +167,7 @@ struct Bvh {
   float* boxes = nullptr;    // [2 n_leaves - 1][6]
   float* root_box = nullptr; // device [6] (points into boxes)
   float* roots = nullptr;    // device [8]: root box, root reference bits, 0
-  float4* cut = nullptr;     // [kCutCap][2]: subtree boxes (lo, leaf count) (hi, 0), see k_cut_write
+  float4* cut = nullptr;     // [kCutCap][2]: subtree boxes (lo, leaf count) (hi, 0), see k_topology
   uint32_t* n_cut = nullptr; // device [1]: entries of `cut` (may exceed kCutCap; read the minimum)
   uint32_t* depth = nullptr; // device [2]: tree depth in internal nodes, 1 if restructured
   uint32_t* density = nullptr;  // [kDensityCells] leaves per grid cell

@@ -16,6 +16,10 @@
 //   RESTART mode: every round starts at the root with the interval (last blended hit,
 //   t_max] and nothing is kept between rounds (the multi-round baseline).
 //
+// A checkpointed launch over sphere instances that writes no counters gives these outputs, bit for
+// bit, by the kernel of trace_group.h (sixteen lanes per ray); what follows is the kernel of the
+// others: counters, restart, proxies.
+//
 // How it maps to CDNA4 (there is no RT unit, so the RT unit's job is done by the wave):
 //   - persistent waves; each lane owns one ray at a time across all of its rounds;
 //     idle lanes are refilled with a ballot + one atomic per wave; rays are taken in
