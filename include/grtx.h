@@ -182,7 +182,8 @@ typedef struct grtx_rays {
  * more than a million leaves, where grtx_trace_noalloc takes 2048 and 512), rounded up
  * to a multiple of 8. A nearly full list is compacted: its nearer entries stay and the
  * ray's distance limit comes down to where the dropped ones begin; the ray falls back to
- * a restart-from-root round only if its blending reaches that limit. Results are the same
+ * a restart-from-root round only if its blending reaches that limit (a round that keeps no
+ * lists where more hits share one distance than the lists hold). Results are the same
  * for every capacity. The lists live in a per-stream pool of
  * 512 B x (288 + 2 x defer + 2 x evict + k) per wave in flight (3072 waves at k <= 32:
  * about 1.7 GB with 256/128, 49 GB with 12288/3072), kept for later calls on the stream;

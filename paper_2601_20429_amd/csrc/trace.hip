@@ -476,6 +476,11 @@ __global__ void __launch_bounds__(kTraceBlock)
   // deferred subtree; hits from distance `lim` on may have been dropped by a full list
   // (infinity: none).
   float lim = INFINITY;
+  // The round keeps no lists, as in restart mode: the ray's last round began at the root, and its
+  // limit came down to the distance that every key in its k-buffer has (more hits share the
+  // distance than the k-buffer and the eviction list hold), so it blended nothing. The same round
+  // again would end the same way, for ever; one without lists has no limit and blends its k-buffer.
+  int bare = 0;
   int nblend = 0;
   bool exhausted = false;
   int chunk = (int)(blockIdx.x % kChunks);
@@ -561,7 +566,7 @@ __global__ void __launch_bounds__(kTraceBlock)
   // them. One that finds its list full is dropped at once and lowers the limit to it:
   // every hit of a subtree lies at its entry distance or beyond.)
   auto defer = [&](uint32_t ref, float t) __attribute__((always_inline)) {
-    if (!ckpt) return;
+    if (!ckpt || bare) return;
     if (ndst_n == Args.cap_d) {
       lim = fminf(lim, t);
       return;
@@ -585,7 +590,7 @@ __global__ void __launch_bounds__(kTraceBlock)
   };
 
   auto evict = [&](uint64_t k64) __attribute__((always_inline)) {
-    if (!ckpt) return;
+    if (!ckpt || bare) return;
     if (edst_n == Args.cap_e) {
       lim = fminf(lim, key_t(k64));
       return;
@@ -954,7 +959,7 @@ __global__ void __launch_bounds__(kTraceBlock)
       const bool full = last != kEmptyKey;
       // with a limit, "no hit left" holds only below it
       const bool limited = lim != INFINITY;
-      const bool done = ert || (!limited && (!full || (ckpt && ndst_n == 0 && edst_n == 0)));
+      const bool done = ert || (!limited && (!full || (ckpt && !bare && ndst_n == 0 && edst_n == 0)));
       // A segment that reached its surface with T >= T_min goes on along its reflected or
       // refracted ray in the same lane: colour, transmittance and the hit list carry over,
       // and the continuation's distances start at the bent path length.
@@ -977,6 +982,7 @@ __global__ void __launch_bounds__(kTraceBlock)
         nsrc_n = nsrc_i = ndst_n = 0;
         esrc_n = esrc_i = edst_n = 0;
         lim = INFINITY;
+        bare = 0;
         root_start();
         state = kTrav;
       } else if (done) {
@@ -997,14 +1003,18 @@ __global__ void __launch_bounds__(kTraceBlock)
 #pragma unroll
           for (int f = 0; f < GRTX_STATS_FIELDS; ++f) st[f] = s_stat[f][tid];
         }
+        bare = 0;
         state = kIdle;
       } else {
+        // (a round that began at the root has no sources)
+        const bool stuck = stopped && lastp == tmin && (nsrc_n | esrc_n) == 0;
         tmin = lastp;
-        if (!ckpt || stopped || (limited && (!full || (ndst_n == 0 && edst_n == 0)))) {
+        if (!ckpt || bare || stopped || (limited && (!full || (ndst_n == 0 && edst_n == 0)))) {
           // restart from the root beyond the last blended hit: restart mode, or a
           // checkpoint whose lists dropped entries and whose remaining keys below the
-          // limit are all blended
+          // limit are all blended, or kept no lists this time
           if (ckpt) STAT(GRTX_STAT_FALLBACKS);
+          bare = stuck;
           lim = INFINITY;
           nsrc_n = nsrc_i = ndst_n = 0;
           esrc_n = esrc_i = edst_n = 0;

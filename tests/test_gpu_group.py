@@ -84,6 +84,28 @@ def test_equal_distances(repeat):
     check(sc, *rays_of(300, 8), cap=1024, T_min=0.0, ref_mode=grtx.RESTART)
 
 
+@pytest.mark.parametrize("kind", [grtx.SPHERE_INSTANCE, grtx.ICO_INSTANCE, grtx.PROXY20])
+@pytest.mark.parametrize("k,caps,ties", [(16, (0, 0), 257), (1, (8, 8), 40), (4, (64, 16), 33), (64, (8, 8), 200)])
+def test_more_ties_than_the_lists_hold(kind, k, caps, ties):
+    """More hits at one distance than the k-buffer and the eviction list hold, in checkpointed
+    launches of the one-lane kernel: a round that could blend none of them is followed by one
+    without lists, and the ray ends with the hits of restart mode."""
+    print("[case] ties", kind, k, caps, ties, flush=True)
+    sc = scene_of(4 * ties, 7, degree=1, repeat=ties, opacity=-2.0)
+    for a in (sc.scales, sc.quats, sc.opacities):
+        a[:] = np.repeat(a[::ties], ties, 0)
+    bvh = grtx.build(grtx.SceneTensors.from_scene(sc, "cuda"), kind=kind, alpha_min=AMIN)
+    o, d = rays_of(130, 8)
+    kw = dict(k=k, T_min=0.0, hit_capacity=1024, stats=True)
+    ref = grtx.trace(bvh, o, d, mode=grtx.RESTART, **kw)
+    got = grtx.trace(bvh, o, d, defer_capacity=caps[0], evict_capacity=caps[1], **kw)
+    torch.cuda.synchronize()
+    assert int(ref["hit_counts"].max()) >= ties
+    assert int(got["stats"][:, grtx.STAT_FALLBACKS].max()) > 0
+    for key in ("rgb", "depth", "opacity", "hit_ids", "hit_counts"):
+        assert torch.equal(got[key], ref[key]), key
+
+
 @pytest.mark.parametrize("degree", [0, 1, 2, 3])
 def test_bounds_and_starting_transmittance(degree):
     o, d = rays_of(900, 9)
