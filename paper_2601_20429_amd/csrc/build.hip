@@ -1283,7 +1283,7 @@ __device__ __forceinline__ void treelet_dp(const float (&lb)[kTreeletLeaves][6],
         }
       }
     float best = INFINITY;
-    int bp = 0;
+    int bp = S & -S;  // (a split also where no cost is finite: boxes of infinite Gaussians)
 #pragma unroll
     for (int P = 1; P < S; ++P) {
       if ((P & S) != P || !(P & S & -S)) continue;  // each split once: the part holding the lowest leaf
@@ -1618,7 +1618,8 @@ __device__ __forceinline__ void team_restructure(SubtreeLds<NS>& L, typename Sub
     float least = c;
 #pragma unroll
     for (int off = 8; off > 0; off >>= 1) least = fminf(least, __shfl_xor(least, off));
-    const uint32_t eq = (uint32_t)(__ballot(c == least) >> (threadIdx.x & 48)) & 0xFFFFu;
+    // (of the fifteen splits; where no cost is a number, the first)
+    const uint32_t eq = (uint32_t)(__ballot(c == least) >> (threadIdx.x & 48)) & 0x7FFFu;
     full_split = 1u | 2u * (uint32_t)(eq ? __ffs((int)eq) - 1 : 0);
     if (tl == 0) L.cost[p] = kCostNode * set_area(L.box[p]) + least;
   }

@@ -71,3 +71,30 @@ def test_restructured_tree_renders_like_the_plain_one(n, dups):
     a, b = (grtx.trace(build(n, 50, p, dups), o, d, image_width=97, hit_capacity=256) for p in (False, True))
     for key in ("rgb", "depth", "opacity", "hit_ids", "hit_counts"):
         assert torch.equal(a[key], b[key]), key
+
+
+@pytest.mark.parametrize("n", [5, 257, 5000, 1_100_000])
+@pytest.mark.parametrize("what", ["scale", "all scales", "mean", "mean and scales"])
+def test_trees_over_infinite_gaussians(n, what):
+    """Boxes whose surface area is infinite or no number leave a treelet without a cheapest split:
+    the build still ends with a tree over all leaves, and so do rays through it, alike in both
+    kernels."""
+    print("[case] infinite", n, what, flush=True)
+    sc = inputs.cluster_scene(61, n, 0)
+    odd = np.arange(0, n, 3 if n <= 5000 else 97)
+    if what == "scale":  # (unrotated: the box is no number on the other axes, and neither is its area)
+        sc.quats[odd] = np.float32([1, 0, 0, 0])
+        sc.scales[odd, 0] = np.inf
+    if "scales" in what:
+        sc.scales[odd] = np.inf
+    if "mean" in what:
+        sc.means[odd, 1] = np.inf
+    bvh = grtx.build(grtx.SceneTensors.from_scene(sc, "cuda"), alpha_min=AMIN)
+    child = bvh.export_topology()["child"].cpu().numpy().view(np.uint32)
+    node = np.where(child >> 31 != 0, (child & 0x7FFFFFFF) + (n - 1), child).astype(np.int64)
+    assert np.array_equal(np.sort(node.ravel()), np.arange(1, 2 * n - 1))  # every node once
+    o, d = grtx.pinhole_rays(inputs.orbit_camera(40, 30))
+    ref = grtx.trace(bvh, o, d, image_width=40, stats=True)
+    got = grtx.trace(bvh, o, d, image_width=40)
+    for key in ("rgb", "depth", "opacity"):
+        assert torch.equal(torch.nan_to_num(got[key], 7.0), torch.nan_to_num(ref[key], 7.0)), key
