@@ -91,8 +91,9 @@ constexpr int kOnceWait = 8;
 struct GroupLds {
   uint64_t key[kGroupHits];
   float rest[kGroupHits];                 // 1 - alpha
-  uint2 item[kGroupRing + kGroupLeaves];  // the node stack's ring, then the leaf stack
-  uint2 none[8];  // written instead of a child not entered; the groups' entries start in different banks
+  // the node stack's ring, then the leaf stack, then what is written for a child not entered
+  // (eight entries, so that the groups' start in different banks)
+  uint2 item[kGroupRing + kGroupLeaves + 8];
 };
 
 // LDS traffic between lanes of one wave needs no barrier (a wave's LDS operations complete
@@ -196,6 +197,8 @@ __device__ __forceinline__ float pass_on(float T, float rest) {
   return before;
 }
 
+// (reads what was stored as uint2)
+typedef uint64_t __attribute__((may_alias)) any_u64;
 // The rows in device memory for the deep end of the group's node stack.
 __device__ __forceinline__ uint2* group_spill(KernArgs& A, int lane) {
   return A.pool + ((int64_t)blockIdx.x * kGroupsPerWave + lane / kGroup) * kGroupSpill;
@@ -829,7 +832,7 @@ __global__ void __launch_bounds__(64)
           n_low -= kGroupMove;
 #pragma unroll
           for (int j = 0; j < kGroupMove; j += kGroup) {
-            const uint64_t v = *reinterpret_cast<const uint64_t*>(spill + n_low + j + gl);
+            const uint64_t v = *reinterpret_cast<const any_u64*>(spill + n_low + j + gl);
             G.item[(n_low + j + gl) & (kGroupRing - 1)] = make_uint2((uint32_t)v, (uint32_t)(v >> 32));
           }
           if (n_low == 0) low_t = INFINITY;
