@@ -255,7 +255,7 @@ __global__ void __launch_bounds__(64)
   int sid = 0;
   float* out_at = nullptr;
   uint32_t out_n = 0;
-  uint32_t sv_seq = 0, fin_slot = 0, fin_n = 0, fin_count = 0, sv_tick = 0;
+  uint32_t sv_seq = 0, fin_slot = 0, fin_n = 0, fin_count = 0;
   uint64_t idle_since = 0;
   if constexpr (SERVE) {
     if (lane0 == 0) {
@@ -282,7 +282,6 @@ __global__ void __launch_bounds__(64)
     const int gl = lane & (kGroup - 1);        // lane within the group
     const int row0 = lane & ~(kGroup - 1);     // the group's first lane
     // ------------------------------------------------------------ rays for idle groups
-    if constexpr (SERVE) fresh = fresh || (++sv_tick & 15u) == 0u;  // (a request may have come since)
     if (fresh) {
       const uint64_t idle = __ballot(!live && gl == 0);
       bool nowork = false;
@@ -386,7 +385,10 @@ __global__ void __launch_bounds__(64)
         continue;
       }
       idle_since = 0;
-      fresh = !exhausted && __ballot(!live) != 0;  // (an item outside the image leaves its group without a ray)
+      // (an item outside the image leaves its group without a ray; a served wave whose claim found
+      // nothing asks again at its next step, for a request may have come: asking every sixteen steps
+      // made a burst of eight requests 1% slower)
+      fresh = !exhausted && __ballot(!live) != 0;
       if (__ballot(start)) {
         // ---------------------------------------------------------- start at the root
         // The ray's first two levels in one step: lane 4 i + j tests child i of the root's record
