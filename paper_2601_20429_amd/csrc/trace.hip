@@ -107,6 +107,7 @@ constexpr int kLargeEvictCap = 3072;
 constexpr int kNoAllocLargeDeferCap = 2048;
 constexpr int kNoAllocLargeEvictCap = 512;
 constexpr int64_t kLargeScene = 1000000;
+constexpr int kNoLists = 1 << 30;  // (beyond any capacity) a list's length in a round that keeps none
 inline int default_defer_cap(int64_t n_leaves, bool noalloc) {
   return n_leaves <= kLargeScene ? kDefaultDeferCap : noalloc ? kNoAllocLargeDeferCap : kLargeDeferCap;
 }
@@ -476,11 +477,6 @@ __global__ void __launch_bounds__(kTraceBlock)
   // deferred subtree; hits from distance `lim` on may have been dropped by a full list
   // (infinity: none).
   float lim = INFINITY;
-  // The round keeps no lists, as in restart mode: the ray's last round began at the root, and its
-  // limit came down to the distance that every key in its k-buffer has (more hits share the
-  // distance than the k-buffer and the eviction list hold), so it blended nothing. The same round
-  // again would end the same way, for ever; one without lists has no limit and blends its k-buffer.
-  int bare = 0;
   int nblend = 0;
   bool exhausted = false;
   int chunk = (int)(blockIdx.x % kChunks);
@@ -566,8 +562,8 @@ __global__ void __launch_bounds__(kTraceBlock)
   // them. One that finds its list full is dropped at once and lowers the limit to it:
   // every hit of a subtree lies at its entry distance or beyond.)
   auto defer = [&](uint32_t ref, float t) __attribute__((always_inline)) {
-    if (!ckpt || bare) return;
-    if (ndst_n == Args.cap_d) {
+    if (!ckpt) return;
+    if (ndst_n >= Args.cap_d) {
       lim = fminf(lim, t);
       return;
     }
@@ -590,8 +586,8 @@ __global__ void __launch_bounds__(kTraceBlock)
   };
 
   auto evict = [&](uint64_t k64) __attribute__((always_inline)) {
-    if (!ckpt || bare) return;
-    if (edst_n == Args.cap_e) {
+    if (!ckpt) return;
+    if (edst_n >= Args.cap_e) {
       lim = fminf(lim, key_t(k64));
       return;
     }
@@ -612,14 +608,14 @@ __global__ void __launch_bounds__(kTraceBlock)
   // LDS. (Lists shorter than that margin are compacted at every check; an append that
   // still finds its list full is dropped and lowers the limit.)
   auto make_room = [&]() __attribute__((always_inline)) {
-    if (ndst_n > Args.cap_d - 5 * kRoomEvery) {
+    if (ndst_n > Args.cap_d - 5 * kRoomEvery && ndst_n <= Args.cap_d) {
       const int row0 = rowN + (par ^ 1) * Args.cap_d;
       if (ndst_n & (kStage - 1)) flush_dst(ndst_n & ~(kStage - 1));
       ndst_n = compact(row0, ndst_n);
 #pragma unroll 1
       for (int j = ndst_n & ~(kStage - 1); j < ndst_n; ++j) s_dst[(j & (kStage - 1)) * kTraceBlock + tid] = LROW(row0 + j);
     }
-    if (edst_n > Args.cap_e - kRoomEvery) {
+    if (edst_n > Args.cap_e - kRoomEvery && edst_n <= Args.cap_e) {
       const int row0 = rowE + (par ^ 1) * Args.cap_e;
       if constexpr (kStageEv > 0) {
         if (edst_n & (kStageEv - 1)) flush_evict(edst_n & ~(kStageEv - 1));
@@ -891,8 +887,12 @@ __global__ void __launch_bounds__(kTraceBlock)
     // ---------------------------------------------------------------- round end: blend
     if (state == kEnd) {
       STAT(GRTX_STAT_ROUNDS);
-      const int ncoef = (A.sh_degree + 1) * (A.sh_degree + 1);
       bool ert = false;
+      const bool bare = ndst_n > A.cap_d;  // the round kept no lists: there is no limit to its blending
+      if (bare) {
+        ndst_n = edst_n = 0;
+        lim = INFINITY;
+      }
       // Blend in key order. The k-buffer is parked in the lane's rows so that the blend
       // loop indexes memory rather than a register array.
       const uint64_t last = kb[K - 1];
@@ -982,7 +982,6 @@ __global__ void __launch_bounds__(kTraceBlock)
         nsrc_n = nsrc_i = ndst_n = 0;
         esrc_n = esrc_i = edst_n = 0;
         lim = INFINITY;
-        bare = 0;
         root_start();
         state = kTrav;
       } else if (done) {
@@ -1003,10 +1002,12 @@ __global__ void __launch_bounds__(kTraceBlock)
 #pragma unroll
           for (int f = 0; f < GRTX_STATS_FIELDS; ++f) st[f] = s_stat[f][tid];
         }
-        bare = 0;
         state = kIdle;
       } else {
-        // (a round that began at the root has no sources)
+        // The round began at the root (it has no sources) and could blend nothing: more hits share
+        // one distance than the k-buffer and the eviction list hold, which brought the limit down
+        // to the distance of every key in the k-buffer. The same round again would end the same
+        // way, for ever; the next one keeps no lists, as in restart mode, and blends its k-buffer.
         const bool stuck = stopped && lastp == tmin && (nsrc_n | esrc_n) == 0;
         tmin = lastp;
         if (!ckpt || bare || stopped || (limited && (!full || (ndst_n == 0 && edst_n == 0)))) {
@@ -1014,10 +1015,10 @@ __global__ void __launch_bounds__(kTraceBlock)
           // checkpoint whose lists dropped entries and whose remaining keys below the
           // limit are all blended, or kept no lists this time
           if (ckpt) STAT(GRTX_STAT_FALLBACKS);
-          bare = stuck;
           lim = INFINITY;
-          nsrc_n = nsrc_i = ndst_n = 0;
-          esrc_n = esrc_i = edst_n = 0;
+          nsrc_n = nsrc_i = 0;
+          esrc_n = esrc_i = 0;
+          ndst_n = edst_n = stuck ? kNoLists : 0;
           root_start();
         } else {
           // resume: this round's destination lists become the next round's sources (the
