@@ -437,9 +437,11 @@ grtx_status grtx_trace_backward(const grtx_bvh* bvh, const grtx_gaussians* g, co
 typedef struct grtx_server grtx_server;
 
 /* memory_budget: device bytes the server may hold (a fixed share for the serving kernel,
- *   about 8.3 GB at k <= 32, the checkpoint lists of one lane per ray with 2048 deferred
- *   nodes and 512 evicted hits, of which the kernel takes 270 MB; the scene set copy, and per admitted request its outputs until released; the outputs
- *   live in an arena grown in chunks of at least 1 GiB within the budget).
+ *   about 8.3 GB at k <= 32: what checkpoint lists of one lane per ray with 2048 deferred
+ *   nodes and 512 evicted hits take, the measure budgets are given in, though the kernel
+ *   holds 100 MB of it; the scene set copy, and per admitted request its outputs until
+ *   released; the outputs live in an arena grown in chunks of at least 1 GiB within the
+ *   budget).
  * k, T_min, mode, bg: as in grtx_trace_params, for every request (mode CHECKPOINT or
  *   RESTART; neither k nor the mode enters: every ray has sixteen lanes, see
  *   grtx_trace_params).
@@ -508,7 +510,7 @@ typedef struct grtx_serve_stats {
 grtx_status grtx_serve_request_bytes(const grtx_request* r, int64_t* bytes);
 
 /* Create a server on the current device. GRTX_ERR_CAPACITY if the budget cannot even
- * hold the serving kernel's checkpoint pool. */
+ * hold the serving kernel's fixed share. */
 grtx_status grtx_serve_create(const grtx_serve_config* cfg, grtx_server** out);
 
 /* Register a built SPHERE_INSTANCE structure (all scenes share one SH degree) before the

@@ -126,7 +126,7 @@ struct Server {
   ServeHost* host_dev = nullptr;  // its device address
   ServeDev* dev = nullptr;
   void* pool = nullptr;
-  int64_t fixed_bytes = 0;        // kernel pool and queue
+  int64_t fixed_bytes = 0;        // the kernel's share and the queue
   uint64_t poll_ticks = 0, idle_ticks = 0;
   uint64_t published = 0;         // requests published so far (request numbers)
   uint64_t slot_ticket[kServeRing] = {};  // ticket of the request in each slot (0: free)
@@ -459,12 +459,12 @@ grtx_status serve_create(const grtx_serve_config* cfg, Server** out) {
   }
   sv->poll_ticks = std::max<uint64_t>(1, (uint64_t)clock_khz * kPollMicros / 1000);
   sv->idle_ticks = std::max<uint64_t>(1, (uint64_t)clock_khz * (uint64_t)sv->cfg.idle_exit_us / 1000);
-  // the kernel's checkpoint pool and the queue count against the budget
+  // a fixed share for the kernel (more than its pool) and the queue count against the budget
   const int64_t pool_bytes = serve_pool_bytes(), counted = serve_budget_bytes(cfg->k);
   sv->fixed_bytes = counted + (int64_t)sizeof(ServeDev);
   sv->available = cfg->memory_budget - sv->fixed_bytes;
   if (pool_bytes <= 0 || sv->available <= 0) {
-    set_error("grtx_serve_create: budget %lld bytes is below the serving kernel's checkpoint pool (%lld bytes)",
+    set_error("grtx_serve_create: budget %lld bytes is below the fixed share for the serving kernel (%lld bytes)",
               (long long)cfg->memory_budget, (long long)counted);
     delete sv;
     return GRTX_ERR_CAPACITY;

@@ -1354,7 +1354,7 @@ int serve_blocks(int degree) {
 
 }  // namespace
 
-int64_t serve_pool_bytes() { return (int64_t)serve_cus() * 32 * kGroupBlockBytes; }
+int64_t serve_pool_bytes() { return (int64_t)serve_cus() * kServeWaves * kGroupBlockBytes; }
 
 // Three workgroups on all but eight CUs (two above k = 32) of four waves, each with lists of 2048 deferred
 // nodes and 512 hits per lane, the stack spill and the k-buffer: what a kernel with one lane
