@@ -6,7 +6,9 @@ transmittances, waves with idle groups. Needs an MI355X."""
 import numpy as np
 import pytest
 
+import oracle
 from paper_2601_20429_amd import inputs
+from tests import parity
 
 pytestmark = pytest.mark.gpu
 torch = pytest.importorskip("torch")
@@ -143,3 +145,43 @@ def test_degenerate_rays():
     got = grtx.trace(bvh, o, d)
     for key in ("rgb", "depth", "opacity"):
         assert torch.equal(torch.nan_to_num(got[key], 7.0), torch.nan_to_num(ref[key], 7.0)), key
+
+
+@pytest.mark.parametrize("k", [1, 2, 4, 8, 16, 32, 64])
+def test_counting_kernel_at_every_k(k):
+    # the rounds of k hits, which only launches with counters, restart mode and proxies take
+    cam = inputs.orbit_camera(160, 120)
+    o, d = grtx.pinhole_rays(cam)
+    ref = check(inputs.cluster_scene(2, 100_000, 3), o, d, cap=128, k=k, image_width=160)
+    assert int(ref["stats"][:, grtx.STAT_ROUNDS].max()) * k >= int(ref["hit_counts"].max()) > 16
+
+
+@pytest.mark.parametrize("what", ["plain frame", "frame", "incoherent"])
+def test_against_the_oracle(what):
+    """The sixteen-lane kernel itself, by the parity rule, without the detour over the other one."""
+    print("[case]", what, flush=True)
+    scene = inputs.small_scene(1, 1000) if what == "plain frame" else inputs.cluster_scene(2, 100_000, 3)
+    width = {"plain frame": 64, "frame": 800, "incoherent": 0}[what]
+    if width:
+        o, d = (a.astype(np.float32) for a in oracle.pinhole_rays(inputs.orbit_camera(width, width)))
+    else:
+        o, d = inputs.incoherent_rays(33, 70_000)
+    bvh = grtx.build(grtx.SceneTensors.from_scene(scene, "cuda"), alpha_min=AMIN)
+    out = grtx.trace(bvh, torch.from_numpy(o).cuda(), torch.from_numpy(d).cuda(), T_min=1e-3, image_width=width,
+                     hit_capacity=512)
+    idx = np.arange(len(o)) if what == "plain frame" else inputs.ray_subsample(321, len(o), 768)
+    sub = {key: v.cpu().numpy()[idx] for key, v in out.items()}
+    ref = oracle.render(scene, o[idx], d[idx], AMIN, 1e-3, cap=512)
+    print(parity.compare_render(scene, o[idx], d[idx], sub, ref, AMIN, 1e-3, label=what), flush=True)
+
+
+def test_largest_launch_equals_the_counting_kernel():
+    """3M Gaussians, 2M incoherent rays and the 1920x1080 frame in one launch: rays that start in
+    dense clusters, whose stacks leave LDS, and every wave taking new work many times over."""
+    print("[case] 3M", flush=True)
+    cfg = inputs.SCENE3M
+    cam = inputs.orbit_camera(cfg["width"], cfg["height"])
+    po, pd = grtx.pinhole_rays(cam)
+    fo, fd = (torch.from_numpy(a).cuda() for a in inputs.incoherent_rays(cfg["incoherent_seed"], cfg["incoherent"]))
+    check(inputs.cluster_scene(cfg["seed"], cfg["n"], 3), torch.cat([fo, po]), torch.cat([fd, pd]), cap=64,
+          image_width=cfg["width"], image_begin=len(fo))
