@@ -79,3 +79,27 @@ def test_noalloc_equals_trace_twice():
     with pytest.raises(grtx.GrtxError) as e:
         grtx.trace_noalloc(bvh, o, d, _outputs(64, 4), k=16, defer_capacity=1 << 20, evict_capacity=1 << 20)
     assert e.value.status == grtx.ERR_CAPACITY
+
+
+@pytest.mark.parametrize("width,height,free", [(0, 0, 5), (0, 0, 20_011), (7, 9, 3), (100, 37, 5_003), (320, 240, 1001)])
+def test_noalloc_without_counters(width, height, free):
+    """The same entry without counters (sixteen lanes per ray): a launch that needs no queue, ragged
+    images behind free rays, and launches of more rays than groups (some 16 thousand), whose work
+    comes from the queue."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    say("noalloc without counters", width, height, free)
+    bvh = grtx.build(grtx.SceneTensors.from_scene(inputs.cluster_scene(2, 100_000, 3), "cuda"), alpha_min=AMIN)
+    o, d = (torch.from_numpy(a).cuda() for a in inputs.incoherent_rays(5, free))
+    if width:
+        po, pd = grtx.pinhole_rays(inputs.orbit_camera(width, height))
+        o, d = torch.cat([o, po]), torch.cat([d, pd])
+    kw = dict(T_min=1e-3, image_width=width, image_begin=free if width else 0)
+    ref = grtx.trace(bvh, o, d, stats=True, hit_capacity=256, **kw)
+    for _ in range(2):
+        out = _outputs(len(o), 256)
+        del out["stats"]
+        got = grtx.trace_noalloc(bvh, o, d, out, **kw)
+        torch.cuda.synchronize()
+        for key in ["rgb", "depth", "opacity", "hit_ids", "hit_counts"]:
+            assert torch.equal(got[key], ref[key]), key
