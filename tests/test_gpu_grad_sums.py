@@ -94,3 +94,45 @@ def test_sums_of_made_up_lists(rays, n, cap, degree, least, given):
         tol = 5e-4 * (np.abs(want) + np.sqrt((want ** 2).mean())) + 2e-7  # (the last: of the ones)
         bad = np.abs(got - want) > tol
         assert not bad.any(), (k, int(bad.sum()), np.abs(got - want)[bad][:4], want[bad][:4])
+
+
+@pytest.mark.parametrize("n", [200, 70_000, 300_000])
+def test_sums_behind_a_scanned_sort(n):
+    """A bound of rays x capacity that gives the sort of the hits a table too large for its workgroups
+    to add up themselves (above 16.8M; digits of eight and nine bits), with few hits in it. Tolerance
+    as above."""
+    rays, cap, most = 300_000, 64, 4
+    print("[case] scanned", n, flush=True)
+    g = torch.Generator().manual_seed(n)
+    rnd = lambda *s: torch.randn(*s, generator=g)
+    uni = lambda *s: torch.rand(*s, generator=g)
+    sc = inputs.cluster_scene(1, n, 0)
+    p = dict(means=0.5 * rnd(n, 3), scales=0.3 + 0.7 * uni(n, 3), quats=rnd(n, 4), opacities=0.02 + 0.5 * uni(n),
+             sh=0.3 * rnd(n, 1, 3))
+    p["quats"] += torch.sign(p["quats"]) * 0.1
+    for k, v in p.items():
+        getattr(sc, k)[...] = v.numpy().reshape(getattr(sc, k).shape)
+    o = torch.tensor([0.0, 0.0, -4.0]) + 0.5 * rnd(rays, 3)
+    d = torch.tensor([0.0, 0.0, 1.0]) + 0.2 * rnd(rays, 3)
+    ids = torch.randint(0, n, (rays, most), generator=g, dtype=torch.int32)
+    counts = torch.randint(0, most + 1, (rays,), generator=g, dtype=torch.int32)
+    live = torch.arange(most) < counts[:, None]
+
+    p64 = {k: v.double().requires_grad_() for k, v in p.items()}
+    Y = torch.full((rays, 1), float(oracle.sh_basis(0, 0, np.float64([0, 0, 1]))), dtype=torch.float64)
+    out = composite(p64, o.double(), d.double(), Y, ids.long(), live)
+    up = (rnd(rays, 3), rnd(rays), rnd(rays))
+    sum((u.double() * x).sum() for u, x in zip(up, out)).backward()
+
+    bvh = grtx.build(grtx.SceneTensors.from_scene(sc, "cuda"))
+    cu = lambda x: x.detach().float().contiguous().cuda()
+    lists = torch.full((rays, cap), -1, dtype=torch.int32)
+    lists[:, :most] = ids
+    fwd = dict(rgb=cu(out[0]), depth=cu(out[1]), opacity=cu(out[2]), hit_ids=lists.cuda(), hit_counts=counts.cuda())
+    grads, cut = grtx.trace_backward(bvh, o.cuda(), d.cuda(), fwd, *(u.cuda() for u in up))
+    assert int(cut.item()) == 0
+    for k in NAMES:
+        want = p64[k].grad.numpy().reshape(-1)
+        got = grads[k].double().cpu().numpy().reshape(-1)
+        bad = np.abs(got - want) > 5e-4 * (np.abs(want) + np.sqrt((want ** 2).mean())) + 2e-7
+        assert not bad.any(), (k, int(bad.sum()), np.abs(got - want)[bad][:4], want[bad][:4])
