@@ -253,7 +253,7 @@ typedef struct grtx_camera {
 } grtx_camera;
 
 /* Build the acceleration structure (LBVH: Morton codes of the means, stable radix
- * sort, radix tree, bottom-up refit, then, unless p->plain_lbvh, bottom-up passes of
+ * sort, radix tree with exact boxes, then, unless p->plain_lbvh, bottom-up passes of
  * treelet restructuring: one, three above 2^20 leaves) over `g`. Enqueued on `stream`; the handle may be
  * used for grtx_trace on the same stream right away. On success *out receives a new
  * handle (free it with grtx_bvh_destroy). */

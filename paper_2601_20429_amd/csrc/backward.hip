@@ -20,7 +20,7 @@
 // The sum over rays is done without atomics and in a fixed order, in three kernels. k_bwd_hits
 // replays each ray and writes one 32-byte record per (ray, blended hit): dL/da, dL/dt and the
 // colour factors dL/dc * T a [c > 0]; the records' positions are sorted by Gaussian (stable, so
-// ray order is kept inside a Gaussian); k_bwd_sums walks the sorted records in equal shares,
+// their order, fixed by rays and lists, is kept inside a Gaussian); k_bwd_sums walks the sorted records in equal shares,
 // forms each record's gradients of mean, scale, rotation, opacity and SH (colour factor x
 // Y(ray direction)), adds them up per Gaussian and, for a Gaussian whose records lie within the
 // share, adds the totals to the caller's arrays; k_bwd_join adds up the Gaussians that reach
@@ -621,7 +621,7 @@ grtx_status trace_backward(const Bvh* bvh, const grtx_gaussians* g, const grtx_r
   GRTX_TRY(sc.get(&a.key, Pmax));
   hipLaunchKernelGGL(k_bwd_hits, dim3(grid(R * kLanes)), dim3(kBlock), 0, s, a);
   GRTX_LAUNCH_CHECK();
-  // 3. group by Gaussian, keeping ray order inside a Gaussian
+  // 3. group by Gaussian, keeping the records' order inside a Gaussian
   int bits = 1;  // keys are 0..N (N marks a record of no Gaussian)
   while (bits < 32 && ((int64_t)1 << bits) <= N) ++bits;
   uint32_t *vals = nullptr, *tkeys = nullptr, *tvals = nullptr, *skey = nullptr, *sval = nullptr;

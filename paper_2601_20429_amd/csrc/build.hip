@@ -1133,11 +1133,11 @@ inline unsigned grid_for(int64_t n) { return (unsigned)std::max<int64_t>(1, (n +
 
 
 
-// Sorts `keys`; `vals` receives, for each, the position it came from.
+// Sorts keys by `passes` digits: *kres and *vres receive the arrays that hold the sorted keys and the
+// positions they came from (after an even number of passes `keys` and `vals`, else the temporaries).
 template <class K, int BITS>
 grtx_status radix_sort(K* keys, uint32_t* vals, K* tkeys, uint32_t* tvals, int64_t n, Scratch& sc, hipStream_t s,
-                       int passes, const uint32_t* n_dev = nullptr, K** kres = nullptr,
-                       uint32_t** vres = nullptr) {
+                       int passes, const uint32_t* n_dev, K** kres, uint32_t** vres) {
   const int items = n <= kRadixSmall ? kRadixItemsSmall : kRadixItems;
   const int64_t tile = (int64_t)kBlock * items;
   const int64_t tiles = (n + tile - 1) / tile;
@@ -1192,13 +1192,8 @@ grtx_status radix_sort(K* keys, uint32_t* vals, K* tkeys, uint32_t* tvals, int64
     std::swap(kin, kout);
     std::swap(vin, vout);
   }
-  if (kres) {  // the caller takes the result where the last pass left it
-    *kres = kin;
-    *vres = vin;
-  } else if (kin != keys) {  // an odd number of passes leaves the result in the temporaries
-    GRTX_HIP(hipMemcpyAsync(keys, kin, sizeof(K) * n, hipMemcpyDeviceToDevice, s));
-    GRTX_HIP(hipMemcpyAsync(vals, vin, sizeof(uint32_t) * n, hipMemcpyDeviceToDevice, s));
-  }
+  *kres = kin;
+  *vres = vin;
   return GRTX_OK;
 }
 
@@ -1209,8 +1204,9 @@ grtx_status radix_sort(K* keys, uint32_t* vals, K* tkeys, uint32_t* tvals, int64
 // found by dynamic programming over the subsets of the treelet leaves (restructuring after
 // Karras and Aila's treelet optimisation). Leaves keep their sorted positions, so the
 // leaf order of the instances and every traced result are unchanged; only internal nodes
-// are rewired, each keeping its index. A node is processed by the second of the two
-// threads that reach it from its children, after both subtrees are final.
+// are rewired, each keeping its index. A node comes after both of its subtrees: inside a subtree
+// the nodes are taken by height, and above the subtrees by the second of the two threads that
+// reach a node from its children.
 constexpr int kTreeletLeaves = 5;
 constexpr float kCostNode = 1.2f;  // surface-area cost of visiting an internal node
 constexpr float kCostLeaf = 1.f;   // ... of testing a leaf
@@ -1234,9 +1230,9 @@ __device__ __forceinline__ uint32_t ref_of(uint32_t u, int64_t nint) {
   return (int64_t)u >= nint ? kLeafFlag | (uint32_t)(u - nint) : u;
 }
 
-// Per-thread work arrays of the subset dynamic programme live in LDS, entry-major
-// ([entry][thread]), so that lanes index them independently; NS threads per workgroup,
-// one per leaf of its subtree.
+// The nodes above the subtrees take a thread each (k_treelet_top). Its work arrays of the subset
+// dynamic programme live in LDS, entry-major ([entry][thread]), so that lanes index them
+// independently; NS threads per workgroup.
 constexpr int kSets = 1 << kTreeletLeaves;
 template <int NS>
 struct TreeletLds {
@@ -2074,7 +2070,8 @@ grtx_status build_bvh(const grtx_gaussians* g, grtx_bvh_kind kind, float alpha_m
   hipLaunchKernelGGL(k_morton, dim3(std::min(grid_for(m), 2048u)), dim3(kBlock), 0, s, points, m, partial, nparts, bounds,
                      b->dbox, b->codes);
   GRTX_LAUNCH_CHECK();
-  GRTX_TRY((radix_sort<uint64_t, 8>(b->codes, b->perm, tkeys, tvals, m, sc, s, 8)));
+  // (eight passes: the result is where the codes were)
+  GRTX_TRY((radix_sort<uint64_t, 8>(b->codes, b->perm, tkeys, tvals, m, sc, s, 8, nullptr, &b->codes, &b->perm)));
   if (proxy) {
     hipLaunchKernelGGL(k_proxy_leaves, dim3(grid_for(m)), dim3(kBlock), 0, s, b->perm, m, ttmp, tbox, b->tris,
                        b->boxes, cent, bounds, b->density);
@@ -2136,12 +2133,8 @@ grtx_status build_bvh(const grtx_gaussians* g, grtx_bvh_kind kind, float alpha_m
         hipLaunchKernelGGL(k_fill_u32, dim3(grid_for(nint)), dim3(kBlock), 0, s, arrivals, nint, 0u);
         hipLaunchKernelGGL(k_fill_u32, dim3(grid_for(nint)), dim3(kBlock), 0, s, th, nint, 0u);
         const unsigned top_groups = (unsigned)((m + ns - 1) / ns);
-        if (ns == 256)
-          hipLaunchKernelGGL(k_treelet_top<256>, dim3(top_groups), dim3(256), 0, s, m, to.roots, n_roots, b->child,
-                             b->parent, b->boxes, costs, count, arrivals);
-        else
-          hipLaunchKernelGGL(k_treelet_top<128>, dim3(top_groups), dim3(128), 0, s, m, to.roots, n_roots, b->child,
-                             b->parent, b->boxes, costs, count, arrivals);
+        hipLaunchKernelGGL(k_treelet_top<128>, dim3(top_groups), dim3(128), 0, s, m, to.roots, n_roots, b->child,
+                           b->parent, b->boxes, costs, count, arrivals);
         hipLaunchKernelGGL(k_tree_height, dim3(grid_for(m)), dim3(kBlock), 0, s, m, b->parent, th, max_depth,
                            (const uint32_t*)nullptr, 0);
         tree_depth = th;

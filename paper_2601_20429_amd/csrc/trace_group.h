@@ -40,17 +40,11 @@ namespace {
 
 constexpr int kGroup = 16;       // lanes per ray: a DPP row
 constexpr int kGroupsPerWave = 64 / kGroup;
-#ifndef GRTX_GROUP_HITS
-#define GRTX_GROUP_HITS 80
-#endif
-#ifndef GRTX_GROUP_LOOK
-#define GRTX_GROUP_LOOK 56
-#endif
 // Hit list entries per ray: 64 and 96 were slower on most cases (64 restarts 11% of the rays of
 // a 1M scene for want of room; 96 leaves room for fourteen waves on a CU instead of sixteen).
-constexpr int kGroupHits = GRTX_GROUP_HITS;
+constexpr int kGroupHits = 80;
 constexpr int kGroupKeep = kGroupHits - kGroup;
-constexpr int kGroupLook = GRTX_GROUP_LOOK;  // hits at which a list is first sorted and cut
+constexpr int kGroupLook = 56;  // hits at which a list is first sorted and cut
 // The node stack's top is a ring of kGroupRing entries in LDS; its bottom, where a step's
 // children might not fit in the ring, moves to the group's rows in device memory, kGroupMove
 // entries at a time (n_low of them are there), and comes back when the ring is empty. Beyond
@@ -58,35 +52,23 @@ constexpr int kGroupLook = GRTX_GROUP_LOOK;  // hits at which a list is first so
 // depth-first traversal's does, by at most three entries per level.
 // (A ring that throttled the steps instead, 80 entries with nothing moved out, left 17 of 64
 // lanes with a node on the 3M scene: 195 ms for the launch that takes 76.)
-#ifndef GRTX_GROUP_LEAFS
-#define GRTX_GROUP_LEAFS 64
-#endif
 constexpr int kGroupRing = 128;
 constexpr int kGroupMove = 3 * kGroup;
 constexpr int kGroupWide = 640;
 constexpr int kGroupSpill = 1024;
 static_assert(kGroupWide + 3 * kGroup + kMaxStack <= kGroupSpill, "the rows hold any stack");
-constexpr int kGroupLeaves = GRTX_GROUP_LEAFS;
+constexpr int kGroupLeaves = 64;
 // Leaves waiting (over the wave's groups) that call for a leaf step (24 to 48 measured alike),
 // and steps a group ready for its finish step waits for a second one (6: 2% slower; for two more:
 // 2% faster at 100k, 3% slower on 1M).
-#ifndef GRTX_GROUP_LEAVES
-#define GRTX_GROUP_LEAVES 32
-#endif
-#ifndef GRTX_GROUP_WAIT
-#define GRTX_GROUP_WAIT 24
-#endif
-constexpr int kGroupLeafLanes = GRTX_GROUP_LEAVES;
-constexpr int kGroupWait = GRTX_GROUP_WAIT;
+constexpr int kGroupLeafLanes = 32;
+constexpr int kGroupWait = 24;
 // A launch without a queue has one ray per group and waves to spare, so what its steps cost
 // counts by the wave's own chain: a finish step is better shared by all four groups, and none
 // waits long for it. 2,777 rays in 50k Gaussians: 142 us with the waits above, 113 with these
 // (4 steps: 123, 12: 139; at two groups, 4 steps: 125); 64x64 in 1,000: 38.4, 31.0.
 constexpr int kOnceReady = 4;
 constexpr int kOnceWait = 8;
-#ifndef GRTX_GROUP_WAVES
-#define GRTX_GROUP_WAVES 4
-#endif
 
 struct GroupLds {
   uint64_t key[kGroupHits];
@@ -220,7 +202,7 @@ constexpr uint32_t kServeBatch = 16;
 // Idle waves wait for new requests and leave once the queue closes.
 template <int DEG, bool SERVE>
 __global__ void __launch_bounds__(64)
-    __attribute__((amdgpu_waves_per_eu(GRTX_GROUP_WAVES, 8))) k_trace_group(TraceArgs Args) {
+    __attribute__((amdgpu_waves_per_eu(4, 8))) k_trace_group(TraceArgs Args) {
   __shared__ GroupLds s_group[kGroupsPerWave];
   __shared__ ServeDesc s_desc;  // serving: the wave's copy of the request its items belong to
   __shared__ uint32_t s_myj;
