@@ -2,11 +2,13 @@
 // trace.hip, whose TraceArgs it takes; sphere instances only.
 //
 // What bounds it: with sixteen waves on a CU (10 KB of LDS and 128 registers each) the vector
-// units' issue, 97% of the time on a 100k-Gaussian 800x800 frame (2,800 wave instructions a
-// ray) and 89% on 524,287 incoherent rays in 1M Gaussians. Measured against one lane per ray
-// (k_trace<16>): 64x64 rays in 1,000 Gaussians 1,390 to 31 us, 2,777 rays in 50k 2,630 to
-// 113 us, the 800x800 frame 5.14 to 2.74 ms, the 524,287 rays 21.2 to 6.96 ms, a step of 2M
-// incoherent rays and a 1920x1080 frame in 3M Gaussians, its build included, 132.7 to 67.5 ms.
+// units' issue. By the counters they are active in all of the launch's cycles on a 100k-Gaussian
+// 800x800 frame (2,470 vector instructions a ray) and on 524,287 incoherent rays in 1M Gaussians
+// (6,690), and in 82% of them in a served burst, with twelve waves. Measured against one lane per
+// ray (k_trace<16>): 64x64 rays in 1,000 Gaussians 1,390 to 31 us, 2,777 rays in 50k 2,630 to
+// 110 to 140 us by the scene drawn, the 800x800 frame 5.14 to 2.74 ms, the 524,287 rays 21.2 to
+// 6.96 ms, a step of 2M incoherent rays and a 1920x1080 frame in 3M Gaussians, its build
+// included, 132.7 to 67.5 ms.
 //
 // A ray traced by one lane is one serial chain of fetches, some 300 for a ray of a 100k
 // scene and tens of thousands for one that starts in a dense cluster; whatever the number
