@@ -103,3 +103,31 @@ def test_noalloc_without_counters(width, height, free):
         torch.cuda.synchronize()
         for key in ["rgb", "depth", "opacity", "hit_ids", "hit_counts"]:
             assert torch.equal(got[key], ref[key]), key
+
+
+@pytest.mark.parametrize("rays", [5, 20_011])
+def test_noalloc_in_a_graph(rays):
+    """Captured once (without the queue and with it) and replayed over other rays, with eager traces
+    between the replays."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    say("noalloc in a graph", rays)
+    bvh = grtx.build(grtx.SceneTensors.from_scene(inputs.cluster_scene(2, 100_000, 3), "cuda"), alpha_min=AMIN)
+    o, d = (torch.from_numpy(a).cuda() for a in inputs.incoherent_rays(6, rays))
+    out = _outputs(rays, 256)
+    del out["stats"]
+    grtx.trace_noalloc(bvh, o, d, out, T_min=1e-3)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        grtx.trace_noalloc(bvh, o, d, out, T_min=1e-3)
+    for seed in (7, 8, 9):
+        for t, a in zip((o, d), inputs.incoherent_rays(seed, rays)):
+            t.copy_(torch.from_numpy(a))
+        ref = grtx.trace(bvh, o, d, T_min=1e-3, hit_capacity=256)
+        for t in out.values():
+            t.fill_(-1)
+        graph.replay()
+        torch.cuda.synchronize()
+        for key in ["rgb", "depth", "opacity", "hit_ids", "hit_counts"]:
+            assert torch.equal(out[key], ref[key]), (seed, key)
