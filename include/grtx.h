@@ -431,7 +431,9 @@ grtx_status grtx_trace_backward(const grtx_bvh* bvh, const grtx_gaussians* g, co
  * camera, and flags the request in host memory when its last pixel is written; a request
  * published while the kernel runs joins it. The launch ends once no work has been taken
  * for `idle_exit_us` (freeing the device for other work) and the next publication starts
- * another. Results are identical to tracing each request alone with grtx_pinhole_rays +
+ * another. Beside it other streams' workgroups find room for four waves of 128 registers
+ * and 36 KB of LDS on each CU: copies and traces of sixteen lanes per ray run; builds, and
+ * traces with counters, in restart mode or over proxies, wait for the launch's end. Results are identical to tracing each request alone with grtx_pinhole_rays +
  * grtx_trace on its scene.
  * ------------------------------------------------------------------------------------- */
 typedef struct grtx_server grtx_server;

@@ -1329,10 +1329,11 @@ grtx_status launch_k(int K, const TraceArgs& a, int blocks, hipStream_t s) {
 }
 
 // Waves per CU of the serving kernel: three per SIMD, which leaves a slot of 128 registers on
-// every SIMD, so that other work on the device (copies of results, other streams' kernels) is
-// not shut out while it runs. (Its workgroups are single waves: a few whole CUs' worth of
-// them fewer leave only single slots here and there, where no workgroup of four waves fits,
-// and a copy then waits for the kernel's end.)
+// every SIMD and 36 KB of LDS, so that copies of results and other streams' light kernels (sixteen
+// lanes per ray, torch's elementwise ones and sorts) are not shut out while it runs. Heavier
+// workgroups wait for its end: a build's (its layout and its large sorts), k_trace's, a library's
+// matrix product. (Its workgroups are single waves: a few whole CUs' worth of them fewer leave only
+// single slots here and there, where no workgroup of four waves fits, and a copy then waits too.)
 constexpr int kServeWaves = 12;
 
 int serve_cus() {
